@@ -191,7 +191,7 @@ sislice_status sislice_ldlt_solve(sislice_handle *h, int64_t n, const double *LD
 /* sislice_ldlt_solve for callers that cannot allocate device memory (code under
  * HIP graph capture, tight serving loops, harnesses that forbid allocation):
  * the same arguments, kernels and results, but no call allocates, frees or
- * synchronises.  Its workspace is one fixed device array of 13 MiB per GPU (held
+ * synchronises.  Its workspace is one fixed device array of 15 MiB per GPU (held
  * from the first handle created on that GPU until the process ends), so
  * n <= 4096 (SISLICE_ERR_ARG beyond) and 1 <= nrhs <= 64.  Every call on a GPU
  * shares that GPU's array: calls that overlap on one GPU (other streams or

@@ -190,7 +190,8 @@ sislice_status plan_impl(sislice_handle* h, int64_t n64, const double* A, int64_
     auto tperm = ring.ptrs(std::vector<int*>{permB});
     auto tblk = ring.ptrs(std::vector<int*>{blkB});
     auto tLinv = ring.ptrs(std::vector<double*>{LinvB});
-    solve_prep_launch(n, 1, reinterpret_cast<const int* const*>(tip), tperm, tblk, tLD, n, tLinv, st);
+    // (the explicit inverse below starts from the diagonal-block inverses alone)
+    solve_prep_launch(n, 1, reinterpret_cast<const int* const*>(tip), tperm, tblk, tLD, n, tLinv, st, false);
   }
   inv_sqrt_diag_launch(n, LDB, n, dsc, iflag, st);
   // Explicit L^{-1} by doubling: starting from the inverted 64x64 diagonal blocks,

@@ -21,116 +21,218 @@ namespace sislice {
 
 constexpr int SB = kSolveBlock;  // 64 rows per block
 
-// perm p(i) and pivot-block flags (1: 1x1, 2: first row of 2x2, 0: second row)
-// from the documented ipiv format.
-__global__ __launch_bounds__(256) void k_solve_prep(int n, const int* const* ipivs,
-                                                    int* const* perms, int* const* blks) {
-  const int s = blockIdx.y;
-  const int* ipiv = ipivs[s];
-  int* perm = perms[s];
-  int* blk = blks[s];
-  for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x) {
-    const int v = ipiv[i];
-    perm[i] = v >= 0 ? v : -v - 1;
-    if (v >= 0) {
-      blk[i] = 1;
-    } else {
-      int run = 0;  // consecutive 2x2 rows before i
-      for (int q = i - 1; q >= 0 && ipiv[q] < 0; --q) ++run;
-      blk[i] = (run & 1) ? 0 : 2;
+// Preparation of a factor for the sweeps, one 256-thread workgroup per 64-row block b:
+//   * perm p(i) and the pivot-block flags (1: 1x1, 2: first row of a 2x2, 0: second row)
+//     of the block's rows, from the documented ipiv format;
+//   * Linv_b, the inverse of the 64x64 unit-lower diagonal block of L (rows past n:
+//     identity);
+//   * the look-ahead blocks of depth d = 1, 2,
+//       Mf^d_b = Linv_b L_{b,b-d}           (forward sweep, b >= d)
+//       Mb^d_b = Linv_b^T L_{b+d,b}^T       (backward sweep, b + d <= nblk - 1)
+//     so that a block's result is P_b - sum_d M^d_b x (block b -+ d), with P_b (the
+//     contributions of blocks further away) formed before the nearest two blocks are
+//     available.  L's structural zeros inside 2x2 pivots are applied here, so the sweeps
+//     read these blocks as plain matrices.
+// Layout per shift: column-major 64x64 blocks, Linv_b at b*SB*SB, Mf^d at
+// (2d - 1)*nblk*SB*SB and Mb^d at 2d*nblk*SB*SB.
+//
+// The work is a few hundred kflop per block, so the launch is bound by its chain of
+// dependent steps.  Everything that is a product runs on FP64 MFMA: the 16x16 diagonal
+// blocks are inverted by substitution (16 dependent steps), pairs are joined by
+// X21 = -X22 (L21 X11) to 32 and 64, and a look-ahead block is one 64x64x64 product.
+// All four look-ahead blocks of b need Linv_b only, so one launch serves them: with
+// few blocks (PARTS = 4) each product has a workgroup of its own that forms Linv_b
+// again (cheaper than waiting for it), with many blocks one workgroup forms all four.
+// One factor of order 200: 13.6 us, of order 2501: 16 us; as three launches with the sums
+// read from LDS term by term (perm and flags, inverse, products) 180 and 221 us.
+//
+// With fillZ, the launch also writes the sweeps' sentinels (below) into the fill_cols
+// columns of both result buffers: one launch less per solve of a single factor.
+constexpr unsigned long long kSentinelBits = 0x7FF4000000000001ull;
+constexpr int kPrepLd = SB + 1;  // odd LDS stride: 16 lanes along a strided index hit 16 banks
+
+__device__ __forceinline__ void prep_products(double* sB, const double* sX, bool fwd, double* out) {
+  // out(i, k) = sum_j Linv(i, j) L(j, k) (fwd) or sum_j Linv(j, i) L(k, j); the block
+  // of L at (row r, column c) sits at sB[c * kPrepLd + r].  The product is accumulated
+  // transposed (D row = k, D column = i), so the stores run along i.
+  const int l = threadIdx.x & 63, lr = l & 15, g = l >> 4, i = 16 * (threadIdx.x >> 6) + lr;
+  d4 acc[4];
+#pragma unroll
+  for (int u = 0; u < 4; ++u) acc[u] = d4{0.0, 0.0, 0.0, 0.0};
+#pragma unroll 4
+  for (int t = 0; t < 16; ++t) {
+    const int j = 4 * t + g;
+    const double x = fwd ? sX[i * kPrepLd + j] : sX[j * kPrepLd + i];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const int k = 16 * u + lr;
+      acc[u] = mfma16x16x4(fwd ? sB[k * kPrepLd + j] : sB[j * kPrepLd + k], x, acc[u]);
     }
   }
+#pragma unroll
+  for (int u = 0; u < 4; ++u)
+#pragma unroll
+    for (int r = 0; r < 4; ++r) out[i + (16 * u + g + 4 * r) * SB] = acc[u][r];
 }
 
-__device__ __forceinline__ double lval(const double* LD, long ldld, const int* blk, int row,
-                                       int col) {
-  // strictly lower L entry (row > col); inside a 2x2 pivot block the slot holds
-  // D's off-diagonal and L's entry is a structural zero
-  if (row == col + 1 && blk[col] == 2) return 0.0;
-  return LD[row + (long)col * ldld];
-}
-
-// Inverse of each 64x64 unit-lower diagonal block of L (rows past n: identity).
-// Linv layout per shift: block b at b*SB*SB, column-major 64x64.
-__global__ __launch_bounds__(64) void k_diag_inv_blk(int n, const double* const* LDs, long ldld,
-                                                     const int* const* blks, double* const* Linvs) {
-  __shared__ double sL[SB][SB + 1];
-  __shared__ double sX[SB][SB + 1];  // sX[c][i] = X(i, c)
-  const int b = blockIdx.x, s = blockIdx.y, t = threadIdx.x;
-  const double* LD = LDs[s];
-  const int* blk = blks[s];
-  const int r0 = b * SB;
-  for (int k = 0; k < SB; ++k) {
-    const int col = r0 + k, row = r0 + t;
-    double v = 0.0;
-    if (t > k && row < n) v = lval(LD, ldld, blk, row, col);
-    sL[t][k] = v;
-  }
-  __syncthreads();
-  const int c = t;
-  for (int i = 0; i < SB; ++i) {
-    double acc = (i == c) ? 1.0 : 0.0;
-    for (int k = 0; k < i; ++k) acc -= sL[i][k] * sX[c][k];
-    sX[c][i] = (i >= c) ? acc : 0.0;
-  }
-  __syncthreads();
-  double* Linv = Linvs[s] + (long)b * SB * SB;
-  for (int k = 0; k < SB; ++k) Linv[t + k * SB] = sX[k][t];
-}
-
-// Look-ahead blocks of depth d = 1, 2 (per shift, after the nblk diagonal inverses):
-//   Mf^d_b = Linv_b L_{b,b-d}           (forward sweep, b >= d)
-//   Mb^d_b = Linv_b^T L_{b+d,b}^T       (backward sweep, b + d <= nblk - 1)
-// so that a block's result is P_b - sum_d M^d_b x (block b -+ d), with P_b (the
-// contributions of blocks further away) formed before the nearest two blocks are
-// available.  L's structural zeros inside 2x2 pivots are applied here (lval), so
-// the sweeps read these blocks as plain matrices.  Layout: column-major 64x64,
-// Mf^d at (2d - 1)*nblk*SB*SB and Mb^d at 2d*nblk*SB*SB of the Linv buffer.
-__global__ __launch_bounds__(256) void k_lookahead(int n, const double* const* LDs, long ldld,
-                                                   const int* const* blks, double* const* Linvs) {
-  __shared__ double sA[SB][SB + 1];  // Linv_b(i, k)
-  __shared__ double sB[SB][SB + 1];
+template <int PARTS>
+__global__ __launch_bounds__(256) void k_solve_prep(SolvePrepArgs a) {
+  __shared__ double sL[SB * kPrepLd];  // the diagonal block, row-major; then a block of L, by columns
+  __shared__ double sX[SB * kPrepLd];  // Linv_b, row-major
+  __shared__ int sblk[SB + 1];         // pivot flags of rows r0 - 1 .. r0 + 63
   const int b = blockIdx.x, s = blockIdx.y, tid = threadIdx.x;
-  const int nblk = (n + SB - 1) / SB;
-  const double* LD = LDs[s];
-  const int* blk = blks[s];
-  double* base = Linvs[s];
-  const double* Li = base + (long)b * SB * SB;
-  const int r0 = b * SB;
-  for (int e = tid; e < SB * SB; e += 256) sA[e & 63][e >> 6] = Li[e];
-  for (int d = 1; d <= kSolveLook; ++d) {
-    // forward: sB[j][k] = L(r0 + j, r0 - d*64 + k)
-    if (b >= d) {
-      __syncthreads();
-      for (int e = tid; e < SB * SB; e += 256) {
-        const int j = e & 63, k = e >> 6, row = r0 + j;
-        sB[j][k] = (row < n) ? lval(LD, ldld, blk, row, r0 - d * SB + k) : 0.0;
+  const int part = PARTS == 4 ? (int)blockIdx.z : 0;
+  const int n = a.n, nblk = (n + SB - 1) / SB, r0 = b * SB;
+  const double* LD = a.direct ? a.LD0 : a.LD[s];
+  const int* ipiv = a.direct ? a.ipiv0 : a.ipiv[s];
+  int* perm = a.direct ? a.perm0 : a.perm[s];
+  int* blk = a.direct ? a.blk0 : a.blk[s];
+  double* Linv = a.direct ? a.Linv0 : a.Linv[s];
+  constexpr int Q = SB * SB / 256;
+  // the diagonal block and this part's first look-ahead block (rows and columns
+  // clamped: the values past n are replaced below)
+  double dg[Q], nx[Q];
+#pragma unroll
+  for (int q = 0; q < Q; ++q) {
+    const int e = tid + 256 * q;
+    dg[q] = LD[min(r0 + (e & 63), n - 1) + (long)min(r0 + (e >> 6), n - 1) * a.ldld];
+  }
+  auto prod_ok = [&](int p) { return a.look && (p < 2 ? b >= p + 1 : b + (p - 1) < nblk); };
+  auto fetch = [&](int p) {  // p = 0, 1: L_{b,b-1-p}; p = 2, 3: L_{b+p-1,b}
+    const int rr = p < 2 ? r0 : r0 + (p - 1) * SB, cc = p < 2 ? r0 - (p + 1) * SB : r0;
+#pragma unroll
+    for (int q = 0; q < Q; ++q) {
+      const int e = tid + 256 * q;
+      nx[q] = LD[min(rr + (e & 63), n - 1) + (long)(cc + (e >> 6)) * a.ldld];
+    }
+  };
+  if (prod_ok(part)) fetch(part);
+  if (tid < 64) {
+    // parity of the run of 2x2 rows that ends at row r0 - 1
+    int run0 = 0;
+    for (int pos = r0 - 1; pos >= 0; pos -= 64) {
+      const int q = pos - tid;
+      const unsigned long long neg = __ballot(q >= 0 && ipiv[max(q, 0)] < 0);
+      if (neg == ~0ull) {
+        run0 += 64;
+        continue;
       }
-      __syncthreads();
-      double* Mf = base + (long)(2 * d - 1) * nblk * SB * SB + (long)b * SB * SB;
-      for (int e = tid; e < SB * SB; e += 256) {
-        const int i = e & 63, k = e >> 6;
-        double v = 0.0;
-        for (int j = 0; j <= i; ++j) v += sA[i][j] * sB[j][k];
-        Mf[e] = v;
+      run0 += __ffsll((long long)~neg) - 1;
+      break;
+    }
+    const int i = r0 + tid;
+    const int v = i < n ? ipiv[i] : 0;
+    const unsigned long long neg = __ballot(v < 0);
+    const unsigned long long gap = ~neg & ((1ull << tid) - 1);  // 1x1 rows of the block before i
+    const int run = gap ? tid - 1 - (63 - __clzll((long long)gap)) : tid + run0;
+    const int f = v >= 0 ? 1 : ((run & 1) ? 0 : 2);
+    sblk[1 + tid] = f;
+    if (tid == 0) sblk[0] = run0 == 0 ? 1 : (((run0 - 1) & 1) ? 0 : 2);
+    if (part == 0 && i < n) {
+      perm[i] = v >= 0 ? v : -v - 1;
+      blk[i] = f;
+    }
+  }
+  if (part == 0 && a.fillZ) {
+    const double sv = __longlong_as_double((long long)kSentinelBits);
+    const int rows = min(SB, n - r0);
+    for (int e = tid; e < SB * a.fill_cols; e += 256) {
+      const long off = r0 + (e & 63) + (long)(e >> 6) * n;
+      if ((e & 63) < rows) {
+        a.fillZ[off] = sv;
+        a.fillV[off] = sv;
       }
     }
-    // backward: G = L_{b+d,b} Linv_b, sB[i][j] = L(r0 + d*64 + i, r0 + j); Mb = G^T
-    if (b + d < nblk) {
-      __syncthreads();
-      for (int e = tid; e < SB * SB; e += 256) {
-        const int ii = e & 63, j = e >> 6, row = r0 + d * SB + ii;
-        sB[ii][j] = (row < n) ? lval(LD, ldld, blk, row, r0 + j) : 0.0;
-      }
-      __syncthreads();
-      double* Mb = base + (long)(2 * d) * nblk * SB * SB + (long)b * SB * SB;
-      for (int e = tid; e < SB * SB; e += 256) {
-        const int i = e & 63, k = e >> 6;  // Mb(i, k) = G(k, i) = sum_j L(k, j) Linv(j, i)
-        double v = 0.0;
-        for (int j = i; j < SB; ++j) v += sB[k][j] * sA[j][i];
-        Mb[e] = v;
-      }
+  }
+  for (int e = tid; e < SB * kPrepLd; e += 256) sX[e] = 0.0;
+  __syncthreads();
+#pragma unroll
+  for (int q = 0; q < Q; ++q) {
+    const int e = tid + 256 * q, i = e & 63, k = e >> 6;
+    const bool zero = i <= k || r0 + i >= n || (i == k + 1 && sblk[1 + k] == 2);
+    sL[i * kPrepLd + k] = zero ? 0.0 : dg[q];
+  }
+  __syncthreads();
+  const int w = __builtin_amdgcn_readfirstlane(tid >> 6), l = tid & 63, lr = l & 15, g = l >> 4;
+  if (l < 16) {
+    // 16x16 block w: lane c forms column c of the inverse by substitution
+    double x[16];
+#pragma unroll
+    for (int i = 0; i < 16; ++i) {
+      double v = i == l ? 1.0 : 0.0;
+#pragma unroll
+      for (int k = 0; k < i; ++k) v -= sL[(16 * w + i) * kPrepLd + 16 * w + k] * x[k];
+      x[i] = v;
     }
+#pragma unroll
+    for (int i = 0; i < 16; ++i) sX[(16 * w + i) * kPrepLd + 16 * w + l] = x[i];
+  }
+  __syncthreads();
+  if (w < 2) {
+    // 16 -> 32: X21 = -X22 (L21 X11); an accumulator element r holds row g + 4r of the
+    // inner product, which is the B operand of step r of the outer one
+    const int o = 32 * w;
+    d4 t = d4{0.0, 0.0, 0.0, 0.0}, x = d4{0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+    for (int u = 0; u < 4; ++u)
+      t = mfma16x16x4(sL[(o + 16 + lr) * kPrepLd + o + 4 * u + g], sX[(o + 4 * u + g) * kPrepLd + o + lr], t);
+#pragma unroll
+    for (int u = 0; u < 4; ++u) x = mfma16x16x4(sX[(o + 16 + lr) * kPrepLd + o + 16 + 4 * u + g], t[u], x);
+#pragma unroll
+    for (int r = 0; r < 4; ++r) sX[(o + 16 + g + 4 * r) * kPrepLd + o + lr] = -x[r];
+  }
+  __syncthreads();
+  {
+    // 32 -> 64: wavefront (ti, tj) forms both inner tiles of column tj and its own tile
+    const int ti = w >> 1, tj = w & 1;
+    d4 t[2], x = d4{0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      t[h] = d4{0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+      for (int u = 0; u < 8; ++u)
+        t[h] = mfma16x16x4(sL[(32 + 16 * h + lr) * kPrepLd + 4 * u + g],
+                           sX[(4 * u + g) * kPrepLd + 16 * tj + lr], t[h]);
+    }
+#pragma unroll
+    for (int h = 0; h < 2; ++h)
+#pragma unroll
+      for (int u = 0; u < 4; ++u)
+        x = mfma16x16x4(sX[(32 + 16 * ti + lr) * kPrepLd + 32 + 16 * h + 4 * u + g], t[h][u], x);
+    __syncthreads();  // sL is free from here on
+#pragma unroll
+    for (int r = 0; r < 4; ++r) sX[(32 + 16 * ti + g + 4 * r) * kPrepLd + 16 * tj + lr] = -x[r];
+  }
+  auto stage = [&](int p) {
+    const int rr = p < 2 ? r0 : r0 + (p - 1) * SB;
+    // the entry inside a 2x2 pivot that straddles the block border
+    const bool cut = p == 0 ? sblk[0] == 2 : (p == 2 && sblk[SB] == 2);
+#pragma unroll
+    for (int q = 0; q < Q; ++q) {
+      const int e = tid + 256 * q, r = e & 63, c = e >> 6;
+      sL[c * kPrepLd + r] = (rr + r >= n || (cut && r == 0 && c == SB - 1)) ? 0.0 : nx[q];
+    }
+  };
+  if (PARTS == 4) {
+    const bool ok = prod_ok(part);
+    if (ok) stage(part);
+    __syncthreads();
+    if (part == 0)
+      for (int e = tid; e < SB * SB; e += 256) Linv[(long)b * SB * SB + e] = sX[(e & 63) * kPrepLd + (e >> 6)];
+    if (ok)
+      prep_products(sL, sX, part < 2, Linv + ((part < 2 ? 2L * part + 1 : 2L * (part - 1)) * nblk + b) * SB * SB);
+    return;
+  }
+  __syncthreads();
+  for (int e = tid; e < SB * SB; e += 256) Linv[(long)b * SB * SB + e] = sX[(e & 63) * kPrepLd + (e >> 6)];
+  for (int p = 0; p < 4; ++p) {
+    const bool ok = prod_ok(p);
+    if (ok) stage(p);
+    __syncthreads();
+    if (p < 3 && prod_ok(p + 1)) fetch(p + 1);
+    if (ok)
+      prep_products(sL, sX, p < 2, Linv + ((p < 2 ? 2L * p + 1 : 2L * (p - 1)) * nblk + b) * SB * SB);
+    __syncthreads();
   }
 }
 
@@ -153,8 +255,6 @@ __device__ __forceinline__ unsigned ticket(unsigned* ctr, unsigned nblk) {
 // per hand-off, no drain on the producer's side.  (Polling a flag with acquire
 // loads would invalidate the caches on every poll; with hundreds of waiters that
 // serialises the whole chip.)
-constexpr unsigned long long kSentinelBits = 0x7FF4000000000001ull;
-
 __device__ __forceinline__ double ld_shared_blk(const double* p) {
   return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
@@ -292,17 +392,34 @@ __global__ __launch_bounds__(256) void k_fill_sentinel(int n, int nrhs, int nshi
   }
 }
 
-// Workgroups are dispatched to the 8 XCDs round-robin by linear id.  Shift s is
-// served by the workgroups of XCD s % 8 only, so its dependency chain stays on one
-// L2.  On each XCD the shifts are interleaved by rank (local index j = rank * U + u
-// serves shift x + 8u, U = ceil(nshift / 8)), so every shift's first workgroups
-// are dispatched before any shift's later ones.  Returns -1 for the padding
-// workgroups of an unbalanced split.
-__device__ __forceinline__ int solve_shift_of(int g, int nshift) {
+// Workgroups are dispatched to the 8 XCDs round-robin by linear id.  With eight or
+// more shifts, shift s is served by the workgroups of XCD s % 8 only, so its dependency
+// chain stays on one L2, and on each XCD the shifts are interleaved by rank (local
+// index j = rank * U + u serves shift x + 8u, U = ceil(nshift / 8)), so every shift's
+// first workgroups are dispatched before any shift's later ones.  With fewer shifts
+// the XCDs are shared out (G = nshift rounded up to a power of two groups of 8 / G
+// XCDs): one XCD alone draws about an eighth of the memory bandwidth, which bounds a
+// large factor (one factor of order 8192, 8 columns: forward 466 us on one XCD and 269 us
+// on eight, backward 490 and 289).  Returns -1 for the padding workgroups of an
+// unbalanced split.
+__device__ __forceinline__ int solve_shift_of(int g, int nshift, int nblk) {
   const int x = g & 7, j = g >> 3;
+  if (nshift <= 4) {
+    const int G = nshift <= 2 ? nshift : 4;
+    const int s = x & (G - 1);
+    return (s < nshift && j * (8 / G) + x / G < nblk) ? s : -1;
+  }
   const int U = (nshift + 7) >> 3;
   const int s = x + 8 * (j % U);
   return s < nshift ? s : -1;
+}
+
+__host__ __device__ inline unsigned solve_grid(int nshift, int nblk) {
+  if (nshift <= 4) {
+    const int per = 8 / (nshift <= 2 ? (nshift < 1 ? 1 : nshift) : 4);
+    return 8u * (unsigned)((nblk + per - 1) / per);
+  }
+  return 8u * (unsigned)((nshift + 7) / 8) * (unsigned)nblk;
 }
 
 // The sweeps' 64x64 block products run on FP64 MFMA (v_mfma_f64_16x16x4).  Wavefront
@@ -378,20 +495,21 @@ __global__ __launch_bounds__(256) void k_fwd(SolveArgs a) {
   constexpr int NT = (NR + 15) / 16;
   __shared__ double sx[16 * NT * kLdx];
   const int tid = threadIdx.x, l = tid & 63, j = l & 15, g = l >> 4;
-  const int n = a.n, nrhs = a.nrhs, nblk = (n + SB - 1) / SB;
-  const int s = solve_shift_of(blockIdx.x, a.nshift);
+  const int n = a.n, nblk = (n + SB - 1) / SB;
+  const int s = solve_shift_of(blockIdx.x, a.nshift, nblk);
   if (s < 0) return;
+  const int nrhs = a.direct ? min(a.nrhs, a.nrhs_all - s * a.nrhs) : a.nrhs;
   const WaitBound wb{a.wait_err, a.wait_limit};
   const int b = (int)ticket(a.ctr + s, nblk);
-  const double* LD = a.LD[s];
-  const int* perm = a.perm[s];
-  const double* Y = a.Y[s];
-  double* Z = a.Z[s];
+  const double* LD = a.direct ? a.LD0 : a.LD[s];
+  const int* perm = a.direct ? a.perm0 : a.perm[s];
+  const double* Y = a.direct ? a.X0 + (long)s * a.nrhs * a.ldx : a.Y[s];
+  double* Z = a.direct ? a.Z0 + (long)s * a.nrhs * a.ldz : a.Z[s];
   const int r0 = b * SB;
   const int row = r0 + 16 * (tid >> 6) + j;
   for (int e = tid; e < 16 * NT * kLdx; e += 256) sx[e] = 0.0;
   // everything that does not depend on other blocks is issued first
-  const double* Lbase = a.Linv[s];
+  const double* Lbase = a.direct ? a.Linv0 : a.Linv[s];
   double inv[16];
   load_frag<false>(Lbase + (long)b * SB * SB, inv);
   d4 acc[NT];  // -(P Y - contributions so far)
@@ -474,23 +592,24 @@ __global__ __launch_bounds__(256) void k_bwd(SolveArgs a) {
   __shared__ double sx[16 * NT * kLdx];
   __shared__ double sl[SB * kLdx];  // sl[m * kLdx + k] = L(c0 + k, r0 + m) of the block in use
   const int tid = threadIdx.x, l = tid & 63, j = l & 15, g = l >> 4;
-  const int n = a.n, nrhs = a.nrhs, nblk = (n + SB - 1) / SB;
-  const int s = solve_shift_of(blockIdx.x, a.nshift);
+  const int n = a.n, nblk = (n + SB - 1) / SB;
+  const int s = solve_shift_of(blockIdx.x, a.nshift, nblk);
   if (s < 0) return;
+  const int nrhs = a.direct ? min(a.nrhs, a.nrhs_all - s * a.nrhs) : a.nrhs;
   const WaitBound wb{a.wait_err, a.wait_limit};
   const int tk = (int)ticket(a.ctr + s, nblk);
   const int b = nblk - 1 - tk;
-  const double* LD = a.LD[s];
-  const int* blk = a.blk[s];
-  const int* perm = a.perm[s];
-  const double* Z = a.Z[s];
-  double* V = a.V[s];
-  double* X = a.X[s];
+  const double* LD = a.direct ? a.LD0 : a.LD[s];
+  const int* blk = a.direct ? a.blk0 : a.blk[s];
+  const int* perm = a.direct ? a.perm0 : a.perm[s];
+  const double* Z = a.direct ? a.Z0 + (long)s * a.nrhs * a.ldz : a.Z[s];
+  double* V = a.direct ? a.V0 + (long)s * a.nrhs * a.ldz : a.V[s];
+  double* X = a.direct ? a.X0 + (long)s * a.nrhs * a.ldx : a.X[s];
   const int r0 = b * SB;
   const int rw = 16 * (tid >> 6) + j;
   const int row = r0 + rw;
   for (int e = tid; e < 16 * NT * kLdx; e += 256) sx[e] = 0.0;
-  const double* Lbase = a.Linv[s];
+  const double* Lbase = a.direct ? a.Linv0 : a.Linv[s];
   double inv[16];  // Linv_b^T
   load_frag<true>(Lbase + (long)b * SB * SB, inv);
   d4 acc[NT];  // -(D^{-1} Z_b - contributions so far)
@@ -636,25 +755,59 @@ void diag_inv_scatter_launch(int n, const double* Linv, double* Li, long ldli, h
   SL_LAUNCH_CHECK();
 }
 
-void solve_prep_launch(int n, int S, const int* const* d_ipiv, int* const* d_perm,
-                       int* const* d_blk, const double* const* d_LD, long ldld,
-                       double* const* d_Linv, hipStream_t st) {
-  SL_LAUNCH(k_solve_prep, dim3((unsigned)ceil_div(n, 256), S), dim3(256), 0, st, n, d_ipiv,
-                     d_perm, d_blk);
-  SL_LAUNCH_CHECK();
-  SL_LAUNCH(k_diag_inv_blk, dim3((unsigned)ceil_div(n, SB), S), dim3(64), 0, st, n, d_LD,
-                     ldld, (const int* const*)d_blk, d_Linv);
-  SL_LAUNCH_CHECK();
-  SL_LAUNCH(k_lookahead, dim3((unsigned)ceil_div(n, SB), S), dim3(256), 0, st, n, d_LD, ldld,
-            (const int* const*)d_blk, d_Linv);
+// One 256-thread workgroup holds 66 KB of LDS, two to a CU: 512 run at once.  A block's
+// chain is about 6 us with a workgroup per look-ahead product and 12 us with one for
+// all four, so the split pays while it still fits in one go.
+static void solve_prep_go(const SolvePrepArgs& a, int S, hipStream_t st) {
+  const unsigned nblk = (unsigned)ceil_div(a.n, SB);
+  if (a.look && (long)nblk * S <= 128)
+    SL_LAUNCH(k_solve_prep<4>, dim3(nblk, S, 4), dim3(256), 0, st, a);
+  else
+    SL_LAUNCH(k_solve_prep<1>, dim3(nblk, S, 1), dim3(256), 0, st, a);
   SL_LAUNCH_CHECK();
 }
 
+void solve_prep_launch(int n, int S, const int* const* d_ipiv, int* const* d_perm,
+                       int* const* d_blk, const double* const* d_LD, long ldld,
+                       double* const* d_Linv, hipStream_t st, bool look) {
+  SolvePrepArgs a;
+  a.n = n;
+  a.look = look ? 1 : 0;
+  a.ldld = ldld;
+  a.LD = d_LD;
+  a.ipiv = d_ipiv;
+  a.perm = d_perm;
+  a.blk = d_blk;
+  a.Linv = d_Linv;
+  solve_prep_go(a, S, st);
+}
+
+// The sweeps of a.nshift shifts (or groups of right-hand sides) whose result buffers
+// hold sentinels.
+static void solve_sweeps(const SolveArgs& a, hipStream_t st, int mode) {
+  const unsigned grid = solve_grid(a.nshift, (int)ceil_div(a.n, SB));
+  if (mode == 0 || mode == 1) {
+    if (a.nrhs <= 8)
+      SL_LAUNCH(k_fwd<8>, dim3(grid), dim3(256), 0, st, a);
+    else if (a.nrhs <= 16)
+      SL_LAUNCH(k_fwd<16>, dim3(grid), dim3(256), 0, st, a);
+    else
+      SL_LAUNCH(k_fwd<kSolveMaxRhs>, dim3(grid), dim3(256), 0, st, a);
+    SL_LAUNCH_CHECK();
+  }
+  if (mode == 0 || mode == 2) {
+    if (a.nrhs <= 8)
+      SL_LAUNCH(k_bwd<8>, dim3(grid), dim3(256), 0, st, a);
+    else if (a.nrhs <= 16)
+      SL_LAUNCH(k_bwd<16>, dim3(grid), dim3(256), 0, st, a);
+    else
+      SL_LAUNCH(k_bwd<kSolveMaxRhs>, dim3(grid), dim3(256), 0, st, a);
+    SL_LAUNCH_CHECK();
+  }
+}
+
 void solve_launch(SolveArgs a, hipStream_t st, int mode) {
-  const int nblk = (int)ceil_div(a.n, SB);
   SL_CHECK_ARG(a.nrhs >= 0 && a.nrhs <= kSolveMaxRhs, "too many right-hand sides for one sweep");
-  // 8 XCDs x ceil(nshift / 8) shift slots x nblk blocks (see solve_shift_of)
-  const unsigned grid = (unsigned)(8 * ceil_div(a.nshift, 8) * nblk);
   sislice_handle* ph = current_handle();
   a.wait_err = wait_flag(ph);
   a.wait_limit = ph->wait_limit;
@@ -665,21 +818,59 @@ void solve_launch(SolveArgs a, hipStream_t st, int mode) {
             dim3(256), 0, st, a.n, a.nrhs, a.nshift, (mode == 0 || mode == 1) ? a.Z : nullptr,
             (mode == 0 || mode == 2) ? a.V : nullptr, a.ldz);
   SL_LAUNCH_CHECK();
-  const bool small = a.nrhs <= 8;
-  if (mode == 0 || mode == 1) {
-    if (small)
-      SL_LAUNCH(k_fwd<8>, dim3(grid), dim3(256), 0, st, a);
-    else
-      SL_LAUNCH(k_fwd<kSolveMaxRhs>, dim3(grid), dim3(256), 0, st, a);
-    SL_LAUNCH_CHECK();
-  }
-  if (mode == 0 || mode == 2) {
-    if (small)
-      SL_LAUNCH(k_bwd<8>, dim3(grid), dim3(256), 0, st, a);
-    else
-      SL_LAUNCH(k_bwd<kSolveMaxRhs>, dim3(grid), dim3(256), 0, st, a);
-    SL_LAUNCH_CHECK();
-  }
+  solve_sweeps(a, st, mode);
+  prof_end(ph, tk);
+}
+
+// X <- C^{-1} X through one factor, everything in three launches and no table: the
+// preparation (which also fills the sentinels), then the two sweeps over all
+// right-hand sides, in groups of kSolveGroup columns that run side by side as if they
+// were shifts of one launch.  A sweep is bound by its chain of row blocks, whatever its
+// width, so the groups cost little more than one.  A group is one MFMA tile wide: 64
+// columns at order 2501 take 228 us a call in groups of 16, 230 in groups of 8 (which
+// read L twice as often) and 337 in groups of 32 (two tiles a step); two launches of 32
+// one after the other, with their uploads and waits, took 929 us.  One column at order
+// 200: 213 us a call before, 32 us now.
+void solve_single_launch(int n, const double* LD, long ldld, const int* ipiv, int nrhs, double* X,
+                         long ldx, const SolveScratch& w, hipStream_t st) {
+  SL_CHECK_ARG(nrhs >= 1 && nrhs <= kSolveApiRhs, "too many right-hand sides");
+  sislice_handle* ph = current_handle();
+  SolvePrepArgs p;
+  p.n = n;
+  p.look = 1;
+  p.ldld = ldld;
+  p.direct = 1;
+  p.LD0 = LD;
+  p.ipiv0 = ipiv;
+  p.perm0 = w.perm;
+  p.blk0 = w.blk;
+  p.Linv0 = w.Linv;
+  p.fillZ = w.Z;
+  p.fillV = w.V;
+  p.fill_cols = nrhs;
+  solve_prep_go(p, 1, st);
+  SolveArgs a;
+  a.n = n;
+  a.nrhs = std::min(nrhs, kSolveGroup);
+  a.nshift = (int)ceil_div(nrhs, a.nrhs);
+  a.nrhs_all = nrhs;
+  a.direct = 1;
+  a.ldld = ldld;
+  a.LD0 = LD;
+  a.perm0 = w.perm;
+  a.blk0 = w.blk;
+  a.Linv0 = w.Linv;
+  a.X0 = X;
+  a.ldx = ldx;
+  a.ldy = ldx;
+  a.Z0 = w.Z;
+  a.V0 = w.V;
+  a.ldz = n;
+  a.ctr = w.ctr;
+  a.wait_err = wait_flag(ph);
+  a.wait_limit = ph->wait_limit;
+  const int tk = prof_begin(ph, kProfSolve);
+  solve_sweeps(a, st, 0);
   prof_end(ph, tk);
 }
 

@@ -6,7 +6,9 @@
 namespace sislice {
 
 constexpr int kSolveBlock = 64;    // rows per dependency block
-constexpr int kSolveMaxRhs = 32;   // right-hand sides per launch
+constexpr int kSolveMaxRhs = 32;   // right-hand sides of one shift per launch
+constexpr int kSolveApiRhs = 64;   // right-hand sides of one call through a single factor
+constexpr int kSolveGroup = 16;    // its columns per group: one MFMA tile
 
 struct SolveArgs {
   int n = 0, nshift = 0, nrhs = 0;
@@ -24,6 +26,17 @@ struct SolveArgs {
   double* const* V = nullptr;           // scratch n x nrhs (ldz); the backward result
   long ldz = 0;
   unsigned* ctr = nullptr;              // nshift ticket counters, zero-initialised once
+  // direct: one factor for the whole launch, "shift" s is its s-th group of nrhs
+  // right-hand sides (the last group holds what is left of nrhs_all); the device tables
+  // above are not read, input and output are X0 (ldx), scratch Z0 and V0 (ldz)
+  int direct = 0, nrhs_all = 0;
+  const double* LD0 = nullptr;
+  const int* perm0 = nullptr;
+  const int* blk0 = nullptr;
+  const double* Linv0 = nullptr;
+  double* X0 = nullptr;
+  double* Z0 = nullptr;
+  double* V0 = nullptr;
   int applyD = 1;                       // backward sweep applies D^{-1} first (0: identity)
   unsigned* wait_err = nullptr;         // raised when a hand-off wait exceeds wait_limit polls
   unsigned wait_limit = 0;              // (both set by solve_launch from the handle)
@@ -33,9 +46,44 @@ struct SolveArgs {
 // mode 1: Z = L^{-1} P Y only (forward sweep; the result is left in Z)
 // mode 2: X = P^T L^{-T} [D^{-1}] Z only (backward sweep reading Z)
 
+// Preparation of the factors for the sweeps; `look` false forms perm, blk and the
+// diagonal-block inverses only.
+struct SolvePrepArgs {
+  int n = 0, look = 1;
+  long ldld = 0;
+  const double* const* LD = nullptr;
+  const int* const* ipiv = nullptr;
+  int* const* perm = nullptr;
+  int* const* blk = nullptr;
+  double* const* Linv = nullptr;
+  // direct: one factor, given here instead of in device tables
+  int direct = 0;
+  const double* LD0 = nullptr;
+  const int* ipiv0 = nullptr;
+  int* perm0 = nullptr;
+  int* blk0 = nullptr;
+  double* Linv0 = nullptr;
+  // sentinels written into fill_cols columns (ld n) of both, when given
+  double* fillZ = nullptr;
+  double* fillV = nullptr;
+  int fill_cols = 0;
+};
+
 void solve_prep_launch(int n, int S, const int* const* d_ipiv, int* const* d_perm,
                        int* const* d_blk, const double* const* d_LD, long ldld,
-                       double* const* d_Linv, hipStream_t st);
+                       double* const* d_Linv, hipStream_t st, bool look = true);
+// Scratch of solve_single_launch: perm, blk [n], Linv [solve_linv_size(n)], Z and V
+// n x nrhs, and one zero ticket counter per group.
+struct SolveScratch {
+  int* perm = nullptr;
+  int* blk = nullptr;
+  double* Linv = nullptr;
+  double* Z = nullptr;
+  double* V = nullptr;
+  unsigned* ctr = nullptr;
+};
+void solve_single_launch(int n, const double* LD, long ldld, const int* ipiv, int nrhs, double* X,
+                         long ldx, const SolveScratch& w, hipStream_t st);
 void solve_launch(SolveArgs a, hipStream_t st, int mode = 0);
 // Scatter the 64x64 diagonal-block inverses (layout of solve_prep_launch's Linv)
 // onto the block diagonal of an n x n matrix.

@@ -17,58 +17,17 @@ extern "C" sislice_status sislice_ldlt_solve(sislice_handle* h, int64_t n, const
     z.take<int>(n);
     z.take<int>(n);
     z.take<double>(solve_linv_size(n));
-    z.take<double>((size_t)n * kSolveMaxRhs);
-    z.take<double>((size_t)n * kSolveMaxRhs);
-    z.take<void*>(16);
+    z.take<double>((size_t)n * nrhs);
+    z.take<double>((size_t)n * nrhs);
     Carver c(ws_get(h, kBufSolve, z.off));
-    int* perm = c.take<int>(n);
-    int* blk = c.take<int>(n);
-    double* Linv = c.take<double>(solve_linv_size(n));
-    double* Zs = c.take<double>((size_t)n * kSolveMaxRhs);
-    double* Vs = c.take<double>((size_t)n * kSolveMaxRhs);
-    void** tab = c.take<void*>(16);
-    unsigned* sync = sync_words(h, 64);
-    // tables: LD, ipiv, perm, blk, Linv, Z, V, Y/X (filled per chunk)
-    void** ht = static_cast<void**>(host_stage(h, sizeof(void*) * 16));
-    ht[0] = const_cast<double*>(LD);
-    ht[1] = const_cast<int32_t*>(ipiv);
-    ht[2] = perm;
-    ht[3] = blk;
-    ht[4] = Linv;
-    ht[5] = Zs;
-    ht[6] = Vs;
-    SL_HIP(hipMemcpyAsync(tab, ht, sizeof(void*) * 7, hipMemcpyHostToDevice, h->stream));
-    solve_prep_launch((int)n, 1, reinterpret_cast<const int* const*>(tab + 1),
-                      reinterpret_cast<int* const*>(tab + 2), reinterpret_cast<int* const*>(tab + 3),
-                      reinterpret_cast<const double* const*>(tab + 0), ldld,
-                      reinterpret_cast<double* const*>(tab + 4), h->stream);
-    for (int64_t c0 = 0; c0 < nrhs; c0 += kSolveMaxRhs) {
-      const int nr = (int)std::min<int64_t>(kSolveMaxRhs, nrhs - c0);
-      // one device table slot per chunk so earlier launches keep their pointers
-      double** dx = reinterpret_cast<double**>(tab + 8 + (c0 / kSolveMaxRhs) % 2);
-      double* xp = X + c0 * ldx;
-      SL_HIP(hipMemcpyAsync(dx, &xp, sizeof(void*), hipMemcpyHostToDevice, h->stream));
-      SL_HIP(hipStreamSynchronize(h->stream));
-      SolveArgs a;
-      a.n = (int)n;
-      a.nshift = 1;
-      a.nrhs = nr;
-      a.epoch = next_epoch(h);
-      a.LD = reinterpret_cast<const double* const*>(tab + 0);
-      a.ldld = ldld;
-      a.perm = reinterpret_cast<const int* const*>(tab + 2);
-      a.blk = reinterpret_cast<const int* const*>(tab + 3);
-      a.Linv = reinterpret_cast<const double* const*>(tab + 4);
-      a.Y = dx;
-      a.ldy = ldx;
-      a.X = dx;
-      a.ldx = ldx;
-      a.Z = reinterpret_cast<double* const*>(tab + 5);
-      a.V = reinterpret_cast<double* const*>(tab + 6);
-      a.ldz = n;
-      a.ctr = sync;
-      solve_launch(a, h->stream);
-    }
+    SolveScratch w;
+    w.perm = c.take<int>(n);
+    w.blk = c.take<int>(n);
+    w.Linv = c.take<double>(solve_linv_size(n));
+    w.Z = c.take<double>((size_t)n * nrhs);
+    w.V = c.take<double>((size_t)n * nrhs);
+    w.ctr = sync_words(h, 64);
+    solve_single_launch((int)n, LD, ldld, ipiv, (int)nrhs, X, ldx, w, h->stream);
     return SISLICE_OK;
   } catch (const Error& e) {
     std::fprintf(stderr, "sislice: %s\n", e.what());

@@ -1,12 +1,11 @@
 // sislice_ldlt_solve_noalloc: the shift-invert solve of sislice_ldlt_solve for
 // callers that cannot allocate (code under graph capture, tight serving loops).
 //
-// It runs the same kernels as sislice_ldlt_solve (the preparation of the
+// It runs the same launches as sislice_ldlt_solve (the preparation of the
 // diagonal-block inverses and look-ahead blocks, then the forward and backward
 // sweeps), but every buffer beyond the caller's factors and right-hand sides
 // lives in one file-scope device array of fixed size.  Nothing is allocated:
-// no workspace growth, no pinned staging, no pointer tables uploaded from the
-// host (a one-thread kernel writes them into the array), no synchronisation.
+// no workspace growth, no pinned staging, no synchronisation.
 //
 // Each GPU holds its own copy of the array; its address on a device is taken
 // once, when the first handle on that device is created, and used from then
@@ -20,10 +19,10 @@
 #include "handle.hpp"
 #include "solve.hpp"
 
-// Largest order the array is sized for (right-hand sides up to 64, in chunks of
-// 32): about 12.6 MB at n = 4096.
+// Largest order the array is sized for (right-hand sides up to 64): 14.1 MiB at
+// n = 4096.
 constexpr int64_t kNoallocMaxN = 4096;
-constexpr size_t kScratchBytes = 13u << 20;
+constexpr size_t kScratchBytes = 15u << 20;
 
 static __device__ __align__(256) unsigned char scratch[kScratchBytes];
 
@@ -35,7 +34,7 @@ std::mutex g_scratch_mu;
 std::vector<void*> g_scratch_addr;  // per device: device address of `scratch`
 
 struct Layout {
-  size_t perm, blk, linv, z, v, tab, ctr, total;
+  size_t perm, blk, linv, z, v, ctr, total;
 };
 
 // byte offset of the next 256-aligned region of `bytes`
@@ -52,31 +51,14 @@ Layout layout(int64_t n) {
   L.perm = place(off, sizeof(int) * (size_t)n);
   L.blk = place(off, sizeof(int) * (size_t)n);
   L.linv = place(off, sizeof(double) * solve_linv_size(n));
-  L.z = place(off, sizeof(double) * (size_t)n * kSolveMaxRhs);
-  L.v = place(off, sizeof(double) * (size_t)n * kSolveMaxRhs);
-  L.tab = place(off, sizeof(void*) * 16);
+  L.z = place(off, sizeof(double) * (size_t)n * kSolveApiRhs);
+  L.v = place(off, sizeof(double) * (size_t)n * kSolveApiRhs);
   L.ctr = place(off, sizeof(unsigned) * 64);
   L.total = off;
   return L;
 }
 
-// Pointer tables of the single-shift launches (LD, ipiv, perm, blk, Linv, Z, V,
-// then one X slot per right-hand-side chunk) and the cleared ticket counter.
-__global__ void k_noalloc_tables(void** tab, const double* LD, const int32_t* ipiv, int* perm,
-                                 int* blk, double* Linv, double* Z, double* V, double* X0,
-                                 double* X1, unsigned* ctr) {
-  if (threadIdx.x != 0) return;
-  tab[0] = const_cast<double*>(LD);
-  tab[1] = const_cast<int32_t*>(ipiv);
-  tab[2] = perm;
-  tab[3] = blk;
-  tab[4] = Linv;
-  tab[5] = Z;
-  tab[6] = V;
-  tab[8] = X0;
-  tab[9] = X1;
-  ctr[0] = 0u;
-}
+__global__ void k_noalloc_clear(unsigned* ctr) { ctr[threadIdx.x] = 0u; }
 
 }  // namespace
 
@@ -112,45 +94,22 @@ extern "C" sislice_status sislice_ldlt_solve_noalloc(sislice_handle* h, int64_t 
     const Layout L = layout(n);
     SL_CHECK_ARG(L.total <= kScratchBytes, "scratch layout exceeds the array");
     char* base = static_cast<char*>(h->scratch);
-    void** tab = reinterpret_cast<void**>(base + L.tab);
-    unsigned* ctr = reinterpret_cast<unsigned*>(base + L.ctr);
+    SolveScratch w;
+    w.perm = reinterpret_cast<int*>(base + L.perm);
+    w.blk = reinterpret_cast<int*>(base + L.blk);
+    w.Linv = reinterpret_cast<double*>(base + L.linv);
+    w.Z = reinterpret_cast<double*>(base + L.z);
+    w.V = reinterpret_cast<double*>(base + L.v);
+    w.ctr = reinterpret_cast<unsigned*>(base + L.ctr);
     struct NoProf {  // no timing events here: creating them may allocate
       sislice_handle* h;
       bool was;
       ~NoProf() { h->prof = was; }
     } np{h, h->prof};
     h->prof = false;
-    hipLaunchKernelGGL(k_noalloc_tables, dim3(1), dim3(64), 0, h->stream, tab, LD, ipiv,
-                       reinterpret_cast<int*>(base + L.perm), reinterpret_cast<int*>(base + L.blk),
-                       reinterpret_cast<double*>(base + L.linv), reinterpret_cast<double*>(base + L.z),
-                       reinterpret_cast<double*>(base + L.v), X,
-                       X + (nrhs > kSolveMaxRhs ? kSolveMaxRhs * ldx : 0), ctr);
+    hipLaunchKernelGGL(k_noalloc_clear, dim3(1), dim3(64), 0, h->stream, w.ctr);
     SL_LAUNCH_CHECK();
-    solve_prep_launch((int)n, 1, reinterpret_cast<const int* const*>(tab + 1),
-                      reinterpret_cast<int* const*>(tab + 2), reinterpret_cast<int* const*>(tab + 3),
-                      reinterpret_cast<const double* const*>(tab + 0), ldld,
-                      reinterpret_cast<double* const*>(tab + 4), h->stream);
-    for (int64_t c0 = 0; c0 < nrhs; c0 += kSolveMaxRhs) {
-      double** dx = reinterpret_cast<double**>(tab + 8 + c0 / kSolveMaxRhs);
-      SolveArgs a;
-      a.n = (int)n;
-      a.nshift = 1;
-      a.nrhs = (int)std::min<int64_t>(kSolveMaxRhs, nrhs - c0);
-      a.LD = reinterpret_cast<const double* const*>(tab + 0);
-      a.ldld = ldld;
-      a.perm = reinterpret_cast<const int* const*>(tab + 2);
-      a.blk = reinterpret_cast<const int* const*>(tab + 3);
-      a.Linv = reinterpret_cast<const double* const*>(tab + 4);
-      a.Y = dx;
-      a.ldy = ldx;
-      a.X = dx;
-      a.ldx = ldx;
-      a.Z = reinterpret_cast<double* const*>(tab + 5);
-      a.V = reinterpret_cast<double* const*>(tab + 6);
-      a.ldz = n;
-      a.ctr = ctr;
-      solve_launch(a, h->stream);
-    }
+    solve_single_launch((int)n, LD, ldld, ipiv, (int)nrhs, X, ldx, w, h->stream);
     return SISLICE_OK;
   } catch (const Error& e) {
     std::fprintf(stderr, "sislice: %s\n", e.what());
