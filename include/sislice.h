@@ -492,8 +492,8 @@ sislice_status sislice_dos_plan(const double *theta, const double *zeta2, int32_
  * random draw of the library. */
 uint64_t sislice_splitmix64(uint64_t seed, uint64_t i);
 
-/* Small dense symmetric eigensolver used for the projected problems of
- * Rayleigh-Ritz (Sec. 2.1): `batch` matrices of order m <= 112, device,
+/* Small dense symmetric eigensolver (Jacobi rotations): `batch` matrices of order
+ * m <= 112, device,
  * column-major with leading dimension lda, lower triangle read.  W device
  * double[batch*m] eigenvalues ascending; V device batch*(m x m) eigenvectors
  * (leading dimension m).  The rotations are recorded in a workspace of the
@@ -504,8 +504,7 @@ uint64_t sislice_splitmix64(uint64_t seed, uint64_t i);
 sislice_status sislice_sym_eig(sislice_handle *h, int32_t m, int32_t batch, const double *A,
                                int64_t lda, double *W, double *V);
 
-/* The same solver for a batch of matrices of different orders, as the solve
- * path launches it: matrix b, of order m[b] (host int32, 0 <= m[b] <= mmax <=
+/* The same solver for a batch of matrices of different orders: matrix b, of order m[b] (host int32, 0 <= m[b] <= mmax <=
  * 112; 0 skips it), is the leading m[b] x m[b] block at A + b*lda*mmax (device,
  * column-major, leading dimension lda >= mmax, lower triangle read).  Its
  * eigenvalues go to W + b*mmax (ascending) and its eigenvectors to
@@ -514,6 +513,15 @@ sislice_status sislice_sym_eig(sislice_handle *h, int32_t m, int32_t batch, cons
 sislice_status sislice_sym_eig_var(sislice_handle *h, int32_t batch, const int32_t *m,
                                    int32_t mmax, const double *A, int64_t lda, double *W,
                                    double *V);
+
+/* The eigensolver of the solve path's projected problems (Rayleigh-Ritz and the Lanczos
+ * matrices, Sec. 2.1): Householder tridiagonalisation and divide and conquer.  Arguments
+ * as sislice_sym_eig_var.  Eigenvalues and residuals are accurate to rounding of the
+ * matrix's norm, the eigenvectors orthogonal to working precision.  The reflectors
+ * are kept in a workspace of the handle (100 KB per matrix of order 112, at most
+ * 64 MB; larger batches run in chunks). */
+sislice_status sislice_proj_eig(sislice_handle *h, int32_t batch, const int32_t *m, int32_t mmax,
+                                const double *A, int64_t lda, double *W, double *V);
 
 #ifdef __cplusplus
 }

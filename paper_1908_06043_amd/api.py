@@ -141,6 +141,16 @@ def sym_eig_var(mats):
     """Eigen-decompositions of a batch of small symmetric matrices of different orders
     (a list of square tensors on one device, orders <= 112), in one launch.  Returns a
     list of (W, V) with W ascending and V[:, j] the eigenvector of W[j]."""
+    return _eig_var("sislice_sym_eig_var", mats)
+
+
+def proj_eig(mats):
+    """The same by the eigensolver of the solve path's projected problems (divide and
+    conquer; accurate to rounding of each matrix's norm)."""
+    return _eig_var("sislice_proj_eig", mats)
+
+
+def _eig_var(entry, mats):
     orders = [int(x.shape[0]) for x in mats]
     batch, mmax = len(mats), max(orders) if mats else 0
     dev = mats[0].device
@@ -151,9 +161,9 @@ def sym_eig_var(mats):
     V = torch.zeros((batch, mmax, mmax), dtype=torch.float64, device=dev)   # V[b, j, i] = vec j, comp i
     m = np.ascontiguousarray(np.asarray(orders, dtype=np.int32))
     lib = _lib.load()
-    st = lib.sislice_sym_eig_var(handle(dev.index), batch, m.ctypes.data_as(_lib.c_int32_p), mmax,
+    st = getattr(lib, entry)(handle(dev.index), batch, m.ctypes.data_as(_lib.c_int32_p), mmax,
                                  Ap.data_ptr(), mmax, W.data_ptr(), V.data_ptr())
-    _check(st, "sislice_sym_eig_var")
+    _check(st, entry)
     return [(W[b, :orders[b]], V[b, :orders[b], :orders[b]].t()) for b in range(batch)]
 
 

@@ -1290,7 +1290,10 @@ sislice_status solve_impl(sislice_handle* h, int64_t n64, const double* A, int64
       e.W = ring.ptrs(pO);
       e.V = ring.ptrs(pY);
       e.ldv = kEigMax;
-      eig_launch(e, NC, cmax, st);
+      // S H S is diagonal to about the residuals.  Jacobi rotations keep the relative accuracy
+      // of such small couplings (and need few sweeps); from a general reduction neighbouring
+      // vectors of different probes come out ten times less orthogonal.
+      eig_jacobi_launch(e, NC, cmax, st);
       gemm(c, false, false, cnts, cnts, cnts, cc(pS), kEigMax, cc(pY), kEigMax, pY2, kEigMax, 1.0, 0.0);
       std::vector<const double*> cY(pY2.begin(), pY2.end());
       gemm(c, false, false, rowsn, cnts, cnts, cX, n, cY, kEigMax,

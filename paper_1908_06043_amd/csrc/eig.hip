@@ -1,6 +1,8 @@
-// Small dense symmetric eigensolver for the projected problems of Rayleigh-Ritz
-// (Section 2.1: (V^T A V) Q = Q Omega) and of the Lanczos tridiagonal-block
-// matrices.
+// Small dense symmetric eigensolver by Jacobi rotations: the public batched solver and the
+// final Rayleigh-Ritz step, whose matrix is diagonal to about the residuals (Section 2.1:
+// (V^T A V) Q = Q Omega).  Rotations keep the relative accuracy of small couplings and
+// small eigenvalues.  The full matrices of the iteration go to eig_dc.hip, which takes a
+// quarter of the time there.
 //
 // Design (gfx950): two kernels per batch.
 //  k_syevj: one 1024-thread workgroup per matrix, the lower triangle of A in LDS
@@ -412,7 +414,7 @@ __global__ __launch_bounds__(64 * kVecWaves) void k_syevj_vecs(EigArgs a,
   }
 }
 
-size_t eig_lds_bytes(int mmax) {
+static size_t eig_lds_bytes(int mmax) {
   const int M = mmax + (mmax & 1);
   const int h = M / 2;
   const size_t npk = (size_t)M * (M + 1);
@@ -423,7 +425,7 @@ size_t eig_lds_bytes(int mmax) {
 // stays near this size however large the batch is.
 constexpr size_t kRotChunkBytes = size_t(256) << 20;
 
-void eig_launch(const EigArgs& a, int batch, int mmax, hipStream_t st) {
+void eig_jacobi_launch(const EigArgs& a, int batch, int mmax, hipStream_t st) {
   static std::once_flag attr;
   std::call_once(attr, [] {
     SL_HIP(hipFuncSetAttribute((const void*)k_syevj, hipFuncAttributeMaxDynamicSharedMemorySize,

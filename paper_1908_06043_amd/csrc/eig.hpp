@@ -5,7 +5,7 @@
 
 namespace sislice {
 
-constexpr int kEigMax = 112;  // largest order of the one-workgroup Jacobi solver (A in LDS)
+constexpr int kEigMax = 112;  // largest order of the one-workgroup solvers (LDS)
 
 struct EigArgs {
   const int* m = nullptr;              // device [batch] orders (<= kEigMax; 0 = skip)
@@ -14,10 +14,12 @@ struct EigArgs {
   double* const* W = nullptr;          // eigenvalues ascending
   double* const* V = nullptr;          // eigenvectors, column j for W[j]
   long ldv = 0;
-  int max_sweeps = 40;
+  int max_sweeps = 40;                 // Jacobi only
 };
 
-size_t eig_lds_bytes(int mmax);
+// Divide and conquer: Lanczos matrices, B-Gram matrices and norm estimates.
 void eig_launch(const EigArgs& a, int batch, int mmax, hipStream_t st);
+// Jacobi: the public batched solver, and nearly diagonal Rayleigh-Ritz matrices.
+void eig_jacobi_launch(const EigArgs& a, int batch, int mmax, hipStream_t st);
 
 }  // namespace sislice

@@ -15,7 +15,7 @@ struct sislice_handle {
     void* ptr = nullptr;
     size_t cap = 0;
   };
-  Buf bufs[10];
+  Buf bufs[11];
   void* host_stage = nullptr;  // pinned staging for small host<->device records
   size_t host_cap = 0;
   unsigned* sync = nullptr;  // epoch flags and ticket counters of the persistent solves
@@ -103,7 +103,8 @@ enum BufId {
   kBufLanczos = 6,
   kBufRing = 7,
   kBufAdjoint = 8,
-  kBufEigRot = 9
+  kBufEigRot = 9,
+  kBufEigRefl = 10
 };
 
 // Returns a device buffer of at least `bytes`, reallocating (contents lost) if needed.

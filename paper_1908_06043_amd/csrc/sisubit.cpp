@@ -184,7 +184,7 @@ SubspaceOut subspace_probes(Ctx& c, int n, const double* Af, const double* Bf,
     e.W = ring.ptrs(pick(act, [&](int j) { return om + (size_t)j * k; }));
     e.V = ring.ptrs(pick(act, [&](int j) { return small(Y, j); }));
     e.ldv = k;
-    eig_launch(e, (int)na, k, st);
+    eig_jacobi_launch(e, (int)na, k, st);  // nearly diagonal once the basis has converged
     const auto cY = pick(act, [&](int j) { return (const double*)small(Y, j); });
     gemm(c, false, false, mn, mk, mk, cV, n, cY, k, pick(act, [&](int j) { return blk(W, j); }), n,
          1.0, 0.0);  // X = V Y
