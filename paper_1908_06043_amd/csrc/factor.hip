@@ -84,8 +84,11 @@ __global__ __launch_bounds__(256) void k_shift_form(int n, int S, const double* 
 }
 
 __global__ __launch_bounds__(256) void k_factor_init(int n, FactorState* states, int* const* perms,
-                                                     int* const* swps) {
+                                                     int* const* swps, unsigned long long* teams) {
   const int s = blockIdx.y;
+  // no mailbox word carries a tag of this factorization yet
+  for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < kTeamWords; i += gridDim.x * blockDim.x)
+    teams[(long)s * kTeamWords + i] = 0;
   int* perm = perms[s];
   int* sw = swps[s];
   for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x) {
@@ -300,7 +303,7 @@ __global__ __launch_bounds__(256) void k_fast_commit(int n, double* const* LDs, 
                                                      const double* const* Wps, long ldw,
                                                      const double* const* auxs, int* const* blks,
                                                      int* const* colpanels, FactorState* states,
-                                                     int nb) {
+                                                     unsigned long long* teams, int nb) {
   __shared__ int js;
   const int s = blockIdx.y, c = blockIdx.x, tid = threadIdx.x;
   const FactorState st = states[s];
@@ -345,6 +348,8 @@ __global__ __launch_bounds__(256) void k_fast_commit(int n, double* const* LDs, 
     const bool negd = acc && Dv[tid] < 0.0;
     const unsigned long long negm = __ballot(negd), posm = __ballot(acc && !negd);
     if (tid == 0) {
+      teams[(long)s * kTeamWords] = 0;  // the pivoting panel's workgroups gather anew
+      teams[(long)s * kTeamWords + 1] = 0;
       states[s].jstart = jst;
       states[s].neg += __popcll(negm);
       states[s].pos += __popcll(posm);
@@ -352,14 +357,17 @@ __global__ __launch_bounds__(256) void k_fast_commit(int n, double* const* LDs, 
   }
 }
 
-template <bool PIVOT>
-__global__ __launch_bounds__(1024) void k_bk_panel(int n, double* const* LDs, long ldld,
-                                                   double* const* Wps, long ldw, int* const* perms,
-                                                   int* const* swps, int* const* blks,
-                                                   int* const* colpanels, int* const* pstarts,
-                                                   FactorState* states, int nb, int nbpiv) {
-  constexpr int NT = 1024, NW = NT / 64;
-  const int s = blockIdx.x, tid = threadIdx.x;
+// The pivoting panel on one workgroup, for any number of rows.  Each column of S is
+// formed from the panel's L in memory, so a column costs one CU's reads of (n - k) j
+// doubles (4 us at order 4096); k_bk_team below keeps L in registers.
+template <bool PIVOT, int NT>
+__device__ __forceinline__ void bk_panel_rows(int n, double* const* LDs, long ldld,
+                                              double* const* Wps, long ldw, int* const* perms,
+                                              int* const* swps, int* const* blks,
+                                              int* const* colpanels, int* const* pstarts,
+                                              FactorState* states, int nb, int nbpiv, int s) {
+  constexpr int NW = NT / 64;
+  const int tid = threadIdx.x;
   FactorState* st = states + s;
   double* __restrict__ LD = LDs[s];
   double* __restrict__ Wp = Wps[s];
@@ -636,6 +644,643 @@ __global__ __launch_bounds__(1024) void k_bk_panel(int n, double* const* LDs, lo
     st->pos += pos;
     st->jstart = 0;
     pstart[P] = k0;
+  }
+}
+
+template <bool PIVOT>
+__global__ __launch_bounds__(1024) void k_bk_panel(int n, double* const* LDs, long ldld,
+                                                   double* const* Wps, long ldw, int* const* perms,
+                                                   int* const* swps, int* const* blks,
+                                                   int* const* colpanels, int* const* pstarts,
+                                                   FactorState* states, int nb, int nbpiv) {
+  bk_panel_rows<PIVOT, 1024>(n, LDs, ldld, Wps, ldw, perms, swps, blks, colpanels, pstarts, states,
+                             nb, nbpiv, blockIdx.x);
+}
+
+// The pivoting panel with the panel's L in registers: every thread holds one row, a
+// workgroup NT rows, and the rows of a shift are spread over a team of workgroups.
+//
+// What bounds it: the chain of pivot decisions.  A column of S is one multiply-add per
+// panel column and thread (no memory but the raw column, loaded two columns ahead); then
+// the team agrees on the pivot.  A row interchange moves no data between threads: the two
+// rows' threads exchange labels (the row a thread stands for), and L is written once, at
+// the end, under the final labels.  A thread that becomes a pivot retires.  The W rows of
+// the panel's own NB rows, which supply the multipliers of coming columns, are replicated
+// in every workgroup's LDS.
+//
+// The team's exchanges.  Per column each workgroup publishes its largest entry and its row,
+// the first one also the new W column of the panel's rows, and each one the W of its best
+// row; a column that fails the first test needs one more exchange, the candidate column's
+// maximum.  Words
+// travel as relaxed agent-scope atomics, each with a tag in its upper half: a reader polls
+// the words it needs until their tags are right, so an exchange is one trip to the
+// coherence point and there is no flag, no fence and no reset (areas alternate by column;
+// a workgroup writes an area again only after every other one has answered the column in
+// between, and so has read it).  Data of S and W that another workgroup may read or write
+// later go through the same kind of access, and a workgroup that wrote some waits for its
+// stores before it publishes again.  Every element is formed by the operations, in the
+// order, of bk_panel_rows, and maxima do not depend on the order, so the factors are the
+// same bits whatever the split.
+//
+// Measured, pivoting panels of 17 shifts in lock step at order 4096 (the slowest shift
+// counts): 9.8 us a column from memory, 5.5 as teams of up to 8; five shifts at order 1001
+// (one workgroup a shift): 4.8 and 3.0 us.  An exchange is 1.5 us of a column.
+//
+// The team must run at the same time.  Workgroups sign in to a roster; the one that
+// completes the team closes it, and if the team is not complete within about 20 us the
+// first one closes it for itself and runs the panel alone (bk_panel_rows) while late ones
+// leave.  So no workgroup ever waits for one that is not running, whatever else occupies
+// the device.  Every wait is bounded besides (wait_limit polls).
+struct TeamArgs {
+  int n;
+  double* const* LDs;
+  long ldld;
+  double* const* Wps;
+  long ldw;
+  int* const* perms;
+  int* const* swps;
+  int* const* blks;
+  int* const* colpanels;
+  int* const* pstarts;
+  FactorState* states;
+  unsigned long long* teams;
+  unsigned* wait_err;
+  unsigned wait_limit;
+  int nb, nbpiv;
+};
+
+__device__ __forceinline__ double team_ld(const double* p) {
+  return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ void team_st(double* p, double v) {
+  __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ void team_post(unsigned long long* w, unsigned tag, double v) {
+  const unsigned long long b = (unsigned long long)__double_as_longlong(v);
+  __hip_atomic_store(w, ((unsigned long long)tag << 32) | (b >> 32), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  __hip_atomic_store(w + 1, ((unsigned long long)tag << 32) | (b & 0xffffffffull), __ATOMIC_RELAXED,
+                     __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ unsigned long long team_word(const unsigned long long* w) {
+  return __hip_atomic_load(w, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ double team_value(unsigned long long hi, unsigned long long lo) {
+  return __longlong_as_double((long long)((hi << 32) | (lo & 0xffffffffull)));
+}
+
+template <int CTRL>
+__device__ __forceinline__ double dpp_f64(double x) {
+  const long long v = __double_as_longlong(x);
+  const int lo = __builtin_amdgcn_mov_dpp((int)v, CTRL, 0xf, 0xf, true);
+  const int hi = __builtin_amdgcn_mov_dpp((int)(v >> 32), CTRL, 0xf, 0xf, true);
+  return __longlong_as_double(((long long)hi << 32) | (unsigned)lo);
+}
+__device__ __forceinline__ double lane_f64(double x, int lane) {
+  const long long v = __double_as_longlong(x);
+  const unsigned lo = __builtin_amdgcn_readlane((int)v, lane);
+  const unsigned hi = __builtin_amdgcn_readlane((int)(v >> 32), lane);
+  return __longlong_as_double(((long long)hi << 32) | lo);
+}
+// The maximum over a row of 16 lanes, in each of them; over the wavefront, uniform.
+__device__ __forceinline__ double max16(double x) {
+  x = fmax(x, dpp_f64<0xB1>(x));
+  x = fmax(x, dpp_f64<0x4E>(x));
+  x = fmax(x, dpp_f64<0x141>(x));
+  return fmax(x, dpp_f64<0x140>(x));
+}
+__device__ __forceinline__ double max_wave(double x) {
+  x = max16(x);
+  return fmax(fmax(lane_f64(x, 0), lane_f64(x, 16)), fmax(lane_f64(x, 32), lane_f64(x, 48)));
+}
+// The smallest index among the lanes of `who` (not empty), uniform.
+__device__ __forceinline__ int min_index(unsigned long long who, int idx) {
+  int best = INT_MAX;
+  while (who) {
+    const int l = __ffsll((long long)who) - 1;
+    who &= who - 1;
+    best = min(best, __builtin_amdgcn_readlane(idx, l));
+  }
+  return best;
+}
+// A workgroup barrier that orders LDS only (stores to memory stay in flight).
+__device__ __forceinline__ void barrier_lds() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+  __builtin_amdgcn_s_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+}
+
+// a += w[0] l[0] + w[2] l[2] + ..., b += w[1] l[1] + ... in order, 16 products in all, where
+// w[p] is lane p's value in each row of 16 lanes.  The multiply-adds take w by DPP row
+// broadcast: no LDS read and no scalar move per product (from LDS, 16 wavefronts' broadcast
+// reads of a panel row took longer than the arithmetic).  The s_nop covers a VALU write of w.
+__device__ __forceinline__ void fmac16_pair(double& a, double& b, double w, const double* l) {
+  asm("s_nop 1\n\t"
+      "v_fmac_f64_dpp %0, %2, %3 row_newbcast:0 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f64_dpp %1, %2, %4 row_newbcast:1 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f64_dpp %0, %2, %5 row_newbcast:2 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f64_dpp %1, %2, %6 row_newbcast:3 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f64_dpp %0, %2, %7 row_newbcast:4 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f64_dpp %1, %2, %8 row_newbcast:5 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f64_dpp %0, %2, %9 row_newbcast:6 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f64_dpp %1, %2, %10 row_newbcast:7 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f64_dpp %0, %2, %11 row_newbcast:8 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f64_dpp %1, %2, %12 row_newbcast:9 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f64_dpp %0, %2, %13 row_newbcast:10 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f64_dpp %1, %2, %14 row_newbcast:11 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f64_dpp %0, %2, %15 row_newbcast:12 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f64_dpp %1, %2, %16 row_newbcast:13 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f64_dpp %0, %2, %17 row_newbcast:14 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f64_dpp %1, %2, %18 row_newbcast:15 row_mask:0xf bank_mask:0xf"
+      : "+v"(a), "+v"(b)
+      : "v"(w), "v"(l[0]), "v"(l[1]), "v"(l[2]), "v"(l[3]), "v"(l[4]), "v"(l[5]), "v"(l[6]), "v"(l[7]),
+        "v"(l[8]), "v"(l[9]), "v"(l[10]), "v"(l[11]), "v"(l[12]), "v"(l[13]), "v"(l[14]), "v"(l[15]));
+}
+// The same as one chain.
+__device__ __forceinline__ void fmac16(double& a, double w, const double* l) {
+  asm("s_nop 1\n\t"
+      "v_fmac_f64_dpp %0, %1, %2 row_newbcast:0 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f64_dpp %0, %1, %3 row_newbcast:1 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f64_dpp %0, %1, %4 row_newbcast:2 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f64_dpp %0, %1, %5 row_newbcast:3 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f64_dpp %0, %1, %6 row_newbcast:4 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f64_dpp %0, %1, %7 row_newbcast:5 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f64_dpp %0, %1, %8 row_newbcast:6 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f64_dpp %0, %1, %9 row_newbcast:7 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f64_dpp %0, %1, %10 row_newbcast:8 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f64_dpp %0, %1, %11 row_newbcast:9 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f64_dpp %0, %1, %12 row_newbcast:10 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f64_dpp %0, %1, %13 row_newbcast:11 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f64_dpp %0, %1, %14 row_newbcast:12 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f64_dpp %0, %1, %15 row_newbcast:13 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f64_dpp %0, %1, %16 row_newbcast:14 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f64_dpp %0, %1, %17 row_newbcast:15 row_mask:0xf bank_mask:0xf"
+      : "+v"(a)
+      : "v"(w), "v"(l[0]), "v"(l[1]), "v"(l[2]), "v"(l[3]), "v"(l[4]), "v"(l[5]), "v"(l[6]), "v"(l[7]),
+        "v"(l[8]), "v"(l[9]), "v"(l[10]), "v"(l[11]), "v"(l[12]), "v"(l[13]), "v"(l[14]), "v"(l[15]));
+}
+
+template <int NB, int NT, bool TEAM>
+__global__ __launch_bounds__(NT) void k_bk_team(TeamArgs a) {
+  constexpr int NW = NT / 64, LW = NB + 1;
+  __shared__ double Wt[NB * LW];  // W of the panel's rows: Wt[r * LW + p] = W(k0 + r, p)
+  __shared__ double wim[NB + 1];  // the candidate row's W, then its entry of column k
+  __shared__ double redv[2][NW];
+  __shared__ int redi[2][NW];
+  __shared__ double redc[NW];
+  __shared__ double sh_v[2], sh_arr;
+  __shared__ int sh_i, sh_own, sh_size, sh_rank;
+  const int s = blockIdx.y, tid = threadIdx.x;
+  const int w = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
+  const int n = a.n, nb = a.nb;
+  FactorState* st = a.states + s;
+  unsigned long long* team = a.teams + (long)s * kTeamWords;
+  const int k0 = __builtin_amdgcn_readfirstlane(st->k0 + st->kb);
+  const int done = __builtin_amdgcn_readfirstlane(st->done);
+  const int P = __builtin_amdgcn_readfirstlane(st->npanel);
+  const int jstart = __builtin_amdgcn_readfirstlane(st->jstart);
+  if (done || k0 >= n) return;  // (the state stays as the last panel left it)
+  const int rem = n - k0;
+  const int need = (rem + NT - 1) / NT;
+  int rank = 0;
+  if (TEAM) {
+    if (tid == 0) {
+      const unsigned closed = 0x80000000u;
+      unsigned* roster = reinterpret_cast<unsigned*>(team);
+      unsigned* size = reinterpret_cast<unsigned*>(team + 1);
+      const unsigned old = __hip_atomic_fetch_add(roster, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      int r = (int)(old & 0xffffu), sz = 0;
+      if ((old & closed) || r >= need) {
+        r = -1;
+      } else if (r == need - 1) {
+        if (!(__hip_atomic_fetch_or(roster, closed, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) & closed))
+          __hip_atomic_store(size, (unsigned)need, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      }
+      if (r >= 0) {
+        // the roster always closes: the first workgroup sees to it
+        for (unsigned polls = 0;; ++polls) {
+          sz = (int)__hip_atomic_load(size, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+          if (sz) break;
+          if (r == 0 && polls >= 40u &&
+              !(__hip_atomic_fetch_or(roster, closed, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) & closed)) {
+            __hip_atomic_store(size, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            sz = 1;
+            break;
+          }
+          __builtin_amdgcn_s_sleep(8);
+        }
+      }
+      sh_rank = r;
+      sh_size = sz;
+    }
+    __syncthreads();
+    rank = __builtin_amdgcn_readfirstlane(sh_rank);
+    const int size = __builtin_amdgcn_readfirstlane(sh_size);
+    if (rank < 0 || rank >= size) return;
+    if (size < need) {
+      bk_panel_rows<true, NT>(n, a.LDs, a.ldld, a.Wps, a.ldw, a.perms, a.swps, a.blks, a.colpanels,
+                              a.pstarts, a.states, nb, a.nbpiv, s);
+      return;
+    }
+  }
+  const int G = TEAM ? need : 1;
+  const bool multi = TEAM && G > 1;
+  // areas by parity: column maxima (B) and candidate maxima (C), G headers of four words,
+  // then 64 values of two words; and each workgroup's best row (R): 64 values, its entry of
+  // the column, S(imax, imax)
+  unsigned long long* mail = team + 64;
+  constexpr int kArea = 4 * kTeamMax + 128;
+  auto areaB = [&](int t) { return mail + (t & 1) * kArea; };
+  auto areaC = [&](int t) { return mail + (2 + (t & 1)) * kArea; };
+  auto areaR = [&](int t, int r) { return mail + 4 * kArea + ((t & 1) * kTeamMax + r) * kTeamRow; };
+  double* LD = a.LDs[s];
+  double* Wp = a.Wps[s];
+  const long ld = a.ldld, ldw = a.ldw;
+  auto ld_s = [&](const double* p) { return multi ? team_ld(p) : *p; };
+  auto st_s = [&](double* p, double v) {
+    if (multi)
+      team_st(p, v);
+    else
+      *p = v;
+  };
+  int* perm = a.perms[s];
+  int* sw = a.swps[s];
+  int* blk = a.blks[s];
+  int* colpanel = a.colpanels[s];
+
+  const int lab0 = k0 + rank * NT + tid;
+  int lab = lab0 < n ? lab0 : INT_MAX;  // the row this thread stands for
+  const int labc = min(lab0, n - 1);
+  const int pv = perm[labc];            // its original row travels with the thread
+  int wlim = -1;                        // columns of L to write, set when the thread retires
+  double L[NB];  // -L of this row (-0 where there is none: adding the product changes nothing)
+#pragma unroll
+  for (int p = 0; p < NB; ++p) L[p] = p < jstart ? -LD[labc + (long)(k0 + p) * ld] : -0.0;
+  for (int e = tid; e < NB * LW; e += NT) {
+    const int r = e / LW, p = e % LW;
+    Wt[e] = (p < jstart && r >= jstart && k0 + r < n) ? Wp[(k0 + r) + (long)p * ldw] : 0.0;
+  }
+  const int cend = min(n, k0 + NB);  // columns this panel may use
+  auto column = [&](int c) { return c < cend && lab >= c && lab < n ? ld_s(LD + lab + (long)c * ld) : 0.0; };
+  int j = jstart;
+  double c0 = column(k0 + j), c1 = column(k0 + j + 1), c2 = column(k0 + j + 2);
+  const int jmax0 = rem <= nb ? rem : nb - 1;
+  const int jmax = min(jmax0, jstart + a.nbpiv);
+  long neg = 0, zer = 0, pos = 0;
+  unsigned polls = 0;  // wavefront 0's unsuccessful polls in all; past the limit it goes on as it is
+  auto expired = [&]() {
+    if (polls++ < a.wait_limit) return false;
+    __hip_atomic_store(a.wait_err, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    return true;
+  };
+  bool stored = false;  // S entries written since the last publication
+  __syncthreads();
+
+  for (int t = 1; j < jmax; ++t) {
+    const int k = k0 + j;
+    const unsigned tag = ((unsigned)(P + 1) << 8) | (unsigned)t;
+    const bool live = lab >= k && lab < n;
+    const bool top = rank == 0 && lab >= k && lab < k0 + NB;  // (in the first wavefront)
+    // ---- column k of the Schur complement: even panel columns into av, odd ones into bv
+    double av = c0, bv = 0.0;
+#pragma unroll
+    for (int g = 0; g < NB; g += 16)
+      if (g < j) {
+        // (entries from j on are being written by the panel rows' threads)
+        const double x = Wt[j * LW + g + (lane & 15)];
+        fmac16_pair(av, bv, g + (lane & 15) < j ? x : 0.0, L + g);
+      }
+    av += bv;
+    double v = live && lab > k ? fabs(av) : -1.0;
+    v = v > -1.0 ? v : -1.0;  // (a NaN is never the largest)
+    double vm = max_wave(v);
+    int im = vm > -1.0 ? min_index(__ballot(v == vm), lab) : INT_MAX;
+    // this wavefront's best row of W (written by this wavefront): the candidate's, if it wins
+    const double wv = (im < n && lane < j) ? ld_s(Wp + im + (long)lane * ldw) : 0.0;
+    if (lane == 0) {
+      redv[t & 1][w] = vm;
+      redi[t & 1][w] = im;
+    }
+    if (!TEAM || rank == 0) {
+      if (top) Wt[(lab - k0) * LW + j] = av;
+    }
+    if (stored) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    barrier_lds();
+    double colmax;
+    int imax, own = 0;
+    {
+      const double x = lane < NW ? redv[t & 1][lane] : -1.0;
+      const int xi = lane < NW ? redi[t & 1][lane] : INT_MAX;
+      colmax = lane_f64(max16(x), 0);
+      imax = colmax > -1.0 ? min_index(__ballot(lane < NW && x == colmax), xi) : INT_MAX;
+    }
+    if (multi && w == 0) {
+      unsigned long long* ar = areaB(t);
+      if (lane == 0) {
+        team_post(ar + 4 * rank, tag, colmax);
+        __hip_atomic_store(ar + 4 * rank + 2, ((unsigned long long)tag << 32) | (unsigned)imax,
+                           __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      }
+      if (rank == 0 && lane < NB) team_post(ar + 4 * kTeamMax + 2 * lane, tag, Wt[lane * LW + j]);
+    }
+    {
+      const unsigned long long hold = imax < n ? __ballot(lab == imax) : 0;
+      if (hold) {
+        const double ev = lane_f64(av, __ffsll((long long)hold) - 1);
+        if (lane < NB) wim[lane] = wv;
+        if (lane == 0) wim[NB] = ev;
+        if (multi) {
+          unsigned long long* ar = areaR(t, rank);
+          if (lane < NB) team_post(ar + 2 * lane, tag, wv);
+          if (lane == 0) team_post(ar + 128, tag, ev);
+        }
+      }
+    }
+    if (multi) {
+      if (w == 0) {
+        const unsigned long long* ar = areaB(t);
+        unsigned long long h0 = 0, h1 = 0, h2 = 0, t0 = 0, t1 = 0;
+        const bool wh = lane < G, wt = rank > 0 && lane < NB;
+        for (;;) {
+          if (wh && ((h0 >> 32) != tag || (h1 >> 32) != tag || (h2 >> 32) != tag)) {
+            h0 = team_word(ar + 4 * lane);
+            h1 = team_word(ar + 4 * lane + 1);
+            h2 = team_word(ar + 4 * lane + 2);
+          }
+          if (wt && ((t0 >> 32) != tag || (t1 >> 32) != tag)) {
+            t0 = team_word(ar + 4 * kTeamMax + 2 * lane);
+            t1 = team_word(ar + 4 * kTeamMax + 2 * lane + 1);
+          }
+          const bool ok = (!wh || ((h0 >> 32) == tag && (h1 >> 32) == tag && (h2 >> 32) == tag)) &&
+                          (!wt || ((t0 >> 32) == tag && (t1 >> 32) == tag));
+          if (__ballot(!ok) == 0 || expired()) break;
+        }
+        const double x = wh ? team_value(h0, h1) : -1.0;
+        const int xi = wh ? (int)(unsigned)h2 : INT_MAX;
+        colmax = max_wave(x);
+        const unsigned long long who = __ballot(wh && x == colmax);
+        imax = colmax > -1.0 && who ? min_index(who, xi) : INT_MAX;
+        const unsigned long long mine = __ballot(wh && x == colmax && xi == imax);
+        if (wt) Wt[lane * LW + j] = team_value(t0, t1);
+        // (a wait that expired may leave a stale index: no access may follow it)
+        if (imax <= k || imax >= n) colmax = -1.0;
+        if (lane == 0) {
+          sh_v[0] = colmax;
+          sh_i = imax;
+          sh_own = mine ? __ffsll((long long)mine) - 1 : -1;
+        }
+      }
+      barrier_lds();
+      colmax = sh_v[0];
+      imax = __builtin_amdgcn_readfirstlane(sh_i);
+      own = __builtin_amdgcn_readfirstlane(sh_own);
+    }
+    const double akk = Wt[j * LW + j], absakk = fabs(akk);
+    colmax = colmax > 0.0 ? colmax : 0.0;
+    int kstep = 1, kp = k;
+    double b = 0.0, arr = 0.0;
+    const bool cand = absakk < kBkAlpha * colmax;  // uniform over the team
+    if (cand) {
+      // ---- candidate column imax of the Schur complement
+      const bool act = live;
+      double raw = 0.0;
+      if (act) raw = ld_s(lab < imax ? LD + imax + (long)lab * ld : LD + lab + (long)imax * ld);
+      if (multi && rank != own && w == 0) {
+        const unsigned long long* ar = areaR(t, max(own, 0));
+        unsigned long long t0 = 0, t1 = 0, e0 = 0, e1 = 0;
+        const bool wt = lane < NB, we = lane == 0;
+        for (;;) {
+          if (wt && ((t0 >> 32) != tag || (t1 >> 32) != tag)) {
+            t0 = team_word(ar + 2 * lane);
+            t1 = team_word(ar + 2 * lane + 1);
+          }
+          if (we && ((e0 >> 32) != tag || (e1 >> 32) != tag)) {
+            e0 = team_word(ar + 128);
+            e1 = team_word(ar + 129);
+          }
+          const bool ok = (!wt || ((t0 >> 32) == tag && (t1 >> 32) == tag)) &&
+                          (!we || ((e0 >> 32) == tag && (e1 >> 32) == tag));
+          if (__ballot(!ok) == 0 || expired()) break;
+        }
+        if (wt) wim[lane] = team_value(t0, t1);
+        if (we) wim[NB] = team_value(e0, e1);
+      }
+      barrier_lds();
+      b = raw;
+#pragma unroll
+      for (int g = 0; g < NB; g += 16)
+        if (g < j) fmac16(b, wim[g + (lane & 15)], L + g);  // (zero from j on)
+      double x = act && lab != imax ? fabs(b) : -1.0;
+      x = x > -1.0 ? x : -1.0;
+      x = max_wave(x);
+      if (lane == 0) redc[w] = x;
+      if (top) Wt[(lab - k0) * LW + j + 1] = b;
+      if (lab == imax) sh_arr = b;
+      barrier_lds();
+      double rowmax = lane_f64(max16(lane < NW ? redc[lane] : -1.0), 0);
+      arr = sh_arr;
+      if (multi) {
+        if (w == 0) {
+          unsigned long long* ar = areaC(t);
+          if (lane == 0) {
+            team_post(ar + 4 * rank, tag, rowmax);
+            if (rank == own) team_post(areaR(t, rank) + 130, tag, arr);
+          }
+          if (rank == 0 && lane < NB) team_post(ar + 4 * kTeamMax + 2 * lane, tag, Wt[lane * LW + j + 1]);
+          unsigned long long h0 = 0, h1 = 0, t0 = 0, t1 = 0, e0 = 0, e1 = 0;
+          const bool wh = lane < G, wt = rank > 0 && lane < NB, we = lane == 0 && rank != own;
+          for (;;) {
+            if (wh && ((h0 >> 32) != tag || (h1 >> 32) != tag)) {
+              h0 = team_word(ar + 4 * lane);
+              h1 = team_word(ar + 4 * lane + 1);
+            }
+            if (wt && ((t0 >> 32) != tag || (t1 >> 32) != tag)) {
+              t0 = team_word(ar + 4 * kTeamMax + 2 * lane);
+              t1 = team_word(ar + 4 * kTeamMax + 2 * lane + 1);
+            }
+            if (we && ((e0 >> 32) != tag || (e1 >> 32) != tag)) {
+              e0 = team_word(areaR(t, max(own, 0)) + 130);
+              e1 = team_word(areaR(t, max(own, 0)) + 131);
+            }
+            const bool ok = (!wh || ((h0 >> 32) == tag && (h1 >> 32) == tag)) &&
+                            (!wt || ((t0 >> 32) == tag && (t1 >> 32) == tag)) &&
+                            (!we || ((e0 >> 32) == tag && (e1 >> 32) == tag));
+            if (__ballot(!ok) == 0 || expired()) break;
+          }
+          const double y = max_wave(wh ? team_value(h0, h1) : -1.0);
+          if (wt) Wt[lane * LW + j + 1] = team_value(t0, t1);
+          if (lane == 0) {
+            sh_v[1] = y;
+            if (we) sh_arr = team_value(e0, e1);
+          }
+        }
+        barrier_lds();
+        rowmax = sh_v[1];
+        arr = sh_arr;
+      }
+      if (absakk * rowmax >= kBkAlpha * colmax * colmax) {
+        kstep = 1;
+        kp = k;
+      } else if (fabs(arr) >= kBkAlpha * rowmax) {
+        kstep = 1;
+        kp = imax;
+      } else {
+        kstep = 2;
+        kp = imax;
+      }
+    }
+    const int kk = k + kstep - 1;
+    const bool swap = kp != kk;
+    const double rawk = kstep == 1 ? c0 : c1;  // column kk as it was, this row
+    const int old = lab;
+    if (swap) {
+      // symmetric interchange kk <-> kp of S: kk becomes a pivot column, so only row and
+      // column kp need column kk's entries; then the two rows' threads exchange labels
+      if (lab > kk && lab < n && lab != kp)
+        st_s(lab > kp ? LD + lab + (long)kp * ld : LD + kp + (long)lab * ld, rawk);
+      if (lab == kk) st_s(LD + kp + (long)kp * ld, rawk);
+      // W of row kk moves to row kp
+      if (rank == 0 && w == 0 && lane < j) st_s(Wp + kp + (long)lane * ldw, Wt[(kk - k0) * LW + lane]);
+      if (old == kk)
+        lab = kp;
+      else if (old == kp)
+        lab = kk;
+    }
+    stored = swap;
+    // pivot and multipliers; the column(s) of W under the final labels
+    const double w1 = (kstep == 1 && swap) ? b : av, w2 = b;
+    const bool below = lab > kk && lab < n;
+    double l1, l2 = 0.0;
+    double d11, d21 = 0.0, d22 = 0.0;
+    if (kstep == 1) {
+      d11 = swap ? arr : akk;
+      const double dinv = d11 != 0.0 ? 1.0 / d11 : 0.0;
+      l1 = w1 * dinv;
+    } else {
+      d11 = akk;
+      d21 = wim[NB];
+      d22 = arr;
+      const double aa = d11 / d21, gg = d22 / d21;
+      const double tt = 1.0 / (d21 * (aa * gg - 1.0));
+      l1 = tt * (gg * w1 - w2);
+      l2 = tt * (aa * w2 - w1);
+    }
+    if (below) {
+      st_s(Wp + lab + (long)j * ldw, w1);
+      if (kstep == 2) st_s(Wp + lab + (long)(j + 1) * ldw, w2);
+    }
+#pragma unroll
+    for (int g = 0; g < NB; g += 8)
+      if (g <= j + kstep - 1 && j < g + 8) {
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+          if (g + u == j && below) L[g + u] = -l1;
+          if (kstep == 2 && g + u == j + 1 && below) L[g + u] = -l2;
+        }
+      }
+    if (live && !below && wlim < 0) wlim = j;  // this row became a pivot
+    // ---- raw columns of the next steps.  Entries that this interchange changed come from
+    // the registers they came from: column kp is column kk as it was, and row kp holds
+    // column kk's entry of the column's own row (its thread is in the same wavefront).
+    auto next_col = [&](int c, double have, bool loaded) {
+      double x = have;
+      if (!loaded) x = (swap && c == kp) ? 0.0 : column(c);
+      if (swap && c < cend) {
+        if (c == kp) {
+          x = rawk;
+        } else if (c < kp && rank == 0 && w == 0) {
+          const unsigned long long src = __ballot(old == c);
+          const double vc = src ? lane_f64(rawk, __ffsll((long long)src) - 1) : 0.0;
+          if (old == kk) x = vc;
+        }
+      }
+      return x;
+    };
+    if (kstep == 1) {
+      c0 = next_col(k + 1, c1, true);
+      c1 = next_col(k + 2, c2, true);
+      c2 = next_col(k + 3, 0.0, false);
+    } else {
+      c0 = next_col(k + 2, c2, true);
+      c1 = next_col(k + 3, 0.0, false);
+      c2 = next_col(k + 4, 0.0, false);
+    }
+    // ---- every workgroup's copy of the panel rows' W
+    if (cand) {
+      if (w == 0) {
+        if (swap && kp < k0 + NB) {  // row kp takes row kk's W
+          const double x0 = Wt[(kk - k0) * LW + min(lane, NB - 1)];
+          if (lane < NB && lane <= j + 1) Wt[(kp - k0) * LW + lane] = x0;
+        }
+        __builtin_amdgcn_wave_barrier();
+        if (kstep == 1 && lane < NB) {
+          const double x1 = Wt[lane * LW + j + 1];
+          if (swap) Wt[lane * LW + j] = x1;
+          Wt[lane * LW + j + 1] = 0.0;
+        }
+      }
+      barrier_lds();
+    }
+    if (rank == 0 && tid == NT - 1) {
+      sw[k] = kstep == 1 ? kp : k;
+      LD[k + (long)k * ld] = d11;
+      colpanel[k] = P;
+      if (kstep == 1) {
+        blk[k] = 1;
+        if (d11 < 0.0)
+          ++neg;
+        else if (d11 > 0.0)
+          ++pos;
+        else
+          ++zer;
+      } else {
+        sw[k + 1] = kp;
+        LD[k + 1 + (long)k * ld] = d21;
+        LD[k + 1 + (long)(k + 1) * ld] = d22;
+        blk[k] = 2;
+        blk[k + 1] = 0;
+        colpanel[k + 1] = P;
+        const double det = d11 * d22 - d21 * d21;
+        const double tr = d11 + d22;
+        if (det < 0.0) {
+          ++neg;
+          ++pos;
+        } else if (det > 0.0) {
+          if (tr < 0.0)
+            neg += 2;
+          else
+            pos += 2;
+        } else {
+          ++zer;
+          if (tr < 0.0)
+            ++neg;
+          else if (tr > 0.0)
+            ++pos;
+          else
+            ++zer;
+        }
+      }
+    }
+    j += kstep;
+  }
+  // ---- L and the permutation under the final labels
+  if (lab < n && lab >= k0 + jstart) {
+    const int lim = wlim >= 0 ? wlim : j;
+    const int from = lab == lab0 ? jstart : 0;
+#pragma unroll
+    for (int p = 0; p < NB; ++p)
+      if (p >= from && p < lim) LD[lab + (long)(k0 + p) * ld] = -L[p];
+    if (lab != lab0) perm[lab] = pv;
+  }
+  if (rank == 0 && tid == NT - 1) {
+    st->k0 = k0;
+    st->kb = j;
+    st->npanel = P + 1;
+    st->done = (k0 + j >= n);
+    st->neg += neg;
+    st->zero += zer;
+    st->pos += pos;
+    st->jstart = 0;
+    a.pstarts[s][P] = k0;
   }
 }
 
@@ -1255,7 +1900,42 @@ static FactorPlan factor_subplan(const FactorPlan& fp, int s0, int cnt) {
   f.d_state = fp.d_state + s0;
   f.d_inertia = fp.d_inertia + 3 * (size_t)s0;
   f.d_aux = fp.d_aux ? fp.d_aux + s0 : nullptr;
+  f.d_team = fp.d_team + (size_t)s0 * kTeamWords;
   return f;
+}
+
+// The pivoting panel of every shift.  rem_max bounds the rows of the least advanced shift;
+// a team per shift must fit the device at once (seven eighths of it, shared by the shift
+// groups), otherwise one workgroup a shift runs the panel from memory.
+static void panel_launch(const FactorPlan& fp, hipStream_t st, long rem_max, int nbpiv) {
+  const int n = fp.n, S = fp.nshift, nb = fp.nb;
+  if (!fp.pivot) {
+    SL_LAUNCH(k_bk_panel<false>, dim3(S), dim3(1024), 0, st, n, fp.d_LD, fp.ldld, fp.d_W, fp.ldw,
+              fp.d_perm, fp.d_sw, fp.d_blk, fp.d_colpanel, fp.d_pstart, fp.d_state, nb, nbpiv);
+    SL_LAUNCH_CHECK();
+    return;
+  }
+  const int rows = nb > 32 ? 512 : 1024;  // of one workgroup
+  const long need = ceil_div(rem_max, rows);
+  if (fp.team && fp.fast && (need <= 1 || (need <= kTeamMax && need * S <= (long)fp.cus * 7 / 8 / fp.groups))) {
+    TeamArgs a{n, fp.d_LD, fp.ldld, fp.d_W, fp.ldw, fp.d_perm, fp.d_sw, fp.d_blk, fp.d_colpanel,
+               fp.d_pstart, fp.d_state, fp.d_team, fp.wait_err, fp.wait_limit, nb, nbpiv};
+    if (rows == 512) {
+      if (need <= 1)
+        SL_LAUNCH((k_bk_team<64, 512, false>), dim3(1, S), dim3(512), 0, st, a);
+      else
+        SL_LAUNCH((k_bk_team<64, 512, true>), dim3((unsigned)need, S), dim3(512), 0, st, a);
+    } else {
+      if (need <= 1)
+        SL_LAUNCH((k_bk_team<32, 1024, false>), dim3(1, S), dim3(1024), 0, st, a);
+      else
+        SL_LAUNCH((k_bk_team<32, 1024, true>), dim3((unsigned)need, S), dim3(1024), 0, st, a);
+    }
+  } else {
+    SL_LAUNCH(k_bk_panel<true>, dim3(S), dim3(1024), 0, st, n, fp.d_LD, fp.ldld, fp.d_W, fp.ldw,
+              fp.d_perm, fp.d_sw, fp.d_blk, fp.d_colpanel, fp.d_pstart, fp.d_state, nb, nbpiv);
+  }
+  SL_LAUNCH_CHECK();
 }
 
 // One panel step of every shift of `fp` on stream `st`: the speculative
@@ -1299,20 +1979,15 @@ static void factor_step(const FactorPlan& fp, hipStream_t st, long k0_lb, sislic
     if (fp.pivot)
       SL_LAUNCH(k_fast_commit<true>, dim3(nb, S), dim3(256), 0, st, n, fp.d_LD, fp.ldld,
                 (const double* const*)fp.d_W, fp.ldw, (const double* const*)fp.d_aux, fp.d_blk,
-                fp.d_colpanel, fp.d_state, nb);
+                fp.d_colpanel, fp.d_state, fp.d_team, nb);
     else
       SL_LAUNCH(k_fast_commit<false>, dim3(nb, S), dim3(256), 0, st, n, fp.d_LD, fp.ldld,
                 (const double* const*)fp.d_W, fp.ldw, (const double* const*)fp.d_aux, fp.d_blk,
-                fp.d_colpanel, fp.d_state, nb);
+                fp.d_colpanel, fp.d_state, fp.d_team, nb);
     SL_LAUNCH_CHECK();
   }
   if (tpan < 0) tpan = prof_begin(ph, kProfPanel, st);
-  if (fp.pivot)
-    SL_LAUNCH(k_bk_panel<true>, dim3(S), dim3(1024), 0, st, n, fp.d_LD, fp.ldld, fp.d_W, fp.ldw,
-              fp.d_perm, fp.d_sw, fp.d_blk, fp.d_colpanel, fp.d_pstart, fp.d_state, nb, nbpiv);
-  else
-    SL_LAUNCH(k_bk_panel<false>, dim3(S), dim3(1024), 0, st, n, fp.d_LD, fp.ldld, fp.d_W, fp.ldw,
-              fp.d_perm, fp.d_sw, fp.d_blk, fp.d_colpanel, fp.d_pstart, fp.d_state, nb, nbpiv);
+  panel_launch(fp, st, n - k0_lb, nbpiv);
   SL_LAUNCH_CHECK();
   prof_end(ph, tpan, st);
   if (after_panel) SL_HIP(hipEventRecord(after_panel, st));
@@ -1365,7 +2040,7 @@ void factor_steps_launch(const FactorPlan& fp, hipStream_t st, bool readback) {
   if (S <= 0 || n <= 0) return;
   factor_prepare();
   SL_LAUNCH(k_factor_init, dim3((unsigned)ceil_div(n, 256), S), dim3(256), 0, st, n,
-                     fp.d_state, fp.d_perm, fp.d_sw);
+                     fp.d_state, fp.d_perm, fp.d_sw, fp.d_team);
   SL_LAUNCH_CHECK();
   sislice_handle* ph = current_handle();
   const int min_kb = factor_min_panel(nb, fp.nbpiv, fp.fast != 0);

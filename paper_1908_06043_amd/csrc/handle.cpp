@@ -158,12 +158,19 @@ void prof_reset(sislice_handle* h) {
 
 int default_nb(int n) { return n >= 2048 ? 64 : 32; }
 
+// Columns of a pivoting panel: as many as the panel holds.  A team's column costs the same
+// however many precede it, and wider panels read and write the trailing matrix less often
+// (order 4096, 17 shifts: 32.1 ms with 32 columns, 29.5 with 64; order 12288, 8 shifts: 209
+// and 197 ms).  The width does not depend on how a panel is run, so the factors do not
+// either.
+static int default_nbpiv(int nb) { return nb > 32 ? kMaxNb : 32; }
+
 FactorPlan build_factor(sislice_handle* h, int bufid, int n, const double* A, long lda,
                         const double* B, long ldb, int S, const double* sigmas_host,
                         double* const* LD_host, long ldld, int32_t* const* ipiv_host, int nb,
                         bool pivot) {
   const FactorPlan defaults;
-  const int nbpiv = h->cur_nbpiv > 0 ? h->cur_nbpiv : defaults.nbpiv;
+  const int nbpiv = h->cur_nbpiv > 0 ? h->cur_nbpiv : default_nbpiv(nb);
   const int npmax = factor_npanel_max(n, nb, nbpiv, defaults.fast != 0);
   const long ldw = n;
   Sizer z;
@@ -176,6 +183,7 @@ FactorPlan build_factor(sislice_handle* h, int bufid, int n, const double* A, lo
   z.take<int64_t>(3 * (size_t)S);
   z.take<void*>(10 * (size_t)S);
   z.take<double>((size_t)S * (3 * nb + nb * nb));   // aux
+  z.take<unsigned long long>((size_t)S * kTeamWords);
   Carver c(ws_get(h, bufid, z.off));
   FactorPlan fp;
   fp.n = n;
@@ -200,6 +208,7 @@ FactorPlan build_factor(sislice_handle* h, int bufid, int n, const double* A, lo
   fp.d_inertia = c.take<int64_t>(3 * (size_t)S);
   void** tab = c.take<void*>(10 * (size_t)S);
   double* aux = c.take<double>((size_t)S * (3 * nb + nb * nb));
+  fp.d_team = c.take<unsigned long long>((size_t)S * kTeamWords);
   // host staging: sigmas then the pointer tables
   size_t hbytes = sizeof(double) * S + sizeof(void*) * 10 * S;
   char* hs = static_cast<char*>(host_stage(h, hbytes));
@@ -234,6 +243,8 @@ FactorPlan build_factor(sislice_handle* h, int bufid, int n, const double* A, lo
   fp.d_aux = reinterpret_cast<double* const*>(tab + 9 * S);
   fp.nbpiv = nbpiv;
   fp.cus = h->cus;
+  fp.wait_err = wait_flag(h);
+  fp.wait_limit = h->wait_limit;
   // two shift groups on two streams overlap one group's panels with the other's
   // updates where the updates are long (measured at n = 12288, 49 shifts: 1080
   // against 1122 ms; at n = 4096 the lock-step form is faster)

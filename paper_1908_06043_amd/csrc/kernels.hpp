@@ -7,6 +7,11 @@
 
 namespace sislice {
 
+// Words of one shift's team area (k_bk_team): the roster, then the mailboxes.
+constexpr int kTeamMax = 32;  // workgroups in a team
+constexpr int kTeamRow = 136;  // words of one workgroup's row
+constexpr int kTeamWords = 64 + 4 * (4 * kTeamMax + 128) + 2 * kTeamMax * kTeamRow;
+
 // One lock-step factorization of `nshift` shifted matrices of order n.
 struct FactorPlan {
   int n = 0, nshift = 0, nb = 32;
@@ -33,8 +38,12 @@ struct FactorPlan {
   // pivot-free speculative panel path (per shift): staged L of the panel (n x nb),
   // D of the panel, inverse of the diagonal block (nb x nb), column maxima
   double* const* d_aux = nullptr;  // [nb] D | [nb] max|w| in block | [nb] max|w| below (uint64 bits) | nb*nb Linv
+  unsigned long long* d_team = nullptr;  // device [nshift * kTeamWords]: mailboxes of the panel teams
+  unsigned* wait_err = nullptr;    // raised when a team's wait exceeds wait_limit polls
+  unsigned wait_limit = 0;
+  int team = 1;                    // pivoting panels by teams of workgroups (L in registers)
   int fast = 1;                    // use the pivot-free path
-  int nbpiv = 32;                  // columns a pivoting panel handles after a rejection
+  int nbpiv = 32;                  // columns a pivoting panel handles after a rejection (default_nbpiv)
   int wide_min = 1024;             // trailing order from which the update takes 128x128 tiles
   int update_pipe = 1;             // 128x128 updates by the persistent pipelined kernel
   int stream_c = 0;                // the 128-tile update streams C (shift groups on two streams)
