@@ -155,7 +155,7 @@ __global__ __launch_bounds__(256, 4) void k_gemm(GemmArgs g) {
         }
     return;
   }
-  double* C = g.C ? g.C[b] : g.C1;
+  double* C = global_ptr(g.C ? g.C[b] : g.C1);
 #pragma unroll
   for (int x = 0; x < 2; ++x)
 #pragma unroll
@@ -176,7 +176,7 @@ __global__ __launch_bounds__(256) void k_gemm_reduce(GemmArgs g) {
   const int b = blockIdx.y;
   const int m = g.m ? g.m[b] : g.m0;
   const int n = g.n ? g.n[b] : g.n0;
-  double* C = g.C ? g.C[b] : g.C1;
+  double* C = global_ptr(g.C ? g.C[b] : g.C1);
   for (long e = blockIdx.x * 256L + threadIdx.x; e < (long)m * n; e += (long)gridDim.x * 256) {
     const int i = (int)(e % m), j = (int)(e / m);
     // summed in split order

@@ -45,6 +45,18 @@ __device__ __forceinline__ d4 mfma16x16x4(double a, double b, d4 c) {
   return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
 }
 
+// p, known to be in global memory.  The compiler takes a pointer read from a table in memory
+// to be generic, and a generic (flat) access counts as an access to LDS as well: every wait
+// for LDS then waits for all such loads and stores, so none can be in flight across a
+// barrier or an exchange through LDS.  p is the same in every lane.
+template <typename T>
+__device__ __forceinline__ T* global_ptr(T* p) {
+  const auto u = reinterpret_cast<unsigned long long>(p);
+  const unsigned lo = __builtin_amdgcn_readfirstlane((int)(unsigned)u);
+  const unsigned hi = __builtin_amdgcn_readfirstlane((int)(unsigned)(u >> 32));
+  return (T*)(__attribute__((address_space(1))) T*)((unsigned long long)hi << 32 | lo);
+}
+
 // Bunch-Kaufman pivot threshold alpha = (1 + sqrt(17)) / 8 (Bunch & Kaufman 1977).
 constexpr double kBkAlpha = 0.6403882032022076;
 

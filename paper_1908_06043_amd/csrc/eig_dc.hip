@@ -247,7 +247,7 @@ __global__ __launch_bounds__(NT) void k_eig_dc(EigArgs a, double* __restrict__ r
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
   const int i = tid >> 2, q = tid & 3;  // row (reduction), element or column; lane of its quad
   double* U = refl + (long)b * rstride;  // reflector k at U + k * P
-  const double* Ain = a.A[b];
+  const double* Ain = global_ptr(a.A[b]);
   const long lda = a.lda;
 
   // ---- 1. reduction to tridiagonal form
@@ -871,7 +871,7 @@ __global__ __launch_bounds__(NT) void k_eig_dc(EigArgs a, double* __restrict__ r
     }
   }
   lds_barrier();
-  double* Vo = a.V[b];
+  double* Vo = global_ptr(a.V[b]);
   for (int c = w; c < m; c += NW) {
     double* v = Vo + (long)S.rank[c] * a.ldv;
     for (int r = lane; r < m; r += 64) v[r] = Q[c * ldx + r];

@@ -89,8 +89,8 @@ __global__ __launch_bounds__(256) void k_factor_init(int n, FactorState* states,
   // no mailbox word carries a tag of this factorization yet
   for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < kTeamWords; i += gridDim.x * blockDim.x)
     teams[(long)s * kTeamWords + i] = 0;
-  int* perm = perms[s];
-  int* sw = swps[s];
+  int* perm = global_ptr(perms[s]);
+  int* sw = global_ptr(swps[s]);
   for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x) {
     perm[i] = i;
     sw[i] = i;
@@ -148,9 +148,9 @@ __global__ __launch_bounds__(256) void k_fast_diag4(int n, const double* const* 
   const int k0 = st.k0 + st.kb;
   if (st.done || k0 >= n) return;
   const int nbe = min(nb, n - k0);
-  const double* LD = LDs[s];
-  double* Wp = Wps[s];
-  double* aux = auxs[s];
+  const double* LD = global_ptr(LDs[s]);
+  double* Wp = global_ptr(Wps[s]);
+  double* aux = global_ptr(auxs[s]);
   double* Dv = aux;
   double* cin = aux + nb;
   unsigned long long* cout = reinterpret_cast<unsigned long long*>(aux + 2 * nb);
@@ -248,9 +248,9 @@ __global__ __launch_bounds__(256) void k_fast_trsm(int n, const double* const* L
   const int nbe = min(nb, n - k0);
   const int r0 = k0 + nbe + 64 * blockIdx.x;
   if (r0 >= n) return;
-  const double* LD = LDs[s];
-  double* Wp = Wps[s];
-  const double* aux = auxs[s];
+  const double* LD = global_ptr(LDs[s]);
+  double* Wp = global_ptr(Wps[s]);
+  const double* aux = global_ptr(auxs[s]);
   unsigned long long* cout = reinterpret_cast<unsigned long long*>(const_cast<double*>(aux) + 2 * nb);
   const double* L11 = aux + 3 * nb;
   for (int e = tid; e < NB * NB; e += 256) {
@@ -311,7 +311,7 @@ __global__ __launch_bounds__(256) void k_fast_commit(int n, double* const* LDs, 
   if (st.done || k0 >= n) return;
   const int nbe = min(nb, n - k0);
   if (c >= nbe) return;
-  const double* aux = auxs[s];
+  const double* aux = global_ptr(auxs[s]);
   const double* Dv = aux;
   const double* cin = aux + nb;
   const unsigned long long* cout = reinterpret_cast<const unsigned long long*>(aux + 2 * nb);
@@ -332,8 +332,8 @@ __global__ __launch_bounds__(256) void k_fast_commit(int n, double* const* LDs, 
   __syncthreads();
   const int jst = js;
   if (c < jst) {
-    double* LD = LDs[s];
-    const double* Wp = Wps[s];
+    double* LD = global_ptr(LDs[s]);
+    const double* Wp = global_ptr(Wps[s]);
     const int col = k0 + c;
     const double rd = 1.0 / Dv[c];  // the column's multipliers l = w (1 / d)
     for (int i = col + 1 + tid; i < n; i += 256) LD[i + (long)col * ldld] = Wp[i + (long)c * ldw] * rd;
@@ -369,13 +369,13 @@ __device__ __forceinline__ void bk_panel_rows(int n, double* const* LDs, long ld
   constexpr int NW = NT / 64;
   const int tid = threadIdx.x;
   FactorState* st = states + s;
-  double* __restrict__ LD = LDs[s];
-  double* __restrict__ Wp = Wps[s];
-  int* perm = perms[s];
-  int* sw = swps[s];
-  int* blk = blks[s];
-  int* colpanel = colpanels[s];
-  int* pstart = pstarts[s];
+  double* __restrict__ LD = global_ptr(LDs[s]);
+  double* __restrict__ Wp = global_ptr(Wps[s]);
+  int* perm = global_ptr(perms[s]);
+  int* sw = global_ptr(swps[s]);
+  int* blk = global_ptr(blks[s]);
+  int* colpanel = global_ptr(colpanels[s]);
+  int* pstart = global_ptr(pstarts[s]);
 
   __shared__ double wk[kMaxNb + 2];
   __shared__ double red_v[NW];
@@ -661,18 +661,18 @@ __global__ __launch_bounds__(1024) void k_bk_panel(int n, double* const* LDs, lo
 // workgroup NT rows, and the rows of a shift are spread over a team of workgroups.
 //
 // What bounds it: the chain of pivot decisions.  A column of S is one multiply-add per
-// panel column and thread (no memory but the raw column, loaded two columns ahead); then
-// the team agrees on the pivot.  A row interchange moves no data between threads: the two
-// rows' threads exchange labels (the row a thread stands for), and L is written once, at
-// the end, under the final labels.  A thread that becomes a pivot retires.  The W rows of
-// the panel's own NB rows, which supply the multipliers of coming columns, are replicated
-// in every workgroup's LDS.
+// panel column and thread (no memory but the raw column, loaded two columns ahead, through
+// pointers known to be global: each barrier would wait for it otherwise); then the team
+// agrees on the pivot.  A row interchange moves no data between threads: the two rows'
+// threads exchange labels (the row a thread stands for), and L is written once, at the
+// end, under the final labels.  A thread that becomes a pivot retires.  The W rows of the
+// panel's own NB rows, which supply the multipliers of coming columns, are replicated in
+// every workgroup's LDS.
 //
 // The team's exchanges.  Per column each workgroup publishes its largest entry and its row,
 // the first one also the new W column of the panel's rows, and each one the W of its best
 // row; a column that fails the first test needs one more exchange, the candidate column's
-// maximum.  Words
-// travel as relaxed agent-scope atomics, each with a tag in its upper half: a reader polls
+// maximum.  Words travel as relaxed agent-scope atomics, each with a tag in its upper half: a reader polls
 // the words it needs until their tags are right, so an exchange is one trip to the
 // coherence point and there is no flag, no fence and no reset (areas alternate by column;
 // a workgroup writes an area again only after every other one has answered the column in
@@ -682,9 +682,10 @@ __global__ __launch_bounds__(1024) void k_bk_panel(int n, double* const* LDs, lo
 // order, of bk_panel_rows, and maxima do not depend on the order, so the factors are the
 // same bits whatever the split.
 //
-// Measured, pivoting panels of 17 shifts in lock step at order 4096 (the slowest shift
-// counts): 9.8 us a column from memory, 5.5 as teams of up to 8; five shifts at order 1001
-// (one workgroup a shift): 4.8 and 3.0 us.  An exchange is 1.5 us of a column.
+// Measured, all pivoting panels of a factorization: 17 shifts in lock step at order 4096
+// (teams of up to 8) 18.9 ms from memory, 9.1 so; five shifts at order 1001 (one workgroup
+// a shift) 2.5 and 1.0 ms, 1.6 us a column that needs a second test.  An exchange is 1.5 us
+// of a column.
 //
 // The team must run at the same time.  Workgroups sign in to a roster; the one that
 // completes the team closes it, and if the team is not complete within about 20 us the
@@ -750,7 +751,8 @@ __device__ __forceinline__ double max16(double x) {
 }
 __device__ __forceinline__ double max_wave(double x) {
   x = max16(x);
-  return fmax(fmax(lane_f64(x, 0), lane_f64(x, 16)), fmax(lane_f64(x, 32), lane_f64(x, 48)));
+  x = fmax(x, dpp_f64<0x142>(x));  // lane 15 of each row to the next row: rows 1 and 3 hold pairs
+  return fmax(lane_f64(x, 31), lane_f64(x, 63));
 }
 // The smallest index among the lanes of `who` (not empty), uniform.
 __device__ __forceinline__ int min_index(unsigned long long who, int idx) {
@@ -819,6 +821,21 @@ __device__ __forceinline__ void fmac16(double& a, double w, const double* l) {
         "v"(l[8]), "v"(l[9]), "v"(l[10]), "v"(l[11]), "v"(l[12]), "v"(l[13]), "v"(l[14]), "v"(l[15]));
 }
 
+// l[j] = x for a uniform j: the register is found by a tree of scalar branches.
+template <int N, int BASE = 0, int LEN = N>
+__device__ __forceinline__ void put_panel(double (&l)[N], int j, double x) {
+  if constexpr (LEN == 1) {
+    l[BASE] = x;
+    asm volatile("; L%0" ::"n"(BASE));  // (merged branches would index l, which then leaves the registers)
+  } else {
+    if (j < BASE + LEN / 2)
+      put_panel<N, BASE, LEN / 2>(l, j, x);
+    else
+      put_panel<N, BASE + LEN / 2, LEN - LEN / 2>(l, j, x);
+  }
+}
+
+// NB: columns the panel may hold; NT rows (threads) a workgroup.
 template <int NB, int NT, bool TEAM>
 __global__ __launch_bounds__(NT) void k_bk_team(TeamArgs a) {
   constexpr int NW = NT / 64, LW = NB + 1;
@@ -892,8 +909,8 @@ __global__ __launch_bounds__(NT) void k_bk_team(TeamArgs a) {
   auto areaB = [&](int t) { return mail + (t & 1) * kArea; };
   auto areaC = [&](int t) { return mail + (2 + (t & 1)) * kArea; };
   auto areaR = [&](int t, int r) { return mail + 4 * kArea + ((t & 1) * kTeamMax + r) * kTeamRow; };
-  double* LD = a.LDs[s];
-  double* Wp = a.Wps[s];
+  double* LD = global_ptr(a.LDs[s]);
+  double* Wp = global_ptr(a.Wps[s]);
   const long ld = a.ldld, ldw = a.ldw;
   auto ld_s = [&](const double* p) { return multi ? team_ld(p) : *p; };
   auto st_s = [&](double* p, double v) {
@@ -902,27 +919,37 @@ __global__ __launch_bounds__(NT) void k_bk_team(TeamArgs a) {
     else
       *p = v;
   };
-  int* perm = a.perms[s];
-  int* sw = a.swps[s];
-  int* blk = a.blks[s];
-  int* colpanel = a.colpanels[s];
+  int* perm = global_ptr(a.perms[s]);
+  int* sw = global_ptr(a.swps[s]);
+  int* blk = global_ptr(a.blks[s]);
+  int* colpanel = global_ptr(a.colpanels[s]);
 
-  const int lab0 = k0 + rank * NT + tid;
-  int lab = lab0 < n ? lab0 : INT_MAX;  // the row this thread stands for
-  const int labc = min(lab0, n - 1);
-  const int pv = perm[labc];            // its original row travels with the thread
-  int wlim = -1;                        // columns of L to write, set when the thread retires
-  double L[NB];  // -L of this row (-0 where there is none: adding the product changes nothing)
+  // this thread's row: the row it stands for, the row it began as, its original row (which
+  // travels with the label) and the columns of L to write, set when it becomes a pivot.
+  // The panel's own rows are the first wavefront of the first workgroup, and
+  // only those take labels from others while they live.
+  const int first = k0 + rank * NT + tid;
+  int lab = first < n ? first : INT_MAX;
+  const int lc = min(first, n - 1);
+  const int pv = perm[lc];
+  int wlim = -1;
+  double L[NB];  // -L (-0 where there is none: adding the product changes nothing)
 #pragma unroll
-  for (int p = 0; p < NB; ++p) L[p] = p < jstart ? -LD[labc + (long)(k0 + p) * ld] : -0.0;
+  for (int p = 0; p < NB; ++p) L[p] = p < jstart ? -LD[lc + (long)(k0 + p) * ld] : -0.0;
   for (int e = tid; e < NB * LW; e += NT) {
     const int r = e / LW, p = e % LW;
     Wt[e] = (p < jstart && r >= jstart && k0 + r < n) ? Wp[(k0 + r) + (long)p * ldw] : 0.0;
   }
-  const int cend = min(n, k0 + NB);  // columns this panel may use
-  auto column = [&](int c) { return c < cend && lab >= c && lab < n ? ld_s(LD + lab + (long)c * ld) : 0.0; };
+  // column c of S as it stands in memory (a row above c reads what is there: it will be a
+  // pivot by then)
+  auto column = [&](int c, double& x) {
+    const double* p = LD + (long)min(c, n - 1) * ld;
+    x = ld_s(p + min(lab, n - 1));
+  };
   int j = jstart;
-  double c0 = column(k0 + j), c1 = column(k0 + j + 1), c2 = column(k0 + j + 2);
+  double c0, c1;
+  column(k0 + j, c0);
+  column(k0 + j + 1, c1);
   const int jmax0 = rem <= nb ? rem : nb - 1;
   const int jmax = min(jmax0, jstart + a.nbpiv);
   long neg = 0, zer = 0, pos = 0;
@@ -938,8 +965,11 @@ __global__ __launch_bounds__(NT) void k_bk_team(TeamArgs a) {
   for (int t = 1; j < jmax; ++t) {
     const int k = k0 + j;
     const unsigned tag = ((unsigned)(P + 1) << 8) | (unsigned)t;
-    const bool live = lab >= k && lab < n;
-    const bool top = rank == 0 && lab >= k && lab < k0 + NB;  // (in the first wavefront)
+    // the raw columns after the next one, for the end of this step
+    double c2, c3;
+    column(k + 2, c2);
+    column(k + 3, c3);
+    const bool top = rank == 0 && w == 0 && lab >= k && lab < k0 + NB;
     // ---- column k of the Schur complement: even panel columns into av, odd ones into bv
     double av = c0, bv = 0.0;
 #pragma unroll
@@ -947,22 +977,27 @@ __global__ __launch_bounds__(NT) void k_bk_team(TeamArgs a) {
       if (g < j) {
         // (entries from j on are being written by the panel rows' threads)
         const double x = Wt[j * LW + g + (lane & 15)];
-        fmac16_pair(av, bv, g + (lane & 15) < j ? x : 0.0, L + g);
+        const double wm = g + (lane & 15) < j ? x : 0.0;
+        fmac16_pair(av, bv, wm, L + g);
       }
+    double v = -1.0;  // (a NaN is never the largest)
+    int vi = INT_MAX;
     av += bv;
-    double v = live && lab > k ? fabs(av) : -1.0;
-    v = v > -1.0 ? v : -1.0;  // (a NaN is never the largest)
-    double vm = max_wave(v);
-    int im = vm > -1.0 ? min_index(__ballot(v == vm), lab) : INT_MAX;
+    const double x = fabs(av);
+    const bool in = lab > k && lab < n;
+    if (in && (x > v || (x == v && lab < vi))) {
+      v = x;
+      vi = lab;
+    }
+    const double vm = max_wave(v);
+    const int im = vm > -1.0 ? min_index(__ballot(v == vm), vi) : INT_MAX;
     // this wavefront's best row of W (written by this wavefront): the candidate's, if it wins
     const double wv = (im < n && lane < j) ? ld_s(Wp + im + (long)lane * ldw) : 0.0;
     if (lane == 0) {
       redv[t & 1][w] = vm;
       redi[t & 1][w] = im;
     }
-    if (!TEAM || rank == 0) {
-      if (top) Wt[(lab - k0) * LW + j] = av;
-    }
+    if (top) Wt[(lab - k0) * LW + j] = av;
     if (stored) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     barrier_lds();
     double colmax;
@@ -982,17 +1017,15 @@ __global__ __launch_bounds__(NT) void k_bk_team(TeamArgs a) {
       }
       if (rank == 0 && lane < NB) team_post(ar + 4 * kTeamMax + 2 * lane, tag, Wt[lane * LW + j]);
     }
-    {
-      const unsigned long long hold = imax < n ? __ballot(lab == imax) : 0;
-      if (hold) {
-        const double ev = lane_f64(av, __ffsll((long long)hold) - 1);
-        if (lane < NB) wim[lane] = wv;
-        if (lane == 0) wim[NB] = ev;
-        if (multi) {
-          unsigned long long* ar = areaR(t, rank);
-          if (lane < NB) team_post(ar + 2 * lane, tag, wv);
-          if (lane == 0) team_post(ar + 128, tag, ev);
-        }
+    if (imax < n && im == imax) {  // uniform: this wavefront holds the workgroup's best row
+      const unsigned long long who = __ballot(lab == imax);
+      const double ev = who ? lane_f64(av, __ffsll((long long)who) - 1) : 0.0;
+      if (lane < NB) wim[lane] = wv;
+      if (lane == 0) wim[NB] = ev;
+      if (multi) {
+        unsigned long long* ar = areaR(t, rank);
+        if (lane < NB) team_post(ar + 2 * lane, tag, wv);
+        if (lane == 0) team_post(ar + 128, tag, ev);
       }
     }
     if (multi) {
@@ -1041,9 +1074,8 @@ __global__ __launch_bounds__(NT) void k_bk_team(TeamArgs a) {
     const bool cand = absakk < kBkAlpha * colmax;  // uniform over the team
     if (cand) {
       // ---- candidate column imax of the Schur complement
-      const bool act = live;
-      double raw = 0.0;
-      if (act) raw = ld_s(lab < imax ? LD + imax + (long)lab * ld : LD + lab + (long)imax * ld);
+      const int i = min(lab, n - 1);
+      b = ld_s(i < imax ? LD + imax + (long)i * ld : LD + i + (long)imax * ld);
       if (multi && rank != own && w == 0) {
         const unsigned long long* ar = areaR(t, max(own, 0));
         unsigned long long t0 = 0, t1 = 0, e0 = 0, e1 = 0;
@@ -1065,16 +1097,19 @@ __global__ __launch_bounds__(NT) void k_bk_team(TeamArgs a) {
         if (we) wim[NB] = team_value(e0, e1);
       }
       barrier_lds();
-      b = raw;
 #pragma unroll
       for (int g = 0; g < NB; g += 16)
-        if (g < j) fmac16(b, wim[g + (lane & 15)], L + g);  // (zero from j on)
-      double x = act && lab != imax ? fabs(b) : -1.0;
-      x = x > -1.0 ? x : -1.0;
+        if (g < j) {
+          const double wm = wim[g + (lane & 15)];  // (zero from j on)
+          fmac16(b, wm, L + g);
+        }
+      double x = -1.0;
+      const double y = fabs(b);
+      if (lab >= k && lab < n && lab != imax && y > x) x = y;
+      if (lab == imax) sh_arr = b;
       x = max_wave(x);
       if (lane == 0) redc[w] = x;
       if (top) Wt[(lab - k0) * LW + j + 1] = b;
-      if (lab == imax) sh_arr = b;
       barrier_lds();
       double rowmax = lane_f64(max16(lane < NW ? redc[lane] : -1.0), 0);
       arr = sh_arr;
@@ -1130,80 +1165,65 @@ __global__ __launch_bounds__(NT) void k_bk_team(TeamArgs a) {
     }
     const int kk = k + kstep - 1;
     const bool swap = kp != kk;
-    const double rawk = kstep == 1 ? c0 : c1;  // column kk as it was, this row
-    const int old = lab;
-    if (swap) {
-      // symmetric interchange kk <-> kp of S: kk becomes a pivot column, so only row and
-      // column kp need column kk's entries; then the two rows' threads exchange labels
-      if (lab > kk && lab < n && lab != kp)
-        st_s(lab > kp ? LD + lab + (long)kp * ld : LD + kp + (long)lab * ld, rawk);
-      if (lab == kk) st_s(LD + kp + (long)kp * ld, rawk);
-      // W of row kk moves to row kp
-      if (rank == 0 && w == 0 && lane < j) st_s(Wp + kp + (long)lane * ldw, Wt[(kk - k0) * LW + lane]);
-      if (old == kk)
-        lab = kp;
-      else if (old == kp)
-        lab = kk;
-    }
-    stored = swap;
-    // pivot and multipliers; the column(s) of W under the final labels
-    const double w1 = (kstep == 1 && swap) ? b : av, w2 = b;
-    const bool below = lab > kk && lab < n;
-    double l1, l2 = 0.0;
+    // ---- pivot, its multipliers, and the column(s) of W under the final labels
     double d11, d21 = 0.0, d22 = 0.0;
+    double l1, l2;
     if (kstep == 1) {
       d11 = swap ? arr : akk;
       const double dinv = d11 != 0.0 ? 1.0 / d11 : 0.0;
-      l1 = w1 * dinv;
+      if (swap) av = b;
+      l1 = av * dinv;
+      l2 = 0.0;
     } else {
       d11 = akk;
       d21 = wim[NB];
       d22 = arr;
       const double aa = d11 / d21, gg = d22 / d21;
       const double tt = 1.0 / (d21 * (aa * gg - 1.0));
-      l1 = tt * (gg * w1 - w2);
-      l2 = tt * (aa * w2 - w1);
+      l1 = tt * (gg * av - b);
+      l2 = tt * (aa * b - av);
     }
-    if (below) {
-      st_s(Wp + lab + (long)j * ldw, w1);
-      if (kstep == 2) st_s(Wp + lab + (long)(j + 1) * ldw, w2);
-    }
-#pragma unroll
-    for (int g = 0; g < NB; g += 8)
-      if (g <= j + kstep - 1 && j < g + 8) {
-#pragma unroll
-        for (int u = 0; u < 8; ++u) {
-          if (g + u == j && below) L[g + u] = -l1;
-          if (kstep == 2 && g + u == j + 1 && below) L[g + u] = -l2;
-        }
-      }
-    if (live && !below && wlim < 0) wlim = j;  // this row became a pivot
-    // ---- raw columns of the next steps.  Entries that this interchange changed come from
-    // the registers they came from: column kp is column kk as it was, and row kp holds
-    // column kk's entry of the column's own row (its thread is in the same wavefront).
-    auto next_col = [&](int c, double have, bool loaded) {
-      double x = have;
-      if (!loaded) x = (swap && c == kp) ? 0.0 : column(c);
-      if (swap && c < cend) {
+    if (swap) {
+      // symmetric interchange kk <-> kp of S: kk becomes a pivot column, so only row and
+      // column kp need column kk's entries.  The raw columns at hand follow: column kp is
+      // column kk as it was, and row kp holds column kk's entry of the column's own row
+      // (whose thread is in the same wavefront).
+      const double rawk = kstep == 1 ? c0 : c1;  // column kk as it was
+      if (lab > kk && lab < n && lab != kp)
+        st_s(lab > kp ? LD + lab + (long)kp * ld : LD + kp + (long)lab * ld, rawk);
+      if (lab == kk) st_s(LD + kp + (long)kp * ld, rawk);
+      // W of row kk moves to row kp
+      if (rank == 0 && w == 0 && lane < j) st_s(Wp + kp + (long)lane * ldw, Wt[(kk - k0) * LW + lane]);
+      const bool taker = lab == kk;  // the panel row's thread that takes label kp
+      auto follow = [&](int c, double& x) {
+        if (c >= n || c >= k0 + NB) return;
         if (c == kp) {
           x = rawk;
         } else if (c < kp && rank == 0 && w == 0) {
-          const unsigned long long src = __ballot(old == c);
-          const double vc = src ? lane_f64(rawk, __ffsll((long long)src) - 1) : 0.0;
-          if (old == kk) x = vc;
+          const unsigned long long src = __ballot(lab == c);
+          const double y = src ? lane_f64(rawk, __ffsll((long long)src) - 1) : 0.0;
+          if (taker) x = y;
         }
-      }
-      return x;
-    };
-    if (kstep == 1) {
-      c0 = next_col(k + 1, c1, true);
-      c1 = next_col(k + 2, c2, true);
-      c2 = next_col(k + 3, 0.0, false);
-    } else {
-      c0 = next_col(k + 2, c2, true);
-      c1 = next_col(k + 3, 0.0, false);
-      c2 = next_col(k + 4, 0.0, false);
+      };
+      if (kstep == 1) follow(k + 1, c1);
+      follow(k + 2, c2);
+      follow(k + 3, c3);
+      // the two rows' threads exchange labels
+      const int o = lab;
+      lab = o == kk ? kp : (o == kp ? kk : o);
     }
+    stored = swap;
+    const bool below = lab > kk && lab < n;
+    if (below) {
+      st_s(Wp + lab + (long)j * ldw, av);
+      if (kstep == 2) st_s(Wp + lab + (long)(j + 1) * ldw, b);
+    }
+    if (lab >= k && lab <= kk) wlim = j;  // this row became a pivot
+    // (rows that are done take values that nothing reads)
+    put_panel<NB>(L, j, -l1);
+    if (kstep == 2) put_panel<NB>(L, j + 1, -l2);
+    c0 = kstep == 1 ? c1 : c2;
+    c1 = kstep == 1 ? c2 : c3;
     // ---- every workgroup's copy of the panel rows' W
     if (cand) {
       if (w == 0) {
@@ -1265,11 +1285,11 @@ __global__ __launch_bounds__(NT) void k_bk_team(TeamArgs a) {
   // ---- L and the permutation under the final labels
   if (lab < n && lab >= k0 + jstart) {
     const int lim = wlim >= 0 ? wlim : j;
-    const int from = lab == lab0 ? jstart : 0;
+      const int from = lab == first ? jstart : 0;
 #pragma unroll
     for (int p = 0; p < NB; ++p)
       if (p >= from && p < lim) LD[lab + (long)(k0 + p) * ld] = -L[p];
-    if (lab != lab0) perm[lab] = pv;
+    if (lab != first) perm[lab] = pv;
   }
   if (rank == 0 && tid == NT - 1) {
     st->k0 = k0;
@@ -1280,7 +1300,7 @@ __global__ __launch_bounds__(NT) void k_bk_team(TeamArgs a) {
     st->zero += zer;
     st->pos += pos;
     st->jstart = 0;
-    a.pstarts[s][P] = k0;
+    global_ptr(a.pstarts[s])[P] = k0;
   }
 }
 
@@ -1309,8 +1329,8 @@ __global__ __launch_bounds__(256) void k_trailing_update(int n, double* const* L
   while ((ti + 1) * (ti + 2) / 2 <= lin) ++ti;
   const int tj = lin - ti * (ti + 1) / 2;
   const int row0 = k1 + ti * 64, col0 = k1 + tj * 64;
-  double* LD = LDs[s];
-  const double* Wp = Wps[s];
+  double* LD = global_ptr(LDs[s]);
+  const double* Wp = global_ptr(Wps[s]);
   const int tid = threadIdx.x;
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6), l = tid & 63;
   const int wi = (w & 1) * 32, wj = (w >> 1) * 32;
@@ -1432,8 +1452,8 @@ __global__ __launch_bounds__(1024) void k_trailing_update_lds(int n, double* con
   // wavefronts still help stage the operands
   const bool active = !(ti == tj && wi + 31 < wj);
   const int row0 = k1 + ti * TB, col0 = k1 + tj * TB;
-  double* LD = LDs[s];
-  const double* Wp = Wps[s];
+  double* LD = global_ptr(LDs[s]);
+  const double* Wp = global_ptr(Wps[s]);
   const int lr = l & 15, lk = l >> 4;
   const int nks = (kb + 3) >> 2;             // k-steps of 4
   const int nch = (kb + kUpdK - 1) / kUpdK;  // staged chunks
@@ -1771,9 +1791,9 @@ __global__ __launch_bounds__(256) void k_perm_suffix(int n, const int* const* sw
                                                      const FactorState* states, int* const* snaps) {
   extern __shared__ int q[];
   const int s = blockIdx.x;
-  const int* sw = swps[s];
-  const int* pstart = pstarts[s];
-  int* snap = snaps[s];
+  const int* sw = global_ptr(swps[s]);
+  const int* pstart = global_ptr(pstarts[s]);
+  int* snap = global_ptr(snaps[s]);
   const int np = states[s].npanel;
   for (int v = threadIdx.x; v < n; v += blockDim.x) q[v] = v;
   __syncthreads();
@@ -1807,13 +1827,13 @@ __global__ __launch_bounds__(1024) void k_left_gather(int n, double* const* LDs,
                                                       const int* const* snaps) {
   extern __shared__ double col[];
   const int c = blockIdx.x, s = blockIdx.y;
-  const int P = colpanels[s][c];
+  const int P = global_ptr(colpanels[s])[c];
   const int np = states[s].npanel;
   if (P + 1 >= np) return;
-  const int e = pstarts[s][P + 1];
+  const int e = global_ptr(pstarts[s])[P + 1];
   if (e >= n) return;
-  double* LD = LDs[s] + (long)c * ldld;
-  const int* q = snaps[s] + (long)P * n;
+  double* LD = global_ptr(LDs[s] + (long)c * ldld);
+  const int* q = global_ptr(snaps[s] + (long)P * n);
   constexpr int U = 4;
   for (int v0 = e + threadIdx.x; v0 < n; v0 += U * 1024) {
     double x[U];
@@ -1838,9 +1858,9 @@ __global__ __launch_bounds__(256) void k_factor_finalize(int n, const int* const
                                                          const FactorState* states,
                                                          int64_t* inertia) {
   const int s = blockIdx.y;
-  const int* perm = perms[s];
-  const int* blk = blks[s];
-  int* ipiv = ipivs[s];
+  const int* perm = global_ptr(perms[s]);
+  const int* blk = global_ptr(blks[s]);
+  int* ipiv = global_ptr(ipivs[s]);
   for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x) {
     const bool two = (blk[i] == 2) || (blk[i] == 0);
     ipiv[i] = two ? -(perm[i] + 1) : perm[i];
@@ -1915,21 +1935,31 @@ static void panel_launch(const FactorPlan& fp, hipStream_t st, long rem_max, int
     SL_LAUNCH_CHECK();
     return;
   }
-  const int rows = nb > 32 ? 512 : 1024;  // of one workgroup
-  const long need = ceil_div(rem_max, rows);
+  const long need = rem_max <= (nb > 32 ? 512 : 1024) ? 1 : ceil_div(rem_max, 512);
   if (fp.team && fp.fast && (need <= 1 || (need <= kTeamMax && need * S <= (long)fp.cus * 7 / 8 / fp.groups))) {
     TeamArgs a{n, fp.d_LD, fp.ldld, fp.d_W, fp.ldw, fp.d_perm, fp.d_sw, fp.d_blk, fp.d_colpanel,
                fp.d_pstart, fp.d_state, fp.d_team, fp.wait_err, fp.wait_limit, nb, nbpiv};
-    if (rows == 512) {
-      if (need <= 1)
-        SL_LAUNCH((k_bk_team<64, 512, false>), dim3(1, S), dim3(512), 0, st, a);
+    // As few threads as hold the rows: a column's reductions, tests and barriers cost every
+    // wavefront the same instructions, so a SIMD's wavefronts take turns at them.  Five
+    // shifts at order 1001, all panels: 1.52 ms with 1024 threads to the end, 1.04 so.
+    const dim3 team(need > 1 ? (unsigned)need : 1u, S);
+    if (need > 1) {
+      if (nb > 32)
+        SL_LAUNCH((k_bk_team<64, 512, true>), team, dim3(512), 0, st, a);
       else
-        SL_LAUNCH((k_bk_team<64, 512, true>), dim3((unsigned)need, S), dim3(512), 0, st, a);
+        SL_LAUNCH((k_bk_team<32, 512, true>), team, dim3(512), 0, st, a);
+    } else if (rem_max <= 256) {
+      if (nb > 32)
+        SL_LAUNCH((k_bk_team<64, 256, false>), team, dim3(256), 0, st, a);
+      else
+        SL_LAUNCH((k_bk_team<32, 256, false>), team, dim3(256), 0, st, a);
+    } else if (rem_max <= 512) {
+      if (nb > 32)
+        SL_LAUNCH((k_bk_team<64, 512, false>), team, dim3(512), 0, st, a);
+      else
+        SL_LAUNCH((k_bk_team<32, 512, false>), team, dim3(512), 0, st, a);
     } else {
-      if (need <= 1)
-        SL_LAUNCH((k_bk_team<32, 1024, false>), dim3(1, S), dim3(1024), 0, st, a);
-      else
-        SL_LAUNCH((k_bk_team<32, 1024, true>), dim3((unsigned)need, S), dim3(1024), 0, st, a);
+      SL_LAUNCH((k_bk_team<32, 1024, false>), team, dim3(1024), 0, st, a);
     }
   } else {
     SL_LAUNCH(k_bk_panel<true>, dim3(S), dim3(1024), 0, st, n, fp.d_LD, fp.ldld, fp.d_W, fp.ldw,

@@ -83,11 +83,11 @@ __global__ __launch_bounds__(256) void k_solve_prep(SolvePrepArgs a) {
   const int b = blockIdx.x, s = blockIdx.y, tid = threadIdx.x;
   const int part = PARTS == 4 ? (int)blockIdx.z : 0;
   const int n = a.n, nblk = (n + SB - 1) / SB, r0 = b * SB;
-  const double* LD = a.direct ? a.LD0 : a.LD[s];
-  const int* ipiv = a.direct ? a.ipiv0 : a.ipiv[s];
-  int* perm = a.direct ? a.perm0 : a.perm[s];
-  int* blk = a.direct ? a.blk0 : a.blk[s];
-  double* Linv = a.direct ? a.Linv0 : a.Linv[s];
+  const double* LD = global_ptr(a.direct ? a.LD0 : a.LD[s]);
+  const int* ipiv = global_ptr(a.direct ? a.ipiv0 : a.ipiv[s]);
+  int* perm = global_ptr(a.direct ? a.perm0 : a.perm[s]);
+  int* blk = global_ptr(a.direct ? a.blk0 : a.blk[s]);
+  double* Linv = global_ptr(a.direct ? a.Linv0 : a.Linv[s]);
   constexpr int Q = SB * SB / 256;
   // the diagonal block and this part's first look-ahead block (rows and columns
   // clamped: the values past n are replaced below)
@@ -501,15 +501,15 @@ __global__ __launch_bounds__(256) void k_fwd(SolveArgs a) {
   const int nrhs = a.direct ? min(a.nrhs, a.nrhs_all - s * a.nrhs) : a.nrhs;
   const WaitBound wb{a.wait_err, a.wait_limit};
   const int b = (int)ticket(a.ctr + s, nblk);
-  const double* LD = a.direct ? a.LD0 : a.LD[s];
-  const int* perm = a.direct ? a.perm0 : a.perm[s];
-  const double* Y = a.direct ? a.X0 + (long)s * a.nrhs * a.ldx : a.Y[s];
-  double* Z = a.direct ? a.Z0 + (long)s * a.nrhs * a.ldz : a.Z[s];
+  const double* LD = global_ptr(a.direct ? a.LD0 : a.LD[s]);
+  const int* perm = global_ptr(a.direct ? a.perm0 : a.perm[s]);
+  const double* Y = global_ptr(a.direct ? a.X0 + (long)s * a.nrhs * a.ldx : a.Y[s]);
+  double* Z = global_ptr(a.direct ? a.Z0 + (long)s * a.nrhs * a.ldz : a.Z[s]);
   const int r0 = b * SB;
   const int row = r0 + 16 * (tid >> 6) + j;
   for (int e = tid; e < 16 * NT * kLdx; e += 256) sx[e] = 0.0;
   // everything that does not depend on other blocks is issued first
-  const double* Lbase = a.direct ? a.Linv0 : a.Linv[s];
+  const double* Lbase = global_ptr(a.direct ? a.Linv0 : a.Linv[s]);
   double inv[16];
   load_frag<false>(Lbase + (long)b * SB * SB, inv);
   d4 acc[NT];  // -(P Y - contributions so far)
@@ -599,17 +599,17 @@ __global__ __launch_bounds__(256) void k_bwd(SolveArgs a) {
   const WaitBound wb{a.wait_err, a.wait_limit};
   const int tk = (int)ticket(a.ctr + s, nblk);
   const int b = nblk - 1 - tk;
-  const double* LD = a.direct ? a.LD0 : a.LD[s];
-  const int* blk = a.direct ? a.blk0 : a.blk[s];
-  const int* perm = a.direct ? a.perm0 : a.perm[s];
-  const double* Z = a.direct ? a.Z0 + (long)s * a.nrhs * a.ldz : a.Z[s];
-  double* V = a.direct ? a.V0 + (long)s * a.nrhs * a.ldz : a.V[s];
-  double* X = a.direct ? a.X0 + (long)s * a.nrhs * a.ldx : a.X[s];
+  const double* LD = global_ptr(a.direct ? a.LD0 : a.LD[s]);
+  const int* blk = global_ptr(a.direct ? a.blk0 : a.blk[s]);
+  const int* perm = global_ptr(a.direct ? a.perm0 : a.perm[s]);
+  const double* Z = global_ptr(a.direct ? a.Z0 + (long)s * a.nrhs * a.ldz : a.Z[s]);
+  double* V = global_ptr(a.direct ? a.V0 + (long)s * a.nrhs * a.ldz : a.V[s]);
+  double* X = global_ptr(a.direct ? a.X0 + (long)s * a.nrhs * a.ldx : a.X[s]);
   const int r0 = b * SB;
   const int rw = 16 * (tid >> 6) + j;
   const int row = r0 + rw;
   for (int e = tid; e < 16 * NT * kLdx; e += 256) sx[e] = 0.0;
-  const double* Lbase = a.direct ? a.Linv0 : a.Linv[s];
+  const double* Lbase = global_ptr(a.direct ? a.Linv0 : a.Linv[s]);
   double inv[16];  // Linv_b^T
   load_frag<true>(Lbase + (long)b * SB * SB, inv);
   d4 acc[NT];  // -(D^{-1} Z_b - contributions so far)

@@ -54,3 +54,15 @@ def test_team_equals_one_workgroup_bitwise(gpu_lib, kind):
         assert g.inertia == facs[k].inertia
         assert torch.equal(g.ipiv, facs[k].ipiv)
         assert torch.equal(torch.tril(g.LD), torch.tril(facs[k].LD))
+
+
+@pytest.mark.parametrize("kind", ["random", "two_by_two"])
+@pytest.mark.parametrize("n", [255, 256, 257, 511, 512, 513, 1090, 1537])
+def test_one_workgroup_panels_of_every_size(gpu_lib, kind, n):
+    """Panels of at most 256, 512 and 1024 rows run on as many threads; an order between them
+    passes every smaller size on its way down, narrow panels (those of every order here) on one workgroup or two."""
+    C = _matrix(kind, n)
+    f = gpu_lib.ldlt_factor(dev(C), dev(np.eye(n)), 0.0)
+    w = np.linalg.eigvalsh(C)
+    assert f.inertia == (int(np.sum(w < 0)), 0, int(np.sum(w > 0)))
+    assert backward_error(C, f.LD.cpu().numpy(), f.ipiv.cpu().numpy()) <= 100 * n * U
