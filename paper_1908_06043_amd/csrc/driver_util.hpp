@@ -208,10 +208,13 @@ inline void gemm(Ctx& c, bool ta, bool tb, const std::vector<int>& m, const std:
   g.beta = beta;
   int splits = 1;
   const long tiles = ceil_div(mmax, 64) * ceil_div(nmax, 64) * (long)batch;
-  if (kmax >= 1024 && tiles < 512) {
-    // splits at least 256 deep; 64 deep (four K chunks) for outputs of a few tiles,
-    // the Gram-type products V^T w of the reorthogonalisations
-    splits = (int)std::min<long>(std::max<long>(1, 1024 / tiles), kmax / (tiles < 16 ? 64 : 256));
+  if (kmax >= 256 && tiles < 512) {
+    // A tile's chain is 0.9 us per 16 of K, the reduction's launch about 4 us: from 256 on
+    // splitting wins (order 1000, one tile column: 58 us whole, 10 split, and 4 to reduce).
+    // Splits at least 256 deep; 64 deep (four K chunks) for outputs of a few tiles: the
+    // Gram-type products V^T w of the reorthogonalisations and a matrix of order up to
+    // 1024 with one tile of columns (solve of order 1000: 128 deep 21.0 ms, 64 deep 20.4).
+    splits = (int)std::min<long>(std::max<long>(1, 1024 / tiles), kmax / (tiles <= 16 ? 64 : 256));
     splits = std::max(1, std::min(splits, 64));
   }
   g.splits = splits;
