@@ -22,6 +22,7 @@
 // progress lives in device memory (FactorState) and the host launches an upper
 // bound of panel/update pairs; launches past the end return at once.
 #include <algorithm>
+#include <cfloat>
 #include <climits>
 
 #include "common.hpp"
@@ -114,222 +115,238 @@ __global__ __launch_bounds__(256) void k_factor_init(int n, FactorState* states,
 // Bunch-Kaufman takes a 1x1 pivot without interchange at column k exactly when
 // |d_k| >= alpha * max_{i>k} |s_ik| for the Schur-complement column s at step k.
 // As long as that holds for every column, the factorization is the pivot-free
-// LDL^T, which parallelises like Cholesky: the panel's diagonal block is factored
-// in LDS (k_fast_diag4), the rows below follow from one triangular solve with the
-// block (k_fast_trsm: W21 = C21 L11^{-T}) together with the column maxima of |W|,
-// and k_fast_commit accepts the longest prefix of columns that pass the test and
-// writes their L = W D^{-1}.  The pivoting panel kernel then continues from the first
+// LDL^T, which parallelises like Cholesky: k_fast_panel factors the panel's diagonal
+// block, solves for the rows below and tests every column, and k_fast_commit accepts
+// the longest prefix of columns that pass and writes their L = W D^{-1}.  The pivoting panel kernel then continues from the first
 // rejected column, so the result is the Bunch-Kaufman factorization itself.
 
-__device__ __forceinline__ double u64_to_f64(unsigned long long v) { return __longlong_as_double((long long)v); }
+// a[i] += m[lane i of the row] * f for the 16 registers a: m supplies one multiplier a lane, the
+// same in each row of 16 lanes.  (s_nop: a DPP source written by the instruction before.)
+__device__ __forceinline__ void axpy16(double* a, double m, double f) {
+  asm("s_nop 1\n\t"
+      "v_fmac_f64_dpp %0, %16, %17 row_newbcast:0 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f64_dpp %1, %16, %17 row_newbcast:1 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f64_dpp %2, %16, %17 row_newbcast:2 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f64_dpp %3, %16, %17 row_newbcast:3 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f64_dpp %4, %16, %17 row_newbcast:4 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f64_dpp %5, %16, %17 row_newbcast:5 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f64_dpp %6, %16, %17 row_newbcast:6 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f64_dpp %7, %16, %17 row_newbcast:7 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f64_dpp %8, %16, %17 row_newbcast:8 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f64_dpp %9, %16, %17 row_newbcast:9 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f64_dpp %10, %16, %17 row_newbcast:10 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f64_dpp %11, %16, %17 row_newbcast:11 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f64_dpp %12, %16, %17 row_newbcast:12 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f64_dpp %13, %16, %17 row_newbcast:13 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f64_dpp %14, %16, %17 row_newbcast:14 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f64_dpp %15, %16, %17 row_newbcast:15 row_mask:0xf bank_mask:0xf"
+      : "+v"(a[0]), "+v"(a[1]), "+v"(a[2]), "+v"(a[3]), "+v"(a[4]), "+v"(a[5]), "+v"(a[6]), "+v"(a[7]),
+        "+v"(a[8]), "+v"(a[9]), "+v"(a[10]), "+v"(a[11]), "+v"(a[12]), "+v"(a[13]), "+v"(a[14]), "+v"(a[15])
+      : "v"(m), "v"(f));
+}
 
+__device__ __forceinline__ double lane_f64(double x, int lane) {
+  const long long u = __double_as_longlong(x);
+  const unsigned lo = (unsigned)__builtin_amdgcn_readlane((int)u, lane);
+  const unsigned hi = (unsigned)__builtin_amdgcn_readlane((int)(u >> 32), lane);
+  return __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
+}
 
-// Pivot-free LDL^T of the panel's diagonal block (nbe <= NB columns), one
-// 256-thread workgroup per shift: lane q of row i holds the columns q + 4m of the
-// row, so each step's update is a quarter of the row per lane, at the price of two
-// workgroup barriers per step (the pivot and the multipliers l_ck = A[c][k] / d go
-// through LDS).  The register window is rotated by one register every four steps,
-// which keeps every register index static (the pivot column of step k = t0 + kk is
-// register 0 of the lanes q == kk).  The finished W columns are kept in LDS for the
-// outputs: the block's rows of W (unscaled), D, the in-block column maxima of |W|,
-// and L11 column-major for the row solves of k_fast_trsm.
-template <int NB>
-__global__ __launch_bounds__(256) void k_fast_diag4(int n, const double* const* LDs, long ldld,
+// The pivot-free panel: LDL^T of the diagonal block (nbe <= NB columns), the rows below it,
+// W21 = C21 L11^{-T} by forward substitution along each row, and the columns that fail the
+// test, one bit a column.
+//
+// What bounds it: the chain of the diagonal block, a pivot, its reciprocal and the
+// multipliers, column by column.  One wavefront factors the block with a row a lane and the
+// columns in registers: no barrier in the chain (a column's multipliers go through LDS to
+// the lanes that broadcast them).  Every workgroup factors the block for itself, its fifth
+// wavefront ahead of the four that hold a row a lane and follow U columns behind, so the
+// rows cost neither a launch nor time of their own.  Columns sit in registers from the
+// current one on and move down every U columns, so that a column's register is known at
+// compile time in a loop small enough for the instruction cache; whole groups of 16 past
+// the block are skipped.
+//
+// The test |d_k| >= alpha max_i |w_ik| holds exactly when it holds for every i, rounding
+// being monotone, so a comparison per element and a bit per column replace the maxima; without
+// the test (B of a definite pencil) an entry has to be finite.
+//
+// Measured, per launch: order 4096, 17 shifts 72 us as a launch for the block (four lanes a
+// row, two barriers a column) and one for the rows, 29.5 so; order 2048, one matrix 55 and
+// 23.4; order 1001, five shifts, 32 columns 23 and 11.7.  A column of the block is about 380
+// cycles, one of the rows 360; without following one behind the other: 38 us at 4096.
+template <int NB, bool PIVOT>
+__global__ __launch_bounds__(320) void k_fast_panel(int n, const double* const* LDs, long ldld,
                                                     double* const* Wps, long ldw,
                                                     double* const* auxs,
                                                     const FactorState* states, int nb) {
-  constexpr int M = NB / 4;
-  __shared__ double Wb[NB][NB + 1];  // Wb[i][k]: final W of column k (rows >= k)
-  __shared__ double lcol[2 * NB];    // multipliers; zero past NB (window registers past the block)
-  __shared__ double dsh;
-  const int s = blockIdx.x, tid = threadIdx.x;
-  const int i = tid >> 2, q = tid & 3;
-  const FactorState st = states[s];
-  const int k0 = st.k0 + st.kb;
-  if (st.done || k0 >= n) return;
-  const int nbe = min(nb, n - k0);
-  const double* LD = global_ptr(LDs[s]);
-  double* Wp = global_ptr(Wps[s]);
-  double* aux = global_ptr(auxs[s]);
-  double* Dv = aux;
-  double* cin = aux + nb;
-  unsigned long long* cout = reinterpret_cast<unsigned long long*>(aux + 2 * nb);
-  double* L11 = aux + 3 * nb;  // column-major nb x nb, strictly lower part
-  const bool row_ok = i < NB && i < nbe;
-  double a[M];  // a[m] = A[i][t0 + q + 4m] for the current group start t0
-#pragma unroll
-  for (int m = 0; m < M; ++m) {
-    const int c = q + 4 * m;
-    a[m] = (row_ok && c < nbe && i >= c) ? LD[(k0 + i) + (long)(k0 + c) * ldld] : 0.0;
-  }
-  for (int c = tid; c < nb; c += 256) cout[c] = 0ull;
-  for (int c = tid; c < 2 * NB; c += 256) lcol[c] = 0.0;
-  for (int t0 = 0; t0 < nbe; t0 += 4) {
-#pragma unroll
-    for (int kk = 0; kk < 4; ++kk) {
-      const int k = t0 + kk;
-      if (k < nbe) {
-        // the pivot column k is register 0 of the lanes q == kk
-        if (q == kk && i < NB) {
-          Wb[i][k] = a[0];
-          if (i == k) dsh = a[0];
-        }
-        __syncthreads();
-        const double r = 1.0 / dsh;
-        if (q == kk && i < NB) lcol[i] = a[0] * r;
-        __syncthreads();
-        const double ak = (i < NB) ? Wb[i][k] : 0.0;
-        // A[i][c] -= A[i][k] l_ck for the columns c = t0 + q + 4m > k of the window
-        // (registers past column NB - 1 hold no column and meet zero multipliers)
-        const double* lc = lcol + t0 + q;
-        if (q > kk) a[0] -= ak * lc[0];
-#pragma unroll
-        for (int m = 1; m < M; ++m) a[m] -= ak * lc[4 * m];
-      }
-    }
-    __syncthreads();  // lcol of this group is read before the next group rewrites it
-#pragma unroll
-    for (int m = 0; m + 1 < M; ++m) a[m] = a[m + 1];
-    a[M - 1] = 0.0;
-  }
-  __syncthreads();
-  // outputs: rows i >= k of each column k, coalesced over rows
-  for (int e = tid; e < NB * NB; e += 256) {
-    const int r = e % NB, k = e / NB;
-    if (k < nbe && r < nbe) {
-      const double w = Wb[r][k];
-      const double lv = (r > k) ? w * (1.0 / Wb[k][k]) : 0.0;
-      if (r >= k) Wp[(k0 + r) + (long)k * ldw] = w;
-      L11[r + (long)k * nb] = lv;
-    }
-  }
-  // in-block column maxima below the diagonal: lane q takes the rows r = i + 1 + q + 4t
-  {
-    double mx = 0.0;
-    if (row_ok) {
-      for (int r = i + 1 + q; r < nbe; r += 4) {
-        const double v = fabs(Wb[r][i]);
-        mx = (v > mx || v != v) ? v : mx;
-      }
-    }
-#pragma unroll
-    for (int off = 1; off < 4; off <<= 1) {
-      const double o = __shfl_xor(mx, off);
-      mx = (o > mx || o != o) ? o : mx;
-    }
-    if (row_ok && q == 0) {
-      cin[i] = mx;
-      Dv[i] = Wb[i][i];
-    }
-  }
-}
-
-// Rows below the diagonal block: W21 = C21 L11^{-T} by forward substitution
-// along each row (w_c = c_c - sum_{q<c} w_q L11[c][q], taken right-looking so the
-// updates of one step are independent) and the column maxima of |W21| (atomic max
-// on the bit patterns of non-negative doubles).  The rows
-// below a panel are too few to give every SIMD a wavefront when each is one
-// thread, so a row is shared by four consecutive lanes: lane g of a row holds
-// columns g, g + 4, ... (registers rotated by one every four steps, so the
-// column of step q is always register 0 of lane q % 4), and w_q reaches the
-// row's other lanes with a shuffle.  64 rows per 256-thread workgroup; L11 is
-// read from LDS.
-template <int NB>
-__global__ __launch_bounds__(256) void k_fast_trsm(int n, const double* const* LDs, long ldld,
-                                                   double* const* Wps, long ldw,
-                                                   const double* const* auxs,
-                                                   const FactorState* states, int nb) {
-  constexpr int M = NB / 4;
-  __shared__ double sL[NB * NB];  // column-major: sL[q * NB + c] = L11[c][q]
+  constexpr int U = 8, G = NB / 16;
+  // Column k of W and of L11 at [k * NB], for rows (of the block) past k.  What lies before,
+  // and past the block, is read as well, into registers that hold no live column.
+  __shared__ double sW[NB * NB];
+  __shared__ double sL[NB * NB + 64];
+  __shared__ unsigned long long sBad;
+  __shared__ int sDone;  // columns whose W and L11 are in LDS
   const int s = blockIdx.y, tid = threadIdx.x;
+  const int w = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
   const FactorState st = states[s];
   const int k0 = st.k0 + st.kb;
   if (st.done || k0 >= n) return;
-  const int nbe = min(nb, n - k0);
-  const int r0 = k0 + nbe + 64 * blockIdx.x;
-  if (r0 >= n) return;
+  const int nbe = __builtin_amdgcn_readfirstlane(min(nb, n - k0));
   const double* LD = global_ptr(LDs[s]);
   double* Wp = global_ptr(Wps[s]);
-  const double* aux = global_ptr(auxs[s]);
-  unsigned long long* cout = reinterpret_cast<unsigned long long*>(const_cast<double*>(aux) + 2 * nb);
-  const double* L11 = aux + 3 * nb;
-  for (int e = tid; e < NB * NB; e += 256) {
-    const int c = e % NB, q = e / NB;
-    sL[e] = (c < nbe && q < nbe) ? L11[c + (long)q * nb] : 0.0;
-  }
-  const int g = tid & 3;
-  const int row = r0 + (tid >> 2);
-  const bool rv = row < n;
-  const double* Cr = LD + (rv ? row : n - 1) + (long)k0 * ldld;
-  double w[M];  // w[m] = W[row][t0 + g + 4m] for the current group start t0
+  double* Dv = global_ptr(auxs[s]);
+  unsigned long long* bad_of = reinterpret_cast<unsigned long long*>(Dv + nb);
+  double x[NB];
+  // (a row past the end stands for the last row once more; so does a column)
+  auto load = [&](int first) {
+    const double* p = LD + min(first + lane, n - 1) + (long)k0 * ldld;
 #pragma unroll
-  for (int m = 0; m < M; ++m) {
-    const int c = g + 4 * m;
-    w[m] = (c < nbe) ? Cr[(long)c * ldld] : 0.0;
+    for (int m = 0; m < NB; ++m) {
+      x[m] = *p;
+      p += m + 1 < nbe ? ldld : 0;
+    }
+  };
+  // (loads and stores share a counter: a load still in flight would make each column wait for
+  // the stores of the column before)
+  auto arrived = [] { __builtin_amdgcn_s_waitcnt(0x0f70); };  // vmcnt(0)
+  auto shift = [&]() {
+#pragma unroll
+    for (int m = 0; m < NB; ++m) x[m] = m + U < NB ? x[m + U] : 0.0;
+  };
+  auto passes = [](double wk, double d) {
+    return PIVOT ? kBkAlpha * fabs(wk) <= fabs(d) : fabs(wk) <= DBL_MAX;
+  };
+  if (tid == 0) {
+    sBad = 0;
+    sDone = 0;
   }
   __syncthreads();
-  const int lane0 = (tid & 63) & ~3;
-  for (int t0 = 0; t0 < nbe; t0 += 4) {
+  unsigned long long bad = 0;
+  if (w == 4) {
+    __builtin_amdgcn_s_setprio(3);  // (it shares a SIMD with one of the others)
+    load(k0);
+    arrived();
+    double* wc = sW + lane;
+    double* lc = sL + lane;
+    auto multipliers = [&](double a, int k) {  // column k of the block
+      const double l = a * (1.0 / lane_f64(a, min(k, 63)));
+      if (NB == 64 || lane < NB) {
+        wc[k * NB] = a;
+        lc[k * NB] = l;
+      }
+    };
+    multipliers(x[0], 0);
+#pragma unroll 1
+    for (int t0 = 0; t0 < nbe; t0 += U) {
+      int left = nbe - t0;
 #pragma unroll
-    for (int kk = 0; kk < 4; ++kk) {
-      const int q = t0 + kk;
-      if (q < nbe) {
-        const double wq = __shfl(w[0], lane0 | kk);
-        const double* Lq = sL + q * NB;
-        // register m holds column c = t0 + g + 4m; it is updated when c > q
-        const double u0 = w[0] - wq * Lq[min(t0 + g, NB - 1)];
-        w[0] = (g > kk) ? u0 : w[0];
+      for (int kk = 0; kk < U; ++kk) {
+        const int k = t0 + kk;
+        const double f = -x[kk];
+        const double* mp = sL + k * NB + t0 + (lane & 15);
+        double m[G];
 #pragma unroll
-        for (int m = 1; m < M; ++m) w[m] -= wq * Lq[min(t0 + g + 4 * m, NB - 1)];
+        for (int g = 0; g < G; ++g) m[g] = mp[16 * g];
+        axpy16(x, m[0], f);
+        // the next column is complete: its multipliers start before the columns to the right
+        if (k + 1 < NB) multipliers(x[kk + 1], k + 1);
+        asm volatile("" : "+s"(left));  // (compared here: not kept for every column, or copied)
+#pragma unroll
+        for (int g = 1; g < G; ++g)
+          if (16 * g < left) axpy16(x + 16 * g, m[g], f);
+      }
+      // (LDS takes a wavefront's accesses in order)
+      asm volatile("" ::: "memory");
+      if (lane == 0) __hip_atomic_store(&sDone, t0 + U, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+      shift();
+    }
+    __builtin_amdgcn_s_setprio(0);
+    if (blockIdx.x == 0) {
+      if (lane < nbe) {
+        const double d = sW[lane * (NB + 1)];
+        Dv[lane] = d;
+        if (!(isfinite(d) && d != 0.0)) bad = 1ull << lane;
+      }
+      if (bad) atomicOr(&sBad, bad);
+      bad = 0;
+#pragma unroll 8
+      for (int k = 0; k < nbe; ++k) {
+        const double wk = sW[k * NB + min(lane, NB - 1)], d = sW[k * (NB + 1)];
+        if (lane >= k && lane < nbe) Wp[(k0 + lane) + (long)k * ldw] = wk;
+        bad |= lane > k && lane < nbe && !passes(wk, d) ? 1ull << k : 0ull;
+      }
+      if (bad) atomicOr(&sBad, bad);
+    }
+  } else {
+    for (int r0 = k0 + nbe + 256 * (int)blockIdx.x + 64 * w; r0 < n; r0 += 256 * (int)gridDim.x) {
+      load(r0);
+      arrived();
+      double* out = Wp + min(r0 + lane, n - 1);
+#pragma unroll 1
+      for (int t0 = 0; t0 < nbe; t0 += U) {
+        while (__hip_atomic_load(&sDone, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) <= t0)
+          __builtin_amdgcn_s_sleep(1);
+        asm volatile("" ::: "memory");
+        const double* mp = sL + t0 * NB + t0 + (lane & 15);
+        const double* dp = sW + t0 * (NB + 1);
+        double m[2][G], d[2];
+        auto fetch = [&](int kk) {
+#pragma unroll
+          for (int g = 0; g < G; ++g) m[kk & 1][g] = mp[kk * NB + 16 * g];
+          d[kk & 1] = dp[kk * (NB + 1)];
+        };
+        int left = nbe - t0;
+        unsigned long long fail[U];
+        fetch(0);
+#pragma unroll
+        for (int kk = 0; kk < U; ++kk) {
+          asm volatile("" : "+s"(left));
+          if (kk + 1 < U) fetch(kk + 1);
+          const double wk = x[kk];
+          if (kk < left) *out = wk;
+          fail[kk] = __ballot(!passes(wk, d[kk & 1]));
+          out += ldw;
+#pragma unroll
+          for (int g = 0; g < G; ++g)
+            if (g == 0 || 16 * g < left) axpy16(x + 16 * g, m[kk & 1][g], -wk);
+        }
+        unsigned bits = 0;
+#pragma unroll
+        for (int kk = 0; kk < U; ++kk) bits |= fail[kk] ? 1u << kk : 0u;
+        bad |= (unsigned long long)bits << t0;
+        shift();
       }
     }
-    // column t0 + g is final: write it, fold it into the column maximum, rotate
-    const int c0 = t0 + g;
-    if (rv && c0 < nbe) Wp[row + (long)c0 * ldw] = w[0];
-    double mx = (rv && c0 < nbe) ? fabs(w[0]) : 0.0;
-    if (mx != mx) mx = __longlong_as_double(0x7FF0000000000000ll);  // NaN ranks as +inf
-#pragma unroll
-    for (int off = 4; off < 64; off <<= 1) mx = fmax(mx, __shfl_xor(mx, off));
-    if ((tid & 63) < 4 && c0 < nbe)
-      atomicMax(cout + c0, (unsigned long long)__double_as_longlong(mx));
-#pragma unroll
-    for (int m = 0; m + 1 < M; ++m) w[m] = w[m + 1];
-    w[M - 1] = 0.0;
+    if (lane == 0 && bad) atomicOr(&sBad, bad);
   }
+  __syncthreads();
+  if (tid == 0) bad_of[blockIdx.x] = sBad;
 }
 
-template <bool PIVOT>
+// Accepts the longest prefix of columns that passed in every one of the `groups` workgroups of
+// k_fast_panel and writes their L = W D^{-1}.
 __global__ __launch_bounds__(256) void k_fast_commit(int n, double* const* LDs, long ldld,
                                                      const double* const* Wps, long ldw,
                                                      const double* const* auxs, int* const* blks,
                                                      int* const* colpanels, FactorState* states,
-                                                     unsigned long long* teams, int nb) {
-  __shared__ int js;
+                                                     unsigned long long* teams, int nb, int groups) {
+  __shared__ unsigned long long bad;
   const int s = blockIdx.y, c = blockIdx.x, tid = threadIdx.x;
   const FactorState st = states[s];
   const int k0 = st.k0 + st.kb;
   if (st.done || k0 >= n) return;
   const int nbe = min(nb, n - k0);
   if (c >= nbe) return;
-  const double* aux = global_ptr(auxs[s]);
-  const double* Dv = aux;
-  const double* cin = aux + nb;
-  const unsigned long long* cout = reinterpret_cast<const unsigned long long*>(aux + 2 * nb);
-  // the accepted prefix: lane j of the first wavefront judges column j (nbe <= 64),
-  // and the first rejected column is the lowest set bit of the ballot
-  if (tid < 64) {
-    const int j = tid;
-    bool ok = false;
-    if (j < nbe) {
-      const double d = Dv[j];
-      const double cm = fmax(cin[j], u64_to_f64(cout[j]));
-      ok = isfinite(d) && d != 0.0 && isfinite(cm) && cin[j] == cin[j];
-      if (PIVOT) ok = ok && fabs(d) >= kBkAlpha * cm;
-    }
-    const unsigned long long bad = __ballot(!ok);
-    if (tid == 0) js = bad ? min(__ffsll((long long)bad) - 1, nbe) : nbe;
+  const double* Dv = global_ptr(auxs[s]);
+  const unsigned long long* bad_of = reinterpret_cast<const unsigned long long*>(Dv + nb);
+  if (tid == 0) bad = 0;
+  __syncthreads();
+  if (tid < groups) {
+    const unsigned long long b = bad_of[tid];
+    if (b) atomicOr(&bad, b);
   }
   __syncthreads();
+  const int js = bad ? min(__ffsll((long long)bad) - 1, nbe) : nbe;
   const int jst = js;
   if (c < jst) {
     double* LD = global_ptr(LDs[s]);
@@ -735,12 +752,6 @@ __device__ __forceinline__ double dpp_f64(double x) {
   const int lo = __builtin_amdgcn_mov_dpp((int)v, CTRL, 0xf, 0xf, true);
   const int hi = __builtin_amdgcn_mov_dpp((int)(v >> 32), CTRL, 0xf, 0xf, true);
   return __longlong_as_double(((long long)hi << 32) | (unsigned)lo);
-}
-__device__ __forceinline__ double lane_f64(double x, int lane) {
-  const long long v = __double_as_longlong(x);
-  const unsigned lo = __builtin_amdgcn_readlane((int)v, lane);
-  const unsigned hi = __builtin_amdgcn_readlane((int)(v >> 32), lane);
-  return __longlong_as_double(((long long)hi << 32) | lo);
 }
 // The maximum over a row of 16 lanes, in each of them; over the wavefront, uniform.
 __device__ __forceinline__ double max16(double x) {
@@ -1982,38 +1993,17 @@ static void factor_step(const FactorPlan& fp, hipStream_t st, long k0_lb, sislic
     // one timed ticket per panel step: the speculative group and the pivoting
     // panel are consecutive launches of the panel class
     tpan = prof_begin(ph, kProfPanel, st);
-    const long rows = n - k0_lb - 1;
-    if (nb > 32) {
-      SL_LAUNCH(k_fast_diag4<64>, dim3(S), dim3(256), 0, st, n, (const double* const*)fp.d_LD,
-                fp.ldld, fp.d_W, fp.ldw, fp.d_aux, fp.d_state, nb);
-      SL_LAUNCH_CHECK();
-      if (rows > 0) {
-        SL_LAUNCH(k_fast_trsm<64>, dim3((unsigned)ceil_div(rows, 64), S), dim3(256), 0, st, n,
-                  (const double* const*)fp.d_LD, fp.ldld, fp.d_W, fp.ldw,
-                  (const double* const*)fp.d_aux,
-                  fp.d_state, nb);
-        SL_LAUNCH_CHECK();
-      }
-    } else {
-      SL_LAUNCH(k_fast_diag4<32>, dim3(S), dim3(256), 0, st, n, (const double* const*)fp.d_LD,
-                fp.ldld, fp.d_W, fp.ldw, fp.d_aux, fp.d_state, nb);
-      SL_LAUNCH_CHECK();
-      if (rows > 0) {
-        SL_LAUNCH(k_fast_trsm<32>, dim3((unsigned)ceil_div(rows, 64), S), dim3(256), 0, st, n,
-                  (const double* const*)fp.d_LD, fp.ldld, fp.d_W, fp.ldw,
-                  (const double* const*)fp.d_aux,
-                  fp.d_state, nb);
-        SL_LAUNCH_CHECK();
-      }
-    }
-    if (fp.pivot)
-      SL_LAUNCH(k_fast_commit<true>, dim3(nb, S), dim3(256), 0, st, n, fp.d_LD, fp.ldld,
-                (const double* const*)fp.d_W, fp.ldw, (const double* const*)fp.d_aux, fp.d_blk,
-                fp.d_colpanel, fp.d_state, fp.d_team, nb);
-    else
-      SL_LAUNCH(k_fast_commit<false>, dim3(nb, S), dim3(256), 0, st, n, fp.d_LD, fp.ldld,
-                (const double* const*)fp.d_W, fp.ldw, (const double* const*)fp.d_aux, fp.d_blk,
-                fp.d_colpanel, fp.d_state, fp.d_team, nb);
+    // a workgroup per 256 rows below the block, as many as run side by side (two a CU)
+    const int groups = (int)std::max<long>(
+        1, std::min<long>({ceil_div(n - k0_lb - 1, 256), (long)kSpecGroups, 2l * fp.cus / S}));
+    const auto panel = nb > 32 ? (fp.pivot ? k_fast_panel<64, true> : k_fast_panel<64, false>)
+                               : (fp.pivot ? k_fast_panel<32, true> : k_fast_panel<32, false>);
+    SL_LAUNCH(panel, dim3((unsigned)groups, S), dim3(320), 0, st, n, (const double* const*)fp.d_LD,
+              fp.ldld, fp.d_W, fp.ldw, fp.d_aux, fp.d_state, nb);
+    SL_LAUNCH_CHECK();
+    SL_LAUNCH(k_fast_commit, dim3(nb, S), dim3(256), 0, st, n, fp.d_LD, fp.ldld,
+              (const double* const*)fp.d_W, fp.ldw, (const double* const*)fp.d_aux, fp.d_blk,
+              fp.d_colpanel, fp.d_state, fp.d_team, nb, groups);
     SL_LAUNCH_CHECK();
   }
   if (tpan < 0) tpan = prof_begin(ph, kProfPanel, st);

@@ -182,7 +182,7 @@ FactorPlan build_factor(sislice_handle* h, int bufid, int n, const double* A, lo
   z.take<FactorState>(S);
   z.take<int64_t>(3 * (size_t)S);
   z.take<void*>(10 * (size_t)S);
-  z.take<double>((size_t)S * (3 * nb + nb * nb));   // aux
+  z.take<double>((size_t)S * (nb + kSpecGroups));   // aux
   z.take<unsigned long long>((size_t)S * kTeamWords);
   Carver c(ws_get(h, bufid, z.off));
   FactorPlan fp;
@@ -207,7 +207,7 @@ FactorPlan build_factor(sislice_handle* h, int bufid, int n, const double* A, lo
   fp.d_state = c.take<FactorState>(S);
   fp.d_inertia = c.take<int64_t>(3 * (size_t)S);
   void** tab = c.take<void*>(10 * (size_t)S);
-  double* aux = c.take<double>((size_t)S * (3 * nb + nb * nb));
+  double* aux = c.take<double>((size_t)S * (nb + kSpecGroups));
   fp.d_team = c.take<unsigned long long>((size_t)S * kTeamWords);
   // host staging: sigmas then the pointer tables
   size_t hbytes = sizeof(double) * S + sizeof(void*) * 10 * S;
@@ -224,7 +224,7 @@ FactorPlan build_factor(sislice_handle* h, int bufid, int n, const double* A, lo
     ht[6 * S + s] = ps + (size_t)s * npmax;
     ht[7 * S + s] = snap + (size_t)s * npmax * n;
     ht[8 * S + s] = ipiv_host[s];
-    ht[9 * S + s] = aux + (size_t)s * (3 * nb + nb * nb);
+    ht[9 * S + s] = aux + (size_t)s * (nb + kSpecGroups);
   }
   SL_HIP(hipMemcpyAsync(d_sig, hs, sizeof(double) * S, hipMemcpyHostToDevice, h->stream));
   SL_HIP(hipMemcpyAsync(tab, ht, sizeof(void*) * 10 * S, hipMemcpyHostToDevice, h->stream));

@@ -7,6 +7,8 @@
 
 namespace sislice {
 
+constexpr int kSpecGroups = 256;  // workgroups of a shift's pivot-free panel, at most
+
 // Words of one shift's team area (k_bk_team): the roster, then the mailboxes.
 constexpr int kTeamMax = 32;  // workgroups in a team
 constexpr int kTeamRow = 136;  // words of one workgroup's row
@@ -37,7 +39,7 @@ struct FactorPlan {
   int npmax = 0;
   // pivot-free speculative panel path (per shift): staged L of the panel (n x nb),
   // D of the panel, inverse of the diagonal block (nb x nb), column maxima
-  double* const* d_aux = nullptr;  // [nb] D | [nb] max|w| in block | [nb] max|w| below (uint64 bits) | nb*nb Linv
+  double* const* d_aux = nullptr;  // [nb] D | [kSpecGroups] rejected columns (a uint64 a workgroup)
   unsigned long long* d_team = nullptr;  // device [nshift * kTeamWords]: mailboxes of the panel teams
   unsigned* wait_err = nullptr;    // raised when a team's wait exceeds wait_limit polls
   unsigned wait_limit = 0;
