@@ -178,7 +178,8 @@ template <int NB, bool PIVOT>
 __global__ __launch_bounds__(320) void k_fast_panel(int n, const double* const* LDs, long ldld,
                                                     double* const* Wps, long ldw,
                                                     double* const* auxs,
-                                                    const FactorState* states, int nb) {
+                                                    const FactorState* states,
+                                                    unsigned long long* teams, int nb) {
   constexpr int U = 8, G = NB / 16;
   // Column k of W and of L11 at [k * NB], for rows (of the block) past k.  What lies before,
   // and past the block, is read as well, into registers that hold no live column.
@@ -219,6 +220,10 @@ __global__ __launch_bounds__(320) void k_fast_panel(int n, const double* const* 
   if (tid == 0) {
     sBad = 0;
     sDone = 0;
+    if (blockIdx.x == 0) {  // the pivoting panel's workgroups gather anew
+      teams[(long)s * kTeamWords] = 0;
+      teams[(long)s * kTeamWords + 1] = 0;
+    }
   }
   __syncthreads();
   unsigned long long bad = 0;
@@ -323,55 +328,67 @@ __global__ __launch_bounds__(320) void k_fast_panel(int n, const double* const* 
   if (tid == 0) bad_of[blockIdx.x] = sBad;
 }
 
-// Accepts the longest prefix of columns that passed in every one of the `groups` workgroups of
-// k_fast_panel and writes their L = W D^{-1}.
+// The accepted columns: the longest prefix that passed in every one of the `groups` (<= the
+// workgroup's threads) workgroups of k_fast_panel.  sh: a word of LDS.
+__device__ __forceinline__ int accepted_columns(const double* Dv, int nb, int nbe, int groups, int* sh) {
+  const unsigned long long* bad_of = reinterpret_cast<const unsigned long long*>(Dv + nb);
+  if (threadIdx.x == 0) *sh = nbe;
+  __syncthreads();
+  if ((int)threadIdx.x < groups) {
+    const unsigned long long b = bad_of[threadIdx.x];
+    if (b) atomicMin(sh, __ffsll((long long)b) - 1);
+  }
+  __syncthreads();
+  return __builtin_amdgcn_readfirstlane(*sh);
+}
+
+// Column c of the accepted prefix: L = W D^{-1}, by the whole workgroup.
+__device__ __forceinline__ void accept_column(int n, double* LD, long ldld, const double* Wp, long ldw,
+                                              const double* Dv, int* blk, int* colpanel, int k0, int c,
+                                              int panel) {
+  const int col = k0 + c;
+  const double rd = 1.0 / Dv[c];  // the column's multipliers l = w (1 / d)
+  for (int i = col + 1 + threadIdx.x; i < n; i += blockDim.x)
+    LD[i + (long)col * ldld] = Wp[i + (long)c * ldw] * rd;
+  if (threadIdx.x == 0) {
+    LD[col + (long)col * ldld] = Dv[c];
+    blk[col] = 1;
+    colpanel[col] = panel;
+  }
+}
+
+// The panel state after js accepted columns, by the first wavefront.
+__device__ __forceinline__ void accept_state(FactorState* st, const double* Dv, int js) {
+  const int lane = threadIdx.x;
+  const bool acc = lane < js;
+  const bool negd = acc && Dv[lane] < 0.0;
+  const unsigned long long negm = __ballot(negd), posm = __ballot(acc && !negd);
+  if (lane == 0) {
+    st->jstart = js;
+    st->neg += __popcll(negm);
+    st->pos += __popcll(posm);
+  }
+}
+
+// Accepts the prefix, one workgroup a column, where no team follows (a team accepts for itself).
 __global__ __launch_bounds__(256) void k_fast_commit(int n, double* const* LDs, long ldld,
                                                      const double* const* Wps, long ldw,
                                                      const double* const* auxs, int* const* blks,
                                                      int* const* colpanels, FactorState* states,
-                                                     unsigned long long* teams, int nb, int groups) {
-  __shared__ unsigned long long bad;
-  const int s = blockIdx.y, c = blockIdx.x, tid = threadIdx.x;
+                                                     int nb, int groups) {
+  __shared__ int sh;
+  const int s = blockIdx.y, c = blockIdx.x;
   const FactorState st = states[s];
   const int k0 = st.k0 + st.kb;
   if (st.done || k0 >= n) return;
   const int nbe = min(nb, n - k0);
   if (c >= nbe) return;
   const double* Dv = global_ptr(auxs[s]);
-  const unsigned long long* bad_of = reinterpret_cast<const unsigned long long*>(Dv + nb);
-  if (tid == 0) bad = 0;
-  __syncthreads();
-  if (tid < groups) {
-    const unsigned long long b = bad_of[tid];
-    if (b) atomicOr(&bad, b);
-  }
-  __syncthreads();
-  const int js = bad ? min(__ffsll((long long)bad) - 1, nbe) : nbe;
-  const int jst = js;
-  if (c < jst) {
-    double* LD = global_ptr(LDs[s]);
-    const double* Wp = global_ptr(Wps[s]);
-    const int col = k0 + c;
-    const double rd = 1.0 / Dv[c];  // the column's multipliers l = w (1 / d)
-    for (int i = col + 1 + tid; i < n; i += 256) LD[i + (long)col * ldld] = Wp[i + (long)c * ldw] * rd;
-    if (tid == 0) {
-      LD[col + (long)col * ldld] = Dv[c];
-      blks[s][col] = 1;
-      colpanels[s][col] = st.npanel;
-    }
-  }
-  if (c == 0 && tid < 64) {
-    const bool acc = tid < jst;
-    const bool negd = acc && Dv[tid] < 0.0;
-    const unsigned long long negm = __ballot(negd), posm = __ballot(acc && !negd);
-    if (tid == 0) {
-      teams[(long)s * kTeamWords] = 0;  // the pivoting panel's workgroups gather anew
-      teams[(long)s * kTeamWords + 1] = 0;
-      states[s].jstart = jst;
-      states[s].neg += __popcll(negm);
-      states[s].pos += __popcll(posm);
-    }
-  }
+  const int js = accepted_columns(Dv, nb, nbe, groups, &sh);
+  if (c < js)
+    accept_column(n, global_ptr(LDs[s]), ldld, global_ptr(Wps[s]), ldw, Dv, global_ptr(blks[s]),
+                  global_ptr(colpanels[s]), k0, c, st.npanel);
+  if (c == 0 && threadIdx.x < 64) accept_state(states + s, Dv, js);
 }
 
 // The pivoting panel on one workgroup, for any number of rows.  Each column of S is
@@ -682,16 +699,18 @@ __global__ __launch_bounds__(1024) void k_bk_panel(int n, double* const* LDs, lo
 // pointers known to be global: each barrier would wait for it otherwise); then the team
 // agrees on the pivot.  A row interchange moves no data between threads: the two rows'
 // threads exchange labels (the row a thread stands for), and L is written once, at the
-// end, under the final labels.  A thread that becomes a pivot retires.  The W rows of the
+// end, under the final labels: the pivot-free columns' L as well, formed from their W when
+// the panel starts (a launch less, and L is written once).  A thread that becomes a pivot
+// retires.  The W rows of the
 // panel's own NB rows, which supply the multipliers of coming columns, are replicated in
 // every workgroup's LDS.
 //
 // The team's exchanges.  Per column each workgroup publishes its largest entry and its row,
 // the first one also the new W column of the panel's rows, and each one the W of its best
 // row; a column that fails the first test needs one more exchange, the candidate column's
-// maximum.  Words travel as relaxed agent-scope atomics, each with a tag in its upper half: a reader polls
-// the words it needs until their tags are right, so an exchange is one trip to the
-// coherence point and there is no flag, no fence and no reset (areas alternate by column;
+// maximum.  Words travel as relaxed agent-scope atomics, each with a tag in its upper half:
+// a reader polls the words it needs until their tags are right, so an exchange is one trip to
+// the coherence point and there is no flag, no fence and no reset (areas alternate by column;
 // a workgroup writes an area again only after every other one has answered the column in
 // between, and so has read it).  Data of S and W that another workgroup may read or write
 // later go through the same kind of access, and a workgroup that wrote some waits for its
@@ -721,10 +740,11 @@ struct TeamArgs {
   int* const* colpanels;
   int* const* pstarts;
   FactorState* states;
+  const double* const* auxs;
   unsigned long long* teams;
   unsigned* wait_err;
   unsigned wait_limit;
-  int nb, nbpiv;
+  int nb, nbpiv, groups;  // groups: workgroups of k_fast_panel
 };
 
 __device__ __forceinline__ double team_ld(const double* p) {
@@ -856,7 +876,7 @@ __global__ __launch_bounds__(NT) void k_bk_team(TeamArgs a) {
   __shared__ int redi[2][NW];
   __shared__ double redc[NW];
   __shared__ double sh_v[2], sh_arr;
-  __shared__ int sh_i, sh_own, sh_size, sh_rank;
+  __shared__ int sh_i, sh_own, sh_size, sh_rank, sh_js;
   const int s = blockIdx.y, tid = threadIdx.x;
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
   const int n = a.n, nb = a.nb;
@@ -865,7 +885,6 @@ __global__ __launch_bounds__(NT) void k_bk_team(TeamArgs a) {
   const int k0 = __builtin_amdgcn_readfirstlane(st->k0 + st->kb);
   const int done = __builtin_amdgcn_readfirstlane(st->done);
   const int P = __builtin_amdgcn_readfirstlane(st->npanel);
-  const int jstart = __builtin_amdgcn_readfirstlane(st->jstart);
   if (done || k0 >= n) return;  // (the state stays as the last panel left it)
   const int rem = n - k0;
   const int need = (rem + NT - 1) / NT;
@@ -905,6 +924,13 @@ __global__ __launch_bounds__(NT) void k_bk_team(TeamArgs a) {
     const int size = __builtin_amdgcn_readfirstlane(sh_size);
     if (rank < 0 || rank >= size) return;
     if (size < need) {
+      const double* Dv = global_ptr(a.auxs[s]);
+      const int js = accepted_columns(Dv, nb, min(nb, rem), a.groups, &sh_js);
+      for (int c = 0; c < js; ++c)
+        accept_column(n, global_ptr(a.LDs[s]), a.ldld, global_ptr(a.Wps[s]), a.ldw, Dv,
+                      global_ptr(a.blks[s]), global_ptr(a.colpanels[s]), k0, c, P);
+      if (tid < 64) accept_state(st, Dv, js);
+      __syncthreads();
       bk_panel_rows<true, NT>(n, a.LDs, a.ldld, a.Wps, a.ldw, a.perms, a.swps, a.blks, a.colpanels,
                               a.pstarts, a.states, nb, a.nbpiv, s);
       return;
@@ -934,6 +960,10 @@ __global__ __launch_bounds__(NT) void k_bk_team(TeamArgs a) {
   int* sw = global_ptr(a.swps[s]);
   int* blk = global_ptr(a.blks[s]);
   int* colpanel = global_ptr(a.colpanels[s]);
+  const double* Dv = global_ptr(a.auxs[s]);
+  const int jstart = accepted_columns(Dv, nb, min(nb, rem), a.groups, &sh_js);
+  if (tid < NB) wim[tid] = tid < jstart ? 1.0 / Dv[tid] : 0.0;
+  __syncthreads();
 
   // this thread's row: the row it stands for, the row it began as, its original row (which
   // travels with the label) and the columns of L to write, set when it becomes a pivot.
@@ -946,7 +976,7 @@ __global__ __launch_bounds__(NT) void k_bk_team(TeamArgs a) {
   int wlim = -1;
   double L[NB];  // -L (-0 where there is none: adding the product changes nothing)
 #pragma unroll
-  for (int p = 0; p < NB; ++p) L[p] = p < jstart ? -LD[lc + (long)(k0 + p) * ld] : -0.0;
+  for (int p = 0; p < NB; ++p) L[p] = p < jstart ? -(Wp[lc + (long)p * ldw] * wim[p]) : -0.0;
   for (int e = tid; e < NB * LW; e += NT) {
     const int r = e / LW, p = e % LW;
     Wt[e] = (p < jstart && r >= jstart && k0 + r < n) ? Wp[(k0 + r) + (long)p * ldw] : 0.0;
@@ -964,6 +994,12 @@ __global__ __launch_bounds__(NT) void k_bk_team(TeamArgs a) {
   const int jmax0 = rem <= nb ? rem : nb - 1;
   const int jmax = min(jmax0, jstart + a.nbpiv);
   long neg = 0, zer = 0, pos = 0;
+  if (w == NW - 1) {  // the accepted columns' pivots (none is zero)
+    const bool acc = lane < jstart;
+    const bool negd = acc && Dv[min(lane, nb - 1)] < 0.0;
+    neg = __popcll(__ballot(negd));
+    pos = __popcll(__ballot(acc && !negd));
+  }
   unsigned polls = 0;  // wavefront 0's unsuccessful polls in all; past the limit it goes on as it is
   auto expired = [&]() {
     if (polls++ < a.wait_limit) return false;
@@ -1294,12 +1330,17 @@ __global__ __launch_bounds__(NT) void k_bk_team(TeamArgs a) {
     j += kstep;
   }
   // ---- L and the permutation under the final labels
-  if (lab < n && lab >= k0 + jstart) {
-    const int lim = wlim >= 0 ? wlim : j;
-      const int from = lab == first ? jstart : 0;
+  if (lab < n) {
+    const bool accepted = lab < k0 + jstart;  // a pivot of the accepted columns
+    const int lim = accepted ? lab - k0 : (wlim >= 0 ? wlim : j);
 #pragma unroll
     for (int p = 0; p < NB; ++p)
-      if (p >= from && p < lim) LD[lab + (long)(k0 + p) * ld] = -L[p];
+      if (p < lim) LD[lab + (long)(k0 + p) * ld] = -L[p];
+    if (accepted) {
+      LD[lab + (long)lab * ld] = Dv[lim];
+      blk[lab] = 1;
+      colpanel[lab] = P;
+    }
     if (lab != first) perm[lab] = pv;
   }
   if (rank == 0 && tid == NT - 1) {
@@ -1938,7 +1979,13 @@ static FactorPlan factor_subplan(const FactorPlan& fp, int s0, int cnt) {
 // The pivoting panel of every shift.  rem_max bounds the rows of the least advanced shift;
 // a team per shift must fit the device at once (seven eighths of it, shared by the shift
 // groups), otherwise one workgroup a shift runs the panel from memory.
-static void panel_launch(const FactorPlan& fp, hipStream_t st, long rem_max, int nbpiv) {
+static bool panel_team(const FactorPlan& fp, long rem_max, long& need) {
+  need = rem_max <= (fp.nb > 32 ? 512 : 1024) ? 1 : ceil_div(rem_max, 512);
+  return fp.pivot && fp.team && fp.fast &&
+         (need <= 1 || (need <= kTeamMax && need * fp.nshift <= (long)fp.cus * 7 / 8 / fp.groups));
+}
+
+static void panel_launch(const FactorPlan& fp, hipStream_t st, long rem_max, int nbpiv, int groups) {
   const int n = fp.n, S = fp.nshift, nb = fp.nb;
   if (!fp.pivot) {
     SL_LAUNCH(k_bk_panel<false>, dim3(S), dim3(1024), 0, st, n, fp.d_LD, fp.ldld, fp.d_W, fp.ldw,
@@ -1946,10 +1993,10 @@ static void panel_launch(const FactorPlan& fp, hipStream_t st, long rem_max, int
     SL_LAUNCH_CHECK();
     return;
   }
-  const long need = rem_max <= (nb > 32 ? 512 : 1024) ? 1 : ceil_div(rem_max, 512);
-  if (fp.team && fp.fast && (need <= 1 || (need <= kTeamMax && need * S <= (long)fp.cus * 7 / 8 / fp.groups))) {
+  long need;
+  if (panel_team(fp, rem_max, need)) {
     TeamArgs a{n, fp.d_LD, fp.ldld, fp.d_W, fp.ldw, fp.d_perm, fp.d_sw, fp.d_blk, fp.d_colpanel,
-               fp.d_pstart, fp.d_state, fp.d_team, fp.wait_err, fp.wait_limit, nb, nbpiv};
+               fp.d_pstart, fp.d_state, fp.d_aux, fp.d_team, fp.wait_err, fp.wait_limit, nb, nbpiv, groups};
     // As few threads as hold the rows: a column's reductions, tests and barriers cost every
     // wavefront the same instructions, so a SIMD's wavefronts take turns at them.  Five
     // shifts at order 1001, all panels: 1.52 ms with 1024 threads to the end, 1.04 so.
@@ -1989,25 +2036,29 @@ static void factor_step(const FactorPlan& fp, hipStream_t st, long k0_lb, sislic
   const int nbpiv = fp.fast ? fp.nbpiv : nb;
   const int min_kb = factor_min_panel(nb, fp.nbpiv, fp.fast != 0);
   int tpan = -1;
+  int groups = 0;
   if (fp.fast) {
     // one timed ticket per panel step: the speculative group and the pivoting
     // panel are consecutive launches of the panel class
     tpan = prof_begin(ph, kProfPanel, st);
     // a workgroup per 256 rows below the block, as many as run side by side (two a CU)
-    const int groups = (int)std::max<long>(
+    groups = (int)std::max<long>(
         1, std::min<long>({ceil_div(n - k0_lb - 1, 256), (long)kSpecGroups, 2l * fp.cus / S}));
     const auto panel = nb > 32 ? (fp.pivot ? k_fast_panel<64, true> : k_fast_panel<64, false>)
                                : (fp.pivot ? k_fast_panel<32, true> : k_fast_panel<32, false>);
     SL_LAUNCH(panel, dim3((unsigned)groups, S), dim3(320), 0, st, n, (const double* const*)fp.d_LD,
-              fp.ldld, fp.d_W, fp.ldw, fp.d_aux, fp.d_state, nb);
+              fp.ldld, fp.d_W, fp.ldw, fp.d_aux, fp.d_state, fp.d_team, nb);
     SL_LAUNCH_CHECK();
-    SL_LAUNCH(k_fast_commit, dim3(nb, S), dim3(256), 0, st, n, fp.d_LD, fp.ldld,
-              (const double* const*)fp.d_W, fp.ldw, (const double* const*)fp.d_aux, fp.d_blk,
-              fp.d_colpanel, fp.d_state, fp.d_team, nb, groups);
-    SL_LAUNCH_CHECK();
+    long need;
+    if (!panel_team(fp, n - k0_lb, need)) {
+      SL_LAUNCH(k_fast_commit, dim3(nb, S), dim3(256), 0, st, n, fp.d_LD, fp.ldld,
+                (const double* const*)fp.d_W, fp.ldw, (const double* const*)fp.d_aux, fp.d_blk,
+                fp.d_colpanel, fp.d_state, nb, groups);
+      SL_LAUNCH_CHECK();
+    }
   }
   if (tpan < 0) tpan = prof_begin(ph, kProfPanel, st);
-  panel_launch(fp, st, n - k0_lb, nbpiv);
+  panel_launch(fp, st, n - k0_lb, nbpiv, groups);
   SL_LAUNCH_CHECK();
   prof_end(ph, tpan, st);
   if (after_panel) SL_HIP(hipEventRecord(after_panel, st));
