@@ -1838,33 +1838,53 @@ __global__ __launch_bounds__(1024) void k_trailing_update_pipe(int n, double* co
 
 // Suffix compositions of the interchanges: for the panel ending at e, Q_e[v] is
 // the final row of the entry found at row v (v >= e) when that panel finished.
-__global__ __launch_bounds__(256) void k_perm_suffix(int n, const int* const* swps,
-                                                     const int* const* pstarts,
-                                                     const FactorState* states, int* const* snaps) {
+//
+// What bounds it: the interchanges are a chain, from the last column back.  One wavefront
+// takes a panel's (at most 64) at once, lane l that of column t = hi - l with row p: in order
+// each does q[t] = q[p], q[p] = t (q[t] is t until then).  A lane reads q[p] as it was before
+// the panel unless an earlier one of its panel wrote that entry, and those are played
+// through in registers, columns without interchange left out.  Order 4096, 17 shifts:
+// 412 us by one thread, 79 so; order 1001: 100 and 27; order 200: 18 and 5.
+__global__ __launch_bounds__(1024) void k_perm_suffix(int n, const int* const* swps,
+                                                      const int* const* pstarts,
+                                                      const FactorState* states, int* const* snaps) {
   extern __shared__ int q[];
-  const int s = blockIdx.x;
+  const int s = blockIdx.x, lane = threadIdx.x & 63;
+  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int* sw = global_ptr(swps[s]);
   const int* pstart = global_ptr(pstarts[s]);
   int* snap = global_ptr(snaps[s]);
-  const int np = states[s].npanel;
+  const int np = __builtin_amdgcn_readfirstlane(states[s].npanel);
   for (int v = threadIdx.x; v < n; v += blockDim.x) q[v] = v;
+  int hi = n - 1;  // the panel's last column
+  int e = np > 1 ? __builtin_amdgcn_readfirstlane(pstart[np - 1]) : 0;
+  int p = sw[max(hi - lane, 0)];
   __syncthreads();
-  int cur = n - 1;
   for (int P = np - 1; P >= 1; --P) {
-    const int e = pstart[P];
-    if (threadIdx.x == 0) {
-      for (int t = cur; t >= e; --t) {
-        const int p = sw[t];
-        if (p != t) {
-          const int x = q[t];
-          q[t] = q[p];
-          q[p] = x;
-        }
+    const int e1 = P > 1 ? __builtin_amdgcn_readfirstlane(pstart[P - 1]) : 0;  // the panel before
+    const int p1 = sw[max(e - 1 - lane, 0)];
+    if (w == 0) {
+      const int t = hi - lane;
+      const bool moves = t >= e && p != t;
+      int val = moves ? q[p] : t;
+      bool last = moves;  // no later column of the panel has the same row
+      for (unsigned long long m = __ballot(moves); m; m &= m - 1) {
+        const int l = __ffsll((long long)m) - 1;
+        const int tl = hi - l, pl = __builtin_amdgcn_readlane(p, l), vl = __builtin_amdgcn_readlane(val, l);
+        const bool later = moves && lane > l;
+        if (__ballot(later && p == pl) && lane == l) last = false;
+        if (later && p == pl) val = tl;
+        if (later && p == tl) val = vl;
       }
+      if (moves) q[t] = val;
+      __builtin_amdgcn_wave_barrier();
+      if (last) q[p] = t;
     }
-    cur = e - 1;
     __syncthreads();
     for (int v = e + threadIdx.x; v < n; v += blockDim.x) snap[(long)(P - 1) * n + v] = q[v];
+    hi = e - 1;
+    e = e1;
+    p = p1;
     __syncthreads();
   }
 }
@@ -2094,7 +2114,7 @@ static void factor_step(const FactorPlan& fp, hipStream_t st, long k0_lb, sislic
 static void factor_tail(const FactorPlan& fp, hipStream_t st) {
   const int n = fp.n, S = fp.nshift;
   if (fp.pivot) {
-    SL_LAUNCH(k_perm_suffix, dim3(S), dim3(256), (size_t)n * sizeof(int), st, n, fp.d_sw,
+    SL_LAUNCH(k_perm_suffix, dim3(S), dim3(1024), (size_t)n * sizeof(int), st, n, fp.d_sw,
               fp.d_pstart, fp.d_state, fp.d_snap);
     SL_LAUNCH_CHECK();
     SL_LAUNCH(k_left_gather, dim3(n, S), dim3(1024), (size_t)n * sizeof(double), st, n, fp.d_LD,
