@@ -12,9 +12,12 @@
 //     a GEMV against the panel so far, pivots are chosen by block-wide argmax
 //     reductions, symmetric interchanges are applied to the not-yet-updated
 //     trailing matrix (lower storage) and to the panel rows.
-//   * k_trailing_update: the lower triangle of the trailing matrix is updated
-//     with C22 -= L21 W21^T on FP64 MFMA (v_mfma_f64_16x16x4), 64x64 tiles, all
-//     shifts in one launch.
+//   * k_bk_team: the same panel by a team of workgroups with L in registers, where
+//     the teams of all shifts fit the device; k_fast_panel before it takes the
+//     columns that need no pivoting.
+//   * k_trailing_update, k_trailing_update_lds: the lower triangle of the trailing
+//     matrix is updated with C22 -= L21 W21^T on FP64 MFMA (v_mfma_f64_16x16x4),
+//     64x64 and 128x128 tiles, all shifts in one launch; large ones two panels at once.
 //   * Interchanges found in later panels are applied to earlier L columns once at
 //     the end (k_perm_suffix builds the suffix permutations, k_left_gather moves
 //     the rows), so that P C P^T = L D L^T with a single permutation P.
@@ -104,7 +107,9 @@ __global__ __launch_bounds__(256) void k_factor_init(int n, FactorState* states,
     z.npanel = 0;
     z.neg = z.zero = z.pos = 0;
     z.jstart = 0;
-    z.pad = 0;
+    z.whole = z.pend = 0;
+    z.u_k0 = z.u_kb = z.u_w0 = 0;
+    z.u_c0 = z.u_c1 = n;
     states[s] = z;
   }
 }
@@ -194,7 +199,7 @@ __global__ __launch_bounds__(320) void k_fast_panel(int n, const double* const* 
   if (st.done || k0 >= n) return;
   const int nbe = __builtin_amdgcn_readfirstlane(min(nb, n - k0));
   const double* LD = global_ptr(LDs[s]);
-  double* Wp = global_ptr(Wps[s]);
+  double* Wp = global_ptr(Wps[s]) + st.pend * ldw;
   double* Dv = global_ptr(auxs[s]);
   unsigned long long* bad_of = reinterpret_cast<unsigned long long*>(Dv + nb);
   double x[NB];
@@ -370,6 +375,31 @@ __device__ __forceinline__ void accept_state(FactorState* st, const double* Dv, 
   }
 }
 
+// The state after a panel of j columns from k0, js of them accepted by the pivot-free path
+// (nbe: the columns that path took on), and the update that follows; one thread.
+__device__ __forceinline__ void panel_done(FactorState* st, int n, int nb, int nbe, int k0, int j, int js,
+                                           int panel, bool defer) {
+  const int pend = st->pend, k1 = k0 + j;
+  const bool pair = pend > 0 && js == nbe;  // (otherwise the panel before has been caught up)
+  const bool whole = js == nb;
+  st->k0 = k0;
+  st->kb = j;
+  st->npanel = panel + 1;
+  st->done = k1 >= n;
+  st->jstart = 0;
+  st->whole += whole;
+  st->u_k0 = pair ? k0 - pend : k0;
+  st->u_kb = pair ? pend + j : j;
+  st->u_w0 = pair ? 0 : pend;
+  st->u_c0 = k1;
+  st->u_c1 = n;
+  st->pend = 0;
+  if (defer && whole && !pend && k1 < n) {
+    st->u_c1 = min(n, k1 + nb);
+    st->pend = j;
+  }
+}
+
 // Accepts the prefix, one workgroup a column, where no team follows (a team accepts for itself).
 __global__ __launch_bounds__(256) void k_fast_commit(int n, double* const* LDs, long ldld,
                                                      const double* const* Wps, long ldw,
@@ -386,7 +416,7 @@ __global__ __launch_bounds__(256) void k_fast_commit(int n, double* const* LDs, 
   const double* Dv = global_ptr(auxs[s]);
   const int js = accepted_columns(Dv, nb, nbe, groups, &sh);
   if (c < js)
-    accept_column(n, global_ptr(LDs[s]), ldld, global_ptr(Wps[s]), ldw, Dv, global_ptr(blks[s]),
+    accept_column(n, global_ptr(LDs[s]), ldld, global_ptr(Wps[s]) + st.pend * ldw, ldw, Dv, global_ptr(blks[s]),
                   global_ptr(colpanels[s]), k0, c, st.npanel);
   if (c == 0 && threadIdx.x < 64) accept_state(states + s, Dv, js);
 }
@@ -399,12 +429,13 @@ __device__ __forceinline__ void bk_panel_rows(int n, double* const* LDs, long ld
                                               double* const* Wps, long ldw, int* const* perms,
                                               int* const* swps, int* const* blks,
                                               int* const* colpanels, int* const* pstarts,
-                                              FactorState* states, int nb, int nbpiv, int s) {
+                                              FactorState* states, int nb, int nbpiv, int s,
+                                              bool defer) {
   constexpr int NW = NT / 64;
   const int tid = threadIdx.x;
   FactorState* st = states + s;
   double* __restrict__ LD = global_ptr(LDs[s]);
-  double* __restrict__ Wp = global_ptr(Wps[s]);
+  double* __restrict__ Wp = global_ptr(Wps[s]) + st->pend * ldw;
   int* perm = global_ptr(perms[s]);
   int* sw = global_ptr(swps[s]);
   int* blk = global_ptr(blks[s]);
@@ -430,6 +461,7 @@ __device__ __forceinline__ void bk_panel_rows(int n, double* const* LDs, long ld
       st->k0 = sh_k0 < n ? sh_k0 : n;
       st->kb = 0;
       st->done = 1;
+      st->u_c0 = n;
     }
     return;
   }
@@ -669,14 +701,10 @@ __device__ __forceinline__ void bk_panel_rows(int n, double* const* LDs, long ld
     j += kstep;
   }
   if (tid == 0) {
-    st->k0 = k0;
-    st->kb = j;
-    st->npanel = P + 1;
-    st->done = (k0 + j >= n);
+    panel_done(st, n, nb, min(nb, rem), k0, j, jstart, P, defer);
     st->neg += neg;
     st->zero += zer;
     st->pos += pos;
-    st->jstart = 0;
     pstart[P] = k0;
   }
 }
@@ -686,9 +714,9 @@ __global__ __launch_bounds__(1024) void k_bk_panel(int n, double* const* LDs, lo
                                                    double* const* Wps, long ldw, int* const* perms,
                                                    int* const* swps, int* const* blks,
                                                    int* const* colpanels, int* const* pstarts,
-                                                   FactorState* states, int nb, int nbpiv) {
+                                                   FactorState* states, int nb, int nbpiv, bool defer) {
   bk_panel_rows<PIVOT, 1024>(n, LDs, ldld, Wps, ldw, perms, swps, blks, colpanels, pstarts, states,
-                             nb, nbpiv, blockIdx.x);
+                             nb, nbpiv, blockIdx.x, defer);
 }
 
 // The pivoting panel with the panel's L in registers: every thread holds one row, a
@@ -745,6 +773,7 @@ struct TeamArgs {
   unsigned* wait_err;
   unsigned wait_limit;
   int nb, nbpiv, groups;  // groups: workgroups of k_fast_panel
+  bool defer;             // a whole panel's update may wait for the next one's
 };
 
 __device__ __forceinline__ double team_ld(const double* p) {
@@ -876,26 +905,30 @@ __global__ __launch_bounds__(NT) void k_bk_team(TeamArgs a) {
   __shared__ int redi[2][NW];
   __shared__ double redc[NW];
   __shared__ double sh_v[2], sh_arr;
-  __shared__ int sh_i, sh_own, sh_size, sh_rank, sh_js;
+  __shared__ int sh_i, sh_own, sh_size, sh_rank, sh_js, sh_k0, sh_panel, sh_pend;
   const int s = blockIdx.y, tid = threadIdx.x;
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
   const int n = a.n, nb = a.nb;
   FactorState* st = a.states + s;
   unsigned long long* team = a.teams + (long)s * kTeamWords;
-  const int k0 = __builtin_amdgcn_readfirstlane(st->k0 + st->kb);
-  const int done = __builtin_amdgcn_readfirstlane(st->done);
-  const int P = __builtin_amdgcn_readfirstlane(st->npanel);
-  if (done || k0 >= n) return;  // (the state stays as the last panel left it)
-  const int rem = n - k0;
-  const int need = (rem + NT - 1) / NT;
-  int rank = 0;
-  if (TEAM) {
-    if (tid == 0) {
+  // One thread reads the state and signs in, in this order: once the team is complete, the
+  // first workgroup may finish the panel and write the state at any time.
+  if (tid == 0) {
+    const int k = st->k0 + st->kb, panel = st->npanel, pend = st->pend;
+    const bool over = st->done || k >= n;  // (the state stays as the last panel left it)
+    asm volatile("" ::"v"(k), "v"(panel), "v"(pend) : "memory");
+    sh_k0 = k;
+    sh_panel = panel;
+    sh_pend = pend;
+    int r = over ? -1 : 0, sz = 1;
+    if (TEAM && !over) {
+      const int need = (n - k + NT - 1) / NT;
       const unsigned closed = 0x80000000u;
       unsigned* roster = reinterpret_cast<unsigned*>(team);
       unsigned* size = reinterpret_cast<unsigned*>(team + 1);
       const unsigned old = __hip_atomic_fetch_add(roster, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      int r = (int)(old & 0xffffu), sz = 0;
+      r = (int)(old & 0xffffu);
+      sz = 0;
       if ((old & closed) || r >= need) {
         r = -1;
       } else if (r == need - 1) {
@@ -916,23 +949,31 @@ __global__ __launch_bounds__(NT) void k_bk_team(TeamArgs a) {
           __builtin_amdgcn_s_sleep(8);
         }
       }
-      sh_rank = r;
-      sh_size = sz;
     }
-    __syncthreads();
-    rank = __builtin_amdgcn_readfirstlane(sh_rank);
+    sh_rank = r;
+    sh_size = sz;
+  }
+  __syncthreads();
+  const int rank = __builtin_amdgcn_readfirstlane(sh_rank);
+  const int k0 = __builtin_amdgcn_readfirstlane(sh_k0);
+  const int P = __builtin_amdgcn_readfirstlane(sh_panel);
+  const int pend = __builtin_amdgcn_readfirstlane(sh_pend);
+  if (rank < 0) return;
+  const int rem = n - k0;
+  const int need = (rem + NT - 1) / NT;
+  if (TEAM) {
     const int size = __builtin_amdgcn_readfirstlane(sh_size);
-    if (rank < 0 || rank >= size) return;
+    if (rank >= size) return;
     if (size < need) {
       const double* Dv = global_ptr(a.auxs[s]);
       const int js = accepted_columns(Dv, nb, min(nb, rem), a.groups, &sh_js);
       for (int c = 0; c < js; ++c)
-        accept_column(n, global_ptr(a.LDs[s]), a.ldld, global_ptr(a.Wps[s]), a.ldw, Dv,
+        accept_column(n, global_ptr(a.LDs[s]), a.ldld, global_ptr(a.Wps[s]) + pend * a.ldw, a.ldw, Dv,
                       global_ptr(a.blks[s]), global_ptr(a.colpanels[s]), k0, c, P);
       if (tid < 64) accept_state(st, Dv, js);
       __syncthreads();
       bk_panel_rows<true, NT>(n, a.LDs, a.ldld, a.Wps, a.ldw, a.perms, a.swps, a.blks, a.colpanels,
-                              a.pstarts, a.states, nb, a.nbpiv, s);
+                              a.pstarts, a.states, nb, a.nbpiv, s, a.defer);
       return;
     }
   }
@@ -947,7 +988,7 @@ __global__ __launch_bounds__(NT) void k_bk_team(TeamArgs a) {
   auto areaC = [&](int t) { return mail + (2 + (t & 1)) * kArea; };
   auto areaR = [&](int t, int r) { return mail + 4 * kArea + ((t & 1) * kTeamMax + r) * kTeamRow; };
   double* LD = global_ptr(a.LDs[s]);
-  double* Wp = global_ptr(a.Wps[s]);
+  double* Wp = global_ptr(a.Wps[s]) + pend * a.ldw;
   const long ld = a.ldld, ldw = a.ldw;
   auto ld_s = [&](const double* p) { return multi ? team_ld(p) : *p; };
   auto st_s = [&](double* p, double v) {
@@ -1344,14 +1385,10 @@ __global__ __launch_bounds__(NT) void k_bk_team(TeamArgs a) {
     if (lab != first) perm[lab] = pv;
   }
   if (rank == 0 && tid == NT - 1) {
-    st->k0 = k0;
-    st->kb = j;
-    st->npanel = P + 1;
-    st->done = (k0 + j >= n);
+    panel_done(st, n, nb, min(nb, rem), k0, j, jstart, P, a.defer);
     st->neg += neg;
     st->zero += zer;
     st->pos += pos;
-    st->jstart = 0;
     global_ptr(a.pstarts[s])[P] = k0;
   }
 }
@@ -1464,72 +1501,98 @@ __global__ __launch_bounds__(256) void k_trailing_update(int n, double* const* L
 
 // The same update on 128x128 tiles for large trailing matrices, one 1024-thread
 // workgroup per tile.  Each of the 16 wavefronts owns a 32x32 block of the tile as
-// 2x2 v_mfma_f64_16x16x4 blocks, so a wavefront needs 62 registers and a CU keeps
-// two workgroups (eight wavefronts per SIMD) in flight; the C tile is read and
+// 2x2 v_mfma_f64_16x16x4 blocks, so a wavefront needs at most 64 registers (asked for) and
+// a CU keeps two workgroups (eight wavefronts per SIMD) in flight; the C tile is read and
 // written once per 128x128.  The operand panels of the tile (128 rows of L and 128
 // rows of W, 16 k-columns per chunk) are fetched once per workgroup with coalesced
-// 1 KB column runs into double-buffered LDS (66 KB), and the next chunk is in
-// flight while the wavefronts run the current one's MFMAs.
-// Layout per chunk and operand: [k][row], rows padded to 132 doubles so that the
-// four k-groups a wavefront reads at once fall on different banks.
+// 1 KB column runs into double-buffered LDS (74 KB), and the next chunk is in
+// flight while the wavefronts run the current one's MFMAs: nothing touches the fetched
+// values before they go to LDS (a sign or a select there waits for them, 30 TF/s).
+// Layout per chunk and operand: [k][row], rows padded to 144 doubles so that two
+// k-groups of a wavefront's reads cover the 64 banks once (132: 1% more per factorization).
+//
+// What bounds it: at 64 columns the C stream, 2 x 8 bytes per 128 flops (4.0 TB/s of the
+// 4.6 a copy reaches); so a panel that the pivot-free path accepted whole updates the next
+// panel's columns only, one column of tiles, and if the next one is whole too both go into
+// C together, 128 columns (45 TF/s: 17 shifts of order 4096 788 us, two updates of 64
+// 1080).  Otherwise the panel before is caught up first (`auxs` given: the panel's masks
+// decide), since pivoting may look at any column.  The order of the sums is the same either
+// way, so the factors are the same bits.
 // With STREAM the C tile is read and written non-temporally: when the shifts run in
 // two groups on two streams (large orders), C has no reuse in the caches before the
 // next update, and streaming it keeps the other group's panel data resident (at
 // order 12288, 49 shifts: 2975 -> 2718 us per update launch, about 2% per
 // factorization).
 constexpr int kUpdK = 16;           // k-columns per staged chunk
-constexpr int kUpdLd = 128 + 4;     // padded row count per k-column
+constexpr int kUpdLd = 128 + 16;    // padded row count per k-column
 template <bool STREAM>
-__global__ __launch_bounds__(1024) void k_trailing_update_lds(int n, double* const* LDs, long ldld,
-                                                             double* const* Wps, long ldw,
-                                                             const FactorState* states) {
+__global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(8))) void k_trailing_update_lds(
+    int n, double* const* LDs, long ldld, double* const* Wps, long ldw, const FactorState* states,
+    const double* const* auxs, int nb, int groups) {
   constexpr int TB = 128;
   __shared__ double sL[2][kUpdK * kUpdLd];
   __shared__ double sW[2][kUpdK * kUpdLd];
+  __shared__ int sh;
   const int s = blockIdx.y;
-  const int k0 = states[s].k0, kb = states[s].kb;
-  const int k1 = k0 + kb;
+  const FactorState st = states[s];
+  int k0 = st.u_k0, kb = st.u_kb, w0 = st.u_w0, k1 = st.u_c0, c1 = st.u_c1;
+  int nbe = 0;
+  if (auxs) {  // the panel before, for the columns past the present one's
+    k1 = st.k0 + st.kb;
+    if (st.done || st.pend == 0 || k1 >= n) return;
+    nbe = min(nb, n - k1);
+    k0 = k1 - st.pend;
+    kb = st.pend;
+    w0 = 0;
+    k1 += nbe;
+    c1 = n;
+  }
   if (kb <= 0 || k1 >= n) return;
   const int T = (n - k1 + TB - 1) / TB;
   const int lin = blockIdx.x;
-  if (lin >= T * (T + 1) / 2) return;
+  const bool strip = c1 - k1 <= TB;  // one column of tiles
+  if (lin >= (strip ? T : T * (T + 1) / 2)) return;
+  if (auxs && accepted_columns(global_ptr(auxs[s]), nb, nbe, groups, &sh) == nbe) return;
   int ti = (int)((sqrt(8.0 * lin + 1.0) - 1.0) * 0.5);
   while (ti * (ti + 1) / 2 > lin) --ti;
   while ((ti + 1) * (ti + 2) / 2 <= lin) ++ti;
-  const int tj = lin - ti * (ti + 1) / 2;
+  int tj = lin - ti * (ti + 1) / 2;
+  if (strip) {
+    ti = lin;
+    tj = 0;
+  }
   const int tid = threadIdx.x;
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6), l = tid & 63;
   const int wi = (w & 3) * 32, wj = (w >> 2) * 32;
   // on a diagonal tile the blocks above the diagonal store nothing, but their
   // wavefronts still help stage the operands
-  const bool active = !(ti == tj && wi + 31 < wj);
   const int row0 = k1 + ti * TB, col0 = k1 + tj * TB;
+  const bool active = !(ti == tj && wi + 31 < wj) && col0 + wj < c1;
   double* LD = global_ptr(LDs[s]);
-  const double* Wp = global_ptr(Wps[s]);
+  const double* Wp = global_ptr(Wps[s]) + w0 * ldw;
   const int lr = l & 15, lk = l >> 4;
   const int nks = (kb + 3) >> 2;             // k-steps of 4
   const int nch = (kb + kUpdK - 1) / kUpdK;  // staged chunks
   // staging: thread t fetches row (t % 128) of columns (t / 128) + 8j, j < 2
-  const int sr = tid & 127, sc = tid >> 7;
-  const int lrow = min(row0 + sr, n - 1), wrow = min(col0 + sr, n - 1);
+  const int sr = tid & 127, sc = w >> 1;
+  const unsigned lrow = min(row0 + sr, n - 1), wrow = min(col0 + sr, n - 1);
   double stL[kUpdK / 8], stW[kUpdK / 8];
+  // (a column past kb is the last one again, and zero when it goes to LDS: the loads are not
+  // touched before the MFMAs of the chunk at hand)
   auto fetch = [&](int ch) {
 #pragma unroll
     for (int j = 0; j < kUpdK / 8; ++j) {
-      const int k = ch * kUpdK + sc + 8 * j;
-      const bool kv = k < kb;
-      const int kc = kv ? k : 0;
-      const double a = LD[lrow + (long)(k0 + kc) * ldld];
-      const double b = Wp[wrow + (long)kc * ldw];
-      stL[j] = kv ? a : 0.0;
-      stW[j] = kv ? -b : 0.0;
+      const int k = min(ch * kUpdK + sc + 8 * j, kb - 1);
+      stL[j] = (LD + (long)(k0 + k) * ldld)[lrow];
+      stW[j] = (Wp + (long)k * ldw)[wrow];
     }
   };
-  auto stage = [&](int buf) {
+  auto stage = [&](int buf, int ch) {
 #pragma unroll
     for (int j = 0; j < kUpdK / 8; ++j) {
-      sL[buf][(sc + 8 * j) * kUpdLd + sr] = stL[j];
-      sW[buf][(sc + 8 * j) * kUpdLd + sr] = stW[j];
+      const bool kv = ch * kUpdK + sc + 8 * j < kb;
+      sL[buf][(sc + 8 * j) * kUpdLd + sr] = kv ? stL[j] : 0.0;
+      sW[buf][(sc + 8 * j) * kUpdLd + sr] = kv ? -stW[j] : 0.0;
     }
   };
   fetch(0);
@@ -1548,7 +1611,7 @@ __global__ __launch_bounds__(1024) void k_trailing_update_lds(int n, double* con
         }
     }
   }
-  stage(0);
+  stage(0, 0);
   __syncthreads();
   for (int ch = 0; ch < nch; ++ch) {
     const int buf = ch & 1;
@@ -1556,8 +1619,9 @@ __global__ __launch_bounds__(1024) void k_trailing_update_lds(int n, double* con
     if (active) {
       const double* L0 = sL[buf] + wi + lr;
       const double* W0 = sW[buf] + wj + lr;
-      const int ksteps = min(kUpdK / 4, nks - ch * (kUpdK / 4));
-      for (int u = 0; u < ksteps; ++u) {
+      // (k-steps past kb meet zeros)
+#pragma unroll
+      for (int u = 0; u < kUpdK / 4; ++u) {
         const int kk = (4 * u + lk) * kUpdLd;
         double lo[2], wo[2];
 #pragma unroll
@@ -1571,7 +1635,7 @@ __global__ __launch_bounds__(1024) void k_trailing_update_lds(int n, double* con
       }
     }
     if (ch + 1 < nch) {
-      stage(buf ^ 1);
+      stage(buf ^ 1, ch + 1);
       __syncthreads();
     }
   }
@@ -1584,7 +1648,7 @@ __global__ __launch_bounds__(1024) void k_trailing_update_lds(int n, double* con
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
         const int jc = col0 + wj + 16 * y + lk + 4 * r;
-        if (i < n && jc < n && i >= jc) {
+        if (i < n && jc < c1 && i >= jc) {
           if (STREAM)
             __builtin_nontemporal_store(acc[x][y][r], LD + i + (long)jc * ldld);
           else
@@ -1592,247 +1656,6 @@ __global__ __launch_bounds__(1024) void k_trailing_update_lds(int n, double* con
         }
       }
     }
-  }
-}
-
-// Persistent form of the 128x128-tile update for large trailing matrices.  A
-// launch has one 1024-thread workgroup per CU.  The (shift, tile) items of every
-// shift are numbered shift by shift, tile rows in order, and each workgroup takes
-// one contiguous run of them (the runs of the workgroups of one XCD adjacent), so
-// consecutive items of a workgroup mostly lie in one tile row and share its L
-// rows.  The rank-kb (<= 64) operand panels of a tile sit in LDS whole (L and -W,
-// [k][row] with rows padded to 132 doubles: 135 KB), so a tile needs no barrier
-// between its MFMAs; the L panel is reloaded only when the tile row changes.  The
-// work is software-pipelined across a workgroup's items: while the MFMAs of item t
-// run, the C tile and the W panel of item t + 1 are in flight into registers and
-// the stores of item t - 1 drain.  Memory goes through buffer instructions whose
-// out-of-range offsets read zero and drop stores, so rows and columns past n,
-// operand columns past kb and the upper half of a diagonal tile need no branch:
-// every item issues the same loads and stores, and the wait for the next item's
-// loads does not wait for the stores issued after them (loads and stores retire
-// in issue order).  The accumulation order per element is that of
-// k_trailing_update_lds.
-constexpr int kPipeMaxShifts = 256;
-constexpr int kPipeK = kMaxNb;  // widest panel (update rank) the persistent update takes
-// An offset past every buffer's range (the host keeps the kernel's buffers below
-// it), low enough that the end of an 8-byte access does not wrap.
-constexpr unsigned kPipeOob = 0xFFFFFF00u;
-
-__device__ __forceinline__ __amdgpu_buffer_rsrc_t pipe_rsrc(const double* p, unsigned bytes) {
-  return __builtin_amdgcn_make_buffer_rsrc(const_cast<double*>(p), (short)0, (int)bytes, 0x00020000);
-}
-typedef unsigned int pipe_u2 __attribute__((ext_vector_type(2)));
-__device__ __forceinline__ double pipe_ld(__amdgpu_buffer_rsrc_t r, unsigned off) {
-  return __builtin_bit_cast(double, __builtin_amdgcn_raw_buffer_load_b64(r, (int)off, 0, 0));
-}
-__device__ __forceinline__ void pipe_st(__amdgpu_buffer_rsrc_t r, unsigned off, double v) {
-  __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(pipe_u2, v), r, (int)off, 0, 0);
-}
-// `off` where `ok`, else an offset out of range, without a branch (a branch that
-// skipped the memory operation would make the count of outstanding operations
-// differ between paths, and the waits would then wait for everything).
-__device__ __forceinline__ unsigned pipe_off(bool ok, unsigned off) {
-  const unsigned m = (unsigned)ok - 1u;
-  return (off & ~m) | (kPipeOob & m);
-}
-// A pointer that every lane holds, as a scalar value.
-__device__ __forceinline__ double* pipe_uniform(double* p) {
-  const unsigned long long v = (unsigned long long)p;
-  const unsigned lo = __builtin_amdgcn_readfirstlane((unsigned)v);
-  const unsigned hi = __builtin_amdgcn_readfirstlane((unsigned)(v >> 32));
-  return (double*)(((unsigned long long)hi << 32) | lo);
-}
-
-__global__ __launch_bounds__(1024) void k_trailing_update_pipe(int n, double* const* LDs, long ldld,
-                                                              double* const* Wps, long ldw,
-                                                              const FactorState* states, int S) {
-  constexpr int TB = 128;
-  __shared__ double sL[kPipeK * kUpdLd];
-  __shared__ double sW[kPipeK * kUpdLd];
-  __shared__ int pre[kPipeMaxShifts + 1];
-  // per-shift panel start and width and matrix / panel pointers, read from LDS
-  // (never through the vector memory counter that the pipeline's waits count)
-  __shared__ int sk0[kPipeMaxShifts], skb[kPipeMaxShifts];
-  __shared__ double* sLD[kPipeMaxShifts];
-  __shared__ double* sWp[kPipeMaxShifts];
-  const int tid = threadIdx.x;
-  for (int q = tid; q < S; q += 1024) {
-    sk0[q] = states[q].k0;
-    skb[q] = states[q].kb;
-    sLD[q] = LDs[q];
-    sWp[q] = Wps[q];
-  }
-  // items per shift (tiles of its trailing lower triangle) and their prefix sums
-  if (tid < 64) {
-    int base = 0;
-    for (int q0 = 0; q0 < S; q0 += 64) {
-      const int q = q0 + tid;
-      int c = 0;
-      if (q < S) {
-        const int kb = states[q].kb, k1 = states[q].k0 + kb;
-        if (kb > 0 && k1 < n) {
-          const int T = (n - k1 + TB - 1) / TB;
-          c = T * (T + 1) / 2;
-        }
-      }
-#pragma unroll
-      for (int off = 1; off < 64; off <<= 1) {
-        const int o = __shfl_up(c, off);
-        if (tid >= off) c += o;
-      }
-      if (q < S) pre[q + 1] = base + c;
-      base += __shfl(c, 63);
-    }
-    if (tid == 0) pre[0] = 0;
-  }
-  __syncthreads();
-  const int M = pre[S];
-  const int G = gridDim.x, b = blockIdx.x;
-  const int slot = (G % 8 == 0) ? (b % 8) * (G / 8) + b / 8 : b;
-  const int i_begin = (int)((long)M * slot / G), i_end = (int)((long)M * (slot + 1) / G);
-  if (i_begin >= i_end) return;
-
-  const int w = __builtin_amdgcn_readfirstlane(tid >> 6), l = tid & 63;
-  const int wi = (w & 3) * 32, wj = (w >> 2) * 32;
-  const int lr = l & 15, lk = l >> 4;
-  const int sr = tid & 127, sc = tid >> 7;  // staging: row sr of k-columns sc + 8j
-  const unsigned ld8 = (unsigned)ldld * 8u, lw8 = (unsigned)ldw * 8u;
-  const unsigned bytes_ld = (unsigned)((size_t)ldld * n * 8);
-  const unsigned bytes_w = (unsigned)((size_t)ldw * (kPipeK + 2) * 8);
-
-  struct Item {
-    int s, k0, kb, ti, row0, col0;
-    bool diag;
-  };
-  int s_cur = 0;
-  auto decode = [&](int item, Item& it) {
-    while (pre[s_cur + 1] <= item) ++s_cur;
-    const int s = __builtin_amdgcn_readfirstlane(s_cur);
-    const int lin = item - pre[s];
-    int ti = (int)((sqrt(8.0 * lin + 1.0) - 1.0) * 0.5);
-    while (ti * (ti + 1) / 2 > lin) --ti;
-    while ((ti + 1) * (ti + 2) / 2 <= lin) ++ti;
-    const int tj = lin - ti * (ti + 1) / 2;
-    it.s = s;
-    it.k0 = __builtin_amdgcn_readfirstlane(sk0[s]);
-    it.kb = __builtin_amdgcn_readfirstlane(skb[s]);
-    const int k1 = it.k0 + it.kb;
-    it.ti = __builtin_amdgcn_readfirstlane(ti);
-    it.row0 = k1 + it.ti * TB;
-    it.col0 = __builtin_amdgcn_readfirstlane(k1 + tj * TB);
-    it.diag = (it.ti == tj);
-  };
-  double cn[2][2][4];
-  double wn[kPipeK / 8];
-  auto prefetch = [&](const Item& it) {
-    const __amdgpu_buffer_rsrc_t rLD = pipe_rsrc(pipe_uniform(sLD[it.s]), bytes_ld);
-    const __amdgpu_buffer_rsrc_t rW = pipe_rsrc(pipe_uniform(sWp[it.s]), bytes_w);
-#pragma unroll
-    for (int x = 0; x < 2; ++x) {
-      const int i = it.row0 + wi + 16 * x + lr;
-#pragma unroll
-      for (int y = 0; y < 2; ++y)
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          const int j = it.col0 + wj + 16 * y + lk + 4 * r;
-          cn[x][y][r] = pipe_ld(rLD, pipe_off((i < n) & (j < n), (unsigned)i * 8u + (unsigned)j * ld8));
-        }
-    }
-    const int wr = it.col0 + sr;
-#pragma unroll
-    for (int jj = 0; jj < kPipeK / 8; ++jj) {
-      const int k = sc + 8 * jj;
-      wn[jj] = pipe_ld(rW, pipe_off((k < it.kb) & (wr < n), (unsigned)wr * 8u + (unsigned)k * lw8));
-    }
-  };
-
-  Item cur, nxt;
-  int item = i_begin;
-  decode(item, nxt);
-  prefetch(nxt);
-  {
-    // the loop's sixteen stores, dropped (out of range): the loads above then have
-    // as many younger memory operations on entry as on the back edge, so the wait
-    // for them at the top of the loop does not wait for the stores
-    const __amdgpu_buffer_rsrc_t rLD = pipe_rsrc(pipe_uniform(sLD[nxt.s]), bytes_ld);
-#pragma unroll
-    for (int q = 0; q < 16; ++q) pipe_st(rLD, kPipeOob + 8u * q, 0.0);
-  }
-  int row_s = -1, row_t = -1;  // tile row whose L panel is in LDS
-  d4 acc[2][2];
-  for (;;) {
-    cur = nxt;
-    __syncthreads();  // every wavefront is done with the previous item's operands
-    if (cur.s != row_s || cur.ti != row_t) {
-      const __amdgpu_buffer_rsrc_t rLD = pipe_rsrc(pipe_uniform(sLD[cur.s]), bytes_ld);
-      const int li = cur.row0 + sr;
-      double lv[kPipeK / 8];
-#pragma unroll
-      for (int jj = 0; jj < kPipeK / 8; ++jj) {
-        const int k = sc + 8 * jj;
-        lv[jj] = pipe_ld(rLD, pipe_off((k < cur.kb) & (li < n), (unsigned)li * 8u + (unsigned)(cur.k0 + k) * ld8));
-      }
-#pragma unroll
-      for (int jj = 0; jj < kPipeK / 8; ++jj) sL[(sc + 8 * jj) * kUpdLd + sr] = lv[jj];
-      row_s = cur.s;
-      row_t = cur.ti;
-    }
-#pragma unroll
-    for (int jj = 0; jj < kPipeK / 8; ++jj) sW[(sc + 8 * jj) * kUpdLd + sr] = -wn[jj];
-#pragma unroll
-    for (int x = 0; x < 2; ++x)
-#pragma unroll
-      for (int y = 0; y < 2; ++y)
-#pragma unroll
-        for (int r = 0; r < 4; ++r) acc[x][y][r] = cn[x][y][r];
-    __syncthreads();
-    // the next item's loads go out before this item's MFMAs and stores; past the
-    // last item the current one is loaded again (unused), so every iteration
-    // issues the same memory operations
-    const bool more = item + 1 < i_end;
-    if (more) decode(item + 1, nxt);
-    prefetch(more ? nxt : cur);
-    const bool active = !(cur.diag && wi + 31 < wj);
-    if (active) {
-      const double* L0 = sL + wi + lr;
-      const double* W0 = sW + wj + lr;
-      // k-steps of 4 in pairs (the operands past kb are zero in LDS)
-      const int npair = (cur.kb + 7) >> 3;
-      for (int u = 0; u < npair; ++u) {
-        double lo[2][2], wo[2][2];
-#pragma unroll
-        for (int h = 0; h < 2; ++h) {
-          const int kk = (8 * u + 4 * h + lk) * kUpdLd;
-#pragma unroll
-          for (int x = 0; x < 2; ++x) lo[h][x] = L0[kk + 16 * x];
-#pragma unroll
-          for (int y = 0; y < 2; ++y) wo[h][y] = W0[kk + 16 * y];
-        }
-#pragma unroll
-        for (int h = 0; h < 2; ++h)
-#pragma unroll
-          for (int x = 0; x < 2; ++x)
-#pragma unroll
-            for (int y = 0; y < 2; ++y) acc[x][y] = mfma16x16x4(wo[h][y], lo[h][x], acc[x][y]);
-      }
-    }
-    {
-      const __amdgpu_buffer_rsrc_t rLD = pipe_rsrc(pipe_uniform(sLD[cur.s]), bytes_ld);
-#pragma unroll
-      for (int x = 0; x < 2; ++x) {
-        const int i = cur.row0 + wi + 16 * x + lr;
-#pragma unroll
-        for (int y = 0; y < 2; ++y)
-#pragma unroll
-          for (int r = 0; r < 4; ++r) {
-            const int j = cur.col0 + wj + 16 * y + lk + 4 * r;
-            pipe_st(rLD, pipe_off(active & (i < n) & (j < n) & (i >= j), (unsigned)i * 8u + (unsigned)j * ld8),
-                    acc[x][y][r]);
-          }
-      }
-    }
-    if (!more) break;
-    ++item;
   }
 }
 
@@ -1963,13 +1786,6 @@ void factor_shift_form_launch(const FactorPlan& fp, hipStream_t st) {
   SL_LAUNCH_CHECK();
 }
 
-// The persistent update addresses each shifted matrix and panel buffer with
-// 32-bit offsets below kPipeOob and keeps the per-shift table in LDS.
-static bool pipe_fits(const FactorPlan& fp) {
-  return fp.nshift <= kPipeMaxShifts && (double)fp.ldld * fp.n * 8.0 < (double)kPipeOob &&
-         fp.nb <= kPipeK && (double)fp.ldw * (kPipeK + 2) * 8.0 < (double)kPipeOob;
-}
-
 void factor_launch(const FactorPlan& fp, hipStream_t st) {
   factor_shift_form_launch(fp, st);
   factor_steps_launch(fp, st, true);
@@ -2005,18 +1821,18 @@ static bool panel_team(const FactorPlan& fp, long rem_max, long& need) {
          (need <= 1 || (need <= kTeamMax && need * fp.nshift <= (long)fp.cus * 7 / 8 / fp.groups));
 }
 
-static void panel_launch(const FactorPlan& fp, hipStream_t st, long rem_max, int nbpiv, int groups) {
+static void panel_launch(const FactorPlan& fp, hipStream_t st, long rem_max, int nbpiv, int groups, bool defer) {
   const int n = fp.n, S = fp.nshift, nb = fp.nb;
   if (!fp.pivot) {
     SL_LAUNCH(k_bk_panel<false>, dim3(S), dim3(1024), 0, st, n, fp.d_LD, fp.ldld, fp.d_W, fp.ldw,
-              fp.d_perm, fp.d_sw, fp.d_blk, fp.d_colpanel, fp.d_pstart, fp.d_state, nb, nbpiv);
+              fp.d_perm, fp.d_sw, fp.d_blk, fp.d_colpanel, fp.d_pstart, fp.d_state, nb, nbpiv, defer);
     SL_LAUNCH_CHECK();
     return;
   }
   long need;
   if (panel_team(fp, rem_max, need)) {
     TeamArgs a{n, fp.d_LD, fp.ldld, fp.d_W, fp.ldw, fp.d_perm, fp.d_sw, fp.d_blk, fp.d_colpanel,
-               fp.d_pstart, fp.d_state, fp.d_aux, fp.d_team, fp.wait_err, fp.wait_limit, nb, nbpiv, groups};
+               fp.d_pstart, fp.d_state, fp.d_aux, fp.d_team, fp.wait_err, fp.wait_limit, nb, nbpiv, groups, defer};
     // As few threads as hold the rows: a column's reductions, tests and barriers cost every
     // wavefront the same instructions, so a SIMD's wavefronts take turns at them.  Five
     // shifts at order 1001, all panels: 1.52 ms with 1024 threads to the end, 1.04 so.
@@ -2041,8 +1857,19 @@ static void panel_launch(const FactorPlan& fp, hipStream_t st, long rem_max, int
     }
   } else {
     SL_LAUNCH(k_bk_panel<true>, dim3(S), dim3(1024), 0, st, n, fp.d_LD, fp.ldld, fp.d_W, fp.ldw,
-              fp.d_perm, fp.d_sw, fp.d_blk, fp.d_colpanel, fp.d_pstart, fp.d_state, nb, nbpiv);
+              fp.d_perm, fp.d_sw, fp.d_blk, fp.d_colpanel, fp.d_pstart, fp.d_state, nb, nbpiv, defer);
   }
+  SL_LAUNCH_CHECK();
+}
+
+// The update on 128x128 tiles, one workgroup a tile, of at most `rem` rows; with groups > 0
+// that of the panel before, where the present one is not whole.
+static void update_tiles_launch(const FactorPlan& fp, hipStream_t st, long rem, int groups) {
+  const long T = ceil_div(rem, 128);
+  const double* const* auxs = groups > 0 ? (const double* const*)fp.d_aux : nullptr;
+  const auto update = fp.stream_c ? k_trailing_update_lds<true> : k_trailing_update_lds<false>;
+  SL_LAUNCH(update, dim3((unsigned)(T * (T + 1) / 2), fp.nshift), dim3(1024), 0, st, fp.n, fp.d_LD,
+            fp.ldld, fp.d_W, fp.ldw, fp.d_state, auxs, fp.nb, groups);
   SL_LAUNCH_CHECK();
 }
 
@@ -2050,8 +1877,10 @@ static void panel_launch(const FactorPlan& fp, hipStream_t st, long rem_max, int
 // pivot-free panel, the pivoting panel and the trailing update.  k0_lb is a lower
 // bound on the step's first column (it sizes the update grid).  `after_panel`,
 // when given, is recorded once the pivoting panel is enqueued.
+// With `defer` a whole panel may leave its update to the next one (the panels run as teams);
+// `pending` says that the step before was such a step.
 static void factor_step(const FactorPlan& fp, hipStream_t st, long k0_lb, sislice_handle* ph,
-                        hipEvent_t after_panel) {
+                        hipEvent_t after_panel, bool defer = false, bool pending = false) {
   const int n = fp.n, S = fp.nshift, nb = fp.nb;
   const int nbpiv = fp.fast ? fp.nbpiv : nb;
   const int min_kb = factor_min_panel(nb, fp.nbpiv, fp.fast != 0);
@@ -2070,6 +1899,7 @@ static void factor_step(const FactorPlan& fp, hipStream_t st, long k0_lb, sislic
               fp.ldld, fp.d_W, fp.ldw, fp.d_aux, fp.d_state, fp.d_team, nb);
     SL_LAUNCH_CHECK();
     long need;
+    if (pending) update_tiles_launch(fp, st, n - k0_lb, groups);  // a panel that is not whole
     if (!panel_team(fp, n - k0_lb, need)) {
       SL_LAUNCH(k_fast_commit, dim3(nb, S), dim3(256), 0, st, n, fp.d_LD, fp.ldld,
                 (const double* const*)fp.d_W, fp.ldw, (const double* const*)fp.d_aux, fp.d_blk,
@@ -2078,29 +1908,15 @@ static void factor_step(const FactorPlan& fp, hipStream_t st, long k0_lb, sislic
     }
   }
   if (tpan < 0) tpan = prof_begin(ph, kProfPanel, st);
-  panel_launch(fp, st, n - k0_lb, nbpiv, groups);
+  panel_launch(fp, st, n - k0_lb, nbpiv, groups, defer);
   SL_LAUNCH_CHECK();
   prof_end(ph, tpan, st);
   if (after_panel) SL_HIP(hipEventRecord(after_panel, st));
   const long k1_lb = std::min<long>(n, k0_lb + min_kb);
   if (k1_lb >= n) return;
   const int tu = prof_begin(ph, kProfUpdate, st);
-  if (n - k1_lb >= fp.wide_min && fp.update_pipe && pipe_fits(fp)) {
-    // one workgroup per CU, at most one per item (an upper bound on the items
-    // from the least advanced shift), a multiple of the 8 XCDs when it can be
-    const long T = ceil_div(n - k1_lb, 128);
-    long G = std::min<long>(std::max(fp.cus, 8), T * (T + 1) / 2 * S);
-    if (G >= 8) G -= G % 8;
-    SL_LAUNCH(k_trailing_update_pipe, dim3((unsigned)G), dim3(1024), 0, st, n, fp.d_LD, fp.ldld,
-              fp.d_W, fp.ldw, fp.d_state, S);
-  } else if (n - k1_lb >= fp.wide_min) {
-    const long T = ceil_div(n - k1_lb, 128);
-    if (fp.stream_c)
-      SL_LAUNCH(k_trailing_update_lds<true>, dim3((unsigned)(T * (T + 1) / 2), S), dim3(1024), 0, st,
-                n, fp.d_LD, fp.ldld, fp.d_W, fp.ldw, fp.d_state);
-    else
-      SL_LAUNCH(k_trailing_update_lds<false>, dim3((unsigned)(T * (T + 1) / 2), S), dim3(1024), 0,
-                st, n, fp.d_LD, fp.ldld, fp.d_W, fp.ldw, fp.d_state);
+  if (defer || pending || n - k1_lb >= fp.wide_min) {
+    update_tiles_launch(fp, st, n - k1_lb, 0);
   } else {
     const long T = ceil_div(n - k1_lb, 64);
     SL_LAUNCH(k_trailing_update, dim3((unsigned)(T * (T + 1) / 2), S), dim3(256), 0, st, n,
@@ -2125,6 +1941,16 @@ static void factor_tail(const FactorPlan& fp, hipStream_t st) {
             fp.d_blk, fp.d_ipiv, fp.d_state, fp.d_inertia);
   SL_LAUNCH_CHECK();
 }
+
+// Whether updates in pairs pay with `rem` rows left: where the trailing triangles (half of
+// 8 rem^2 bytes each) outgrow the 256 MB memory-side cache and an update is a pass over
+// memory.  With every panel whole, pairs on and off: order 4096, 17 shifts 19.1 and 21.4 ms;
+// 8192, 24 shifts 137 and 165; 8192, 2 shifts 21.0 and 23.1; below, 4096, 4 shifts 8.30 and
+// 8.20; 2048, 8 shifts 3.76 and 3.61 (two more launches a pair).
+static bool pairs_pay(long rem, int nb, int nshift) {
+  return nb == kMaxNb && 4.0 * (double)rem * (double)rem * nshift >= (double)(256u << 20);
+}
+bool factor_pairs(int n, int nb, int nshift, bool pivot) { return pivot && pairs_pay(n, nb, nshift); }
 
 void factor_steps_launch(const FactorPlan& fp, hipStream_t st, bool readback) {
   const int n = fp.n, S = fp.nshift, nb = fp.nb;
@@ -2157,15 +1983,14 @@ void factor_steps_launch(const FactorPlan& fp, hipStream_t st, bool readback) {
   std::vector<long> kmin(G, 0);
   std::vector<int> steps(G, 0);
   std::vector<char> launched(G, 0);
+  // updates in pairs: whether the last chunk's panels were mostly whole, the panels and whole
+  // panels so far, and whether the step before deferred
+  std::vector<char> mostly(G, 1), pending(G, 0);
+  std::vector<long> panels(G, 0), whole(G, 0);
   for (int g = 0; g < G; ++g) {
     const int s0 = (int)((long)S * g / G), s1 = (int)((long)S * (g + 1) / G);
     sub[g] = factor_subplan(fp, s0, s1 - s0);
-    // a persistent update would hold every CU for its whole launch and keep the
-    // other groups' panels waiting: grouped runs take the workgroup-per-tile form
-    if (G > 1) {
-      sub[g].update_pipe = 0;
-      sub[g].stream_c = 1;
-    }
+    if (G > 1) sub[g].stream_c = 1;
     gs[g] = g == 0 ? st : group_stream(ph, g - 1);
   }
   FactorState* hs = static_cast<FactorState*>(host_stage(ph, sizeof(FactorState) * S));
@@ -2183,7 +2008,10 @@ void factor_steps_launch(const FactorPlan& fp, hipStream_t st, bool readback) {
       any = true;
       for (int q = 0; q < kChunk && steps[g] < step_cap; ++q, ++steps[g]) {
         hipEvent_t mark = (first && q == 0 && g + 1 < G) ? group_event(ph, g + 1) : nullptr;
-        factor_step(sub[g], gs[g], std::min<long>(n, kmin[g] + (long)q * min_kb), ph, mark);
+        const long lb = std::min<long>(n, kmin[g] + (long)q * min_kb);
+        const bool defer = mostly[g] && sub[g].defer && pairs_pay(n - lb, nb, S);
+        factor_step(sub[g], gs[g], lb, ph, mark, defer, pending[g]);
+        pending[g] = defer;
         if (mark) SL_HIP(hipStreamWaitEvent(gs[g + 1], mark, 0));
       }
       const FactorPlan& f = sub[g];
@@ -2197,8 +2025,16 @@ void factor_steps_launch(const FactorPlan& fp, hipStream_t st, bool readback) {
       const FactorPlan& f = sub[g];
       const FactorState* h0 = hs + (f.d_state - fp.d_state);
       long km = n;
-      for (int q = 0; q < f.nshift; ++q) km = std::min<long>(km, h0[q].done ? n : h0[q].k0 + h0[q].kb);
+      long np = 0, nw = 0;
+      for (int q = 0; q < f.nshift; ++q) {
+        km = std::min<long>(km, h0[q].done ? n : h0[q].k0 + h0[q].kb);
+        np += h0[q].npanel;
+        nw += h0[q].whole;
+      }
       kmin[g] = km;
+      mostly[g] = 4 * (nw - whole[g]) >= 3 * (np - panels[g]);
+      panels[g] = np;
+      whole[g] = nw;
     }
   }
   for (int g = 0; g < G; ++g)

@@ -175,7 +175,9 @@ FactorPlan build_factor(sislice_handle* h, int bufid, int n, const double* A, lo
   const long ldw = n;
   Sizer z;
   z.take<double>(S);                          // sigmas
-  z.take<double>((size_t)S * ldw * (nb + 2));  // W
+  const bool defer = factor_pairs(n, nb, S, pivot);
+  const int wcols = (defer ? 2 * nb : nb) + 2;
+  z.take<double>((size_t)S * ldw * wcols);  // W
   for (int q = 0; q < 4; ++q) z.take<int>((size_t)S * n);
   z.take<int>((size_t)S * npmax);
   z.take<int>((size_t)S * npmax * n);
@@ -197,7 +199,8 @@ FactorPlan build_factor(sislice_handle* h, int bufid, int n, const double* A, lo
   fp.ldld = ldld;
   fp.ldw = ldw;
   double* d_sig = c.take<double>(S);
-  double* W = c.take<double>((size_t)S * ldw * (nb + 2));
+  double* W = c.take<double>((size_t)S * ldw * wcols);
+  fp.defer = defer;
   int* perm = c.take<int>((size_t)S * n);
   int* sw = c.take<int>((size_t)S * n);
   int* blk = c.take<int>((size_t)S * n);
@@ -216,7 +219,7 @@ FactorPlan build_factor(sislice_handle* h, int bufid, int n, const double* A, lo
   void** ht = reinterpret_cast<void**>(hs + sizeof(double) * S);
   for (int s = 0; s < S; ++s) {
     ht[0 * S + s] = LD_host[s];
-    ht[1 * S + s] = W + (size_t)s * ldw * (nb + 2);
+    ht[1 * S + s] = W + (size_t)s * ldw * wcols;
     ht[2 * S + s] = perm + (size_t)s * n;
     ht[3 * S + s] = sw + (size_t)s * n;
     ht[4 * S + s] = blk + (size_t)s * n;

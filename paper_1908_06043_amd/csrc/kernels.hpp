@@ -47,7 +47,7 @@ struct FactorPlan {
   int fast = 1;                    // use the pivot-free path
   int nbpiv = 32;                  // columns a pivoting panel handles after a rejection (default_nbpiv)
   int wide_min = 1024;             // trailing order from which the update takes 128x128 tiles
-  int update_pipe = 1;             // 128x128 updates by the persistent pipelined kernel
+  int defer = 0;                   // W has room for two panels: whole ones may be updated in pairs
   int stream_c = 0;                // the 128-tile update streams C (shift groups on two streams)
   int cus = 256;                   // compute units of the device (its persistent grid)
   int groups = 1;                  // shift groups run on separate streams (with readback)
@@ -63,6 +63,8 @@ void factor_launch(const FactorPlan& fp, hipStream_t st);
 // device tables only).
 void factor_shift_form_launch(const FactorPlan& fp, hipStream_t st);
 void factor_steps_launch(const FactorPlan& fp, hipStream_t st, bool readback);
+// Columns of W a shift needs, and whether updates in pairs can pay at all.
+bool factor_pairs(int n, int nb, int nshift, bool pivot);
 // One-time kernel attributes of the factorization (outside any capture).
 void factor_prepare();
 

@@ -60,3 +60,26 @@ def test_more_shifts_than_workgroups_a_shift(gpu_lib, shifts):
         g = gpu_lib.ldlt_factor(dev(C), dev(np.eye(n)), sig[k])
         assert torch.equal(g.ipiv, facs[k].ipiv)
         assert torch.equal(torch.tril(g.LD), torch.tril(facs[k].LD))
+
+
+@pytest.mark.parametrize("rows", [[], [0], [1], [2, 3], [5, 8, 9], [0, 1, 2, 3, 4, 5, 6, 7, 8], [31]])
+def test_paired_updates_equal_single_ones_bitwise(gpu_lib, rows):
+    """17 shifts of order 2085 are large enough for whole panels to be updated in pairs, one
+    shift alone is not.  The panels named get an entry that needs pivoting, so that pairs are
+    completed, caught up, left at the end or never begun."""
+    n, S = 2085, 17
+    C = _dominant(n)
+    for p in rows:
+        i, j = 64 * p + 11, min(64 * p + 900, n - 1)
+        C[i, j] = C[j, i] = 1e3 * np.abs(C).max()
+    A, I = dev(C), dev(np.eye(n))
+    sig = [float(s) for s in np.linspace(-3.0, 3.0, S)]
+    facs = gpu_lib.ldlt_factor_multi(A, I, sig)
+    for k in (0, 9, S - 1):
+        g = gpu_lib.ldlt_factor(A, I, sig[k])
+        assert g.inertia == facs[k].inertia
+        assert torch.equal(g.ipiv, facs[k].ipiv)
+        assert torch.equal(torch.tril(g.LD), torch.tril(facs[k].LD))
+    f = facs[9]
+    B = C - sig[9] * np.eye(n)
+    assert backward_error(B, f.LD.cpu().numpy(), f.ipiv.cpu().numpy()) <= 100 * n * U
