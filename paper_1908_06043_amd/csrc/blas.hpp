@@ -38,7 +38,12 @@ void sym_full_launch(int n, const double* S, long lds, double* F, long ldf, hipS
 // in the other half), X n x ncol, ncol <= kSkinnyMaxCol; `partial` holds
 // ceil(n / kSkinnyKc) * n * ncol doubles.
 constexpr int kSkinnyMaxCol = 32;
-constexpr int kSkinnyKc = 256;
+// Columns of M a workgroup takes: few enough that a small matrix still gives every CU a
+// workgroup and its chain (staging X, then 64 cycles per MFMA) is short, enough that the
+// partials stay a small part of the traffic.  Products of 20 columns at order 1000: 14 us
+// with 256, 7 with 128, 6 with 64; planning at 2048: 5.91, 5.51 and 5.62 ms; a solve at 4096:
+// 71.3, 70.9 and 71.6 ms.
+constexpr int kSkinnyKc = 128;
 inline size_t skinny_partial_size(int n, int ncol) {
   return (size_t)ceil_div(n, kSkinnyKc) * n * ncol;
 }
