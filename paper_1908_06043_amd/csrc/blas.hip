@@ -433,18 +433,19 @@ void skinny_launch(int n, int ncol, const double* M, long ldm, int tri, const do
 // reading the n x m basis once.  The generic 64x64-tile GEMM spends 8x its work on
 // padding here; these kernels stream the basis instead.
 //
-// k_tsmt: C_b = V_b^T X_b (m_b x 8).  A workgroup takes kTsRows rows of one batch
+// k_tsmt: C_b = V_b^T X_b (m_b x 8).  A workgroup takes ts_rows rows of one batch
 // entry and 64 columns of V, stages 64-row slices of V through LDS (coalesced
 // along the rows) and accumulates 8 dot products per column in four row phases;
 // per-chunk partials are summed in chunk order by k_tsmt_reduce.
+template <int ROWS>
 __global__ __launch_bounds__(256) void k_tsmt(TsArgs a) {
   __shared__ double sV[64][65];
-  __shared__ double sX[kTsRows][8];
+  __shared__ double sX[ROWS][8];
   const int b = blockIdx.z, q = blockIdx.x;
   const int m = a.m[b];
   const int i0 = blockIdx.y * 64;
   if (i0 >= m) return;
-  const int n = a.n, r0 = q * kTsRows;
+  const int n = a.n, r0 = q * ROWS;
   const double* V = a.V[b];
   const double* X = a.X[b];
   const int tid = threadIdx.x;
@@ -455,11 +456,11 @@ __global__ __launch_bounds__(256) void k_tsmt(TsArgs a) {
   const gcd* Vg = (const gcd*)V;
   // the X slice: every load issued before any store (a rolled load / wait / store loop
   // made one memory round trip per element a thread stages)
-  constexpr int XE = kTsRows * 8 / 256;
+  constexpr int XE = ROWS * 8 / 256;
   double xv[XE];
 #pragma unroll
   for (int u = 0; u < XE; ++u) {
-    const int e = tid + 256 * u, r = e % kTsRows, c = e / kTsRows;
+    const int e = tid + 256 * u, r = e % ROWS, c = e / ROWS;
     xv[u] = Xg[min(r0 + r, n - 1) + (long)c * a.ldx];
   }
   const int i = tid & 63, rg = tid >> 6;
@@ -480,10 +481,10 @@ __global__ __launch_bounds__(256) void k_tsmt(TsArgs a) {
   load_v(0);
 #pragma unroll
   for (int u = 0; u < XE; ++u) {
-    const int e = tid + 256 * u, r = e % kTsRows, c = e / kTsRows;
+    const int e = tid + 256 * u, r = e % ROWS, c = e / ROWS;
     sX[r][c] = (r0 + r < n) ? xv[u] : 0.0;
   }
-  for (int st = 0; st < kTsRows / 64; ++st) {
+  for (int st = 0; st < ROWS / 64; ++st) {
     __syncthreads();
     const int rs = r0 + 64 * st;
 #pragma unroll
@@ -491,7 +492,7 @@ __global__ __launch_bounds__(256) void k_tsmt(TsArgs a) {
       const int e = tid + 256 * j, r = e & 63, ii = e >> 6;
       sV[r][ii] = ((rs + r < n) & (i0 + ii < m)) ? vn[j] : 0.0;
     }
-    if (st + 1 < kTsRows / 64) load_v(st + 1);
+    if (st + 1 < ROWS / 64) load_v(st + 1);
     __syncthreads();
     for (int rr = rg; rr < 64; rr += 4) {
       const double v = sV[rr][i];
@@ -530,10 +531,11 @@ __global__ __launch_bounds__(256) void k_tsmt_reduce(TsArgs a) {
 void tsmt_launch(TsArgs a, int batch, int mmax, hipStream_t st) {
   if (batch <= 0 || mmax <= 0) return;
   a.mmax = mmax;
-  a.nchunk = (int)ceil_div(a.n, kTsRows);
+  const int rows = ts_rows(a.n);
+  a.nchunk = (int)ceil_div(a.n, rows);
   sislice_handle* ph = current_handle();
   const int tk = prof_begin(ph, kProfGemm, st);
-  SL_LAUNCH(k_tsmt, dim3(a.nchunk, (unsigned)ceil_div(mmax, 64), batch), dim3(256), 0, st, a);
+  SL_LAUNCH(rows == 64 ? k_tsmt<64> : k_tsmt<256>, dim3(a.nchunk, (unsigned)ceil_div(mmax, 64), batch), dim3(256), 0, st, a);
   SL_LAUNCH_CHECK();
   SL_LAUNCH(k_tsmt_reduce, dim3((unsigned)ceil_div(mmax * 8, 256), batch), dim3(256), 0, st, a);
   SL_LAUNCH_CHECK();

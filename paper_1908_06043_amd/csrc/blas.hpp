@@ -70,8 +70,11 @@ void scale_cols_launch(int n, int ncol, const double* s2, const double* X, long 
 //   tsmt: C_b (m_b x 8, ldc) = alpha V_b^T X_b          (V_b n x m_b, X_b n x 8)
 //   tsmm: Y_b (n x 8, ldy) = beta Y_b + alpha (V_b C_b + V2_b C2_b)
 //         (V2/C2/m2 optional; C_b m_b x 8 with ldc, C2_b m2_b x 8 with ldc2)
-// tsmt needs `partial` with batch * ceil(n / kTsRows) * mmax * 8 doubles.
-constexpr int kTsRows = 256;
+// tsmt needs `partial` with batch * ceil(n / ts_rows(n)) * mmax * 8 doubles.
+// Rows a workgroup takes: one 64-row slice where few rows would otherwise leave most CUs
+// idle, four where the partials' sum would grow long (gradient at order 2048: 35.3 ms with
+// 256, 34.6 with 64; solves at 1000: 18.5 and 18.2, at 4096: 71.3 and 71.4).
+inline int ts_rows(int n) { return n <= 2048 ? 64 : 256; }
 constexpr size_t kTsmmMaxLds = 160 * 1024;
 struct TsArgs {
   int n = 0;
@@ -95,7 +98,7 @@ struct TsArgs {
   int nchunk = 0, mmax = 0;
 };
 inline size_t tsmt_partial_size(int n, int batch, int mmax) {
-  return (size_t)batch * ceil_div(n, kTsRows) * mmax * 8;
+  return (size_t)batch * ceil_div(n, ts_rows(n)) * mmax * 8;
 }
 void tsmt_launch(TsArgs a, int batch, int mmax, hipStream_t st);
 void tsmm_launch(TsArgs a, int batch, int mtot_max, hipStream_t st);
