@@ -70,8 +70,8 @@ struct FactorState {
   int64_t neg, zero, pos;  // inertia of D accumulated over the pivots
   int32_t jstart;    // columns of the current panel accepted by the pivot-free path
   int32_t whole;     // panels accepted whole by it so far
-  // A whole panel's update may wait for the next panel's (its width, else 0): the next
-  // panel's columns have it, the columns after them do not.  Its W stays in columns
+  // Whole panels' updates may wait for later panels (their columns so far, else 0): the next
+  // panel's columns have them, the columns after it do not.  Their W stays in columns
   // 0 .. pend - 1 of the workspace; the next panel's goes behind it.
   int32_t pend;
   // the update after the panel: columns u_c0 .. u_c1 - 1 by the u_kb columns of L from

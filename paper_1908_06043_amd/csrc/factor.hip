@@ -17,7 +17,7 @@
 //     columns that need no pivoting.
 //   * k_trailing_update, k_trailing_update_lds: the lower triangle of the trailing
 //     matrix is updated with C22 -= L21 W21^T on FP64 MFMA (v_mfma_f64_16x16x4),
-//     64x64 and 128x128 tiles, all shifts in one launch; large ones two panels at once.
+//     64x64 and 128x128 tiles, all shifts in one launch; large ones several panels at once.
 //   * Interchanges found in later panels are applied to earlier L columns once at
 //     the end (k_perm_suffix builds the suffix permutations, k_left_gather moves
 //     the rows), so that P C P^T = L D L^T with a single permutation P.
@@ -376,11 +376,12 @@ __device__ __forceinline__ void accept_state(FactorState* st, const double* Dv, 
 }
 
 // The state after a panel of j columns from k0, js of them accepted by the pivot-free path
-// (nbe: the columns that path took on), and the update that follows; one thread.
+// (nbe: the columns that path took on), and the update that follows, at most `defer` whole
+// panels together; one thread.
 __device__ __forceinline__ void panel_done(FactorState* st, int n, int nb, int nbe, int k0, int j, int js,
-                                           int panel, bool defer) {
+                                           int panel, int defer) {
   const int pend = st->pend, k1 = k0 + j;
-  const bool pair = pend > 0 && js == nbe;  // (otherwise the panel before has been caught up)
+  const int before = js == nbe ? pend : 0;  // (otherwise the panels before have been caught up)
   const bool whole = js == nb;
   st->k0 = k0;
   st->kb = j;
@@ -388,16 +389,13 @@ __device__ __forceinline__ void panel_done(FactorState* st, int n, int nb, int n
   st->done = k1 >= n;
   st->jstart = 0;
   st->whole += whole;
-  st->u_k0 = pair ? k0 - pend : k0;
-  st->u_kb = pair ? pend + j : j;
-  st->u_w0 = pair ? 0 : pend;
+  const bool wait = whole && before + nb < defer * nb && k1 < n;
+  st->u_k0 = k0 - before;
+  st->u_kb = before + j;
+  st->u_w0 = pend - before;
   st->u_c0 = k1;
-  st->u_c1 = n;
-  st->pend = 0;
-  if (defer && whole && !pend && k1 < n) {
-    st->u_c1 = min(n, k1 + nb);
-    st->pend = j;
-  }
+  st->u_c1 = wait ? min(n, k1 + nb) : n;
+  st->pend = wait ? before + j : 0;
 }
 
 // Accepts the prefix, one workgroup a column, where no team follows (a team accepts for itself).
@@ -430,7 +428,7 @@ __device__ __forceinline__ void bk_panel_rows(int n, double* const* LDs, long ld
                                               int* const* swps, int* const* blks,
                                               int* const* colpanels, int* const* pstarts,
                                               FactorState* states, int nb, int nbpiv, int s,
-                                              bool defer) {
+                                              int defer) {
   constexpr int NW = NT / 64;
   const int tid = threadIdx.x;
   FactorState* st = states + s;
@@ -714,7 +712,7 @@ __global__ __launch_bounds__(1024) void k_bk_panel(int n, double* const* LDs, lo
                                                    double* const* Wps, long ldw, int* const* perms,
                                                    int* const* swps, int* const* blks,
                                                    int* const* colpanels, int* const* pstarts,
-                                                   FactorState* states, int nb, int nbpiv, bool defer) {
+                                                   FactorState* states, int nb, int nbpiv, int defer) {
   bk_panel_rows<PIVOT, 1024>(n, LDs, ldld, Wps, ldw, perms, swps, blks, colpanels, pstarts, states,
                              nb, nbpiv, blockIdx.x, defer);
 }
@@ -773,7 +771,7 @@ struct TeamArgs {
   unsigned* wait_err;
   unsigned wait_limit;
   int nb, nbpiv, groups;  // groups: workgroups of k_fast_panel
-  bool defer;             // a whole panel's update may wait for the next one's
+  int defer;              // whole panels that may be updated together (0: each by itself)
 };
 
 __device__ __forceinline__ double team_ld(const double* p) {
@@ -1505,26 +1503,22 @@ __global__ __launch_bounds__(256) void k_trailing_update(int n, double* const* L
 // a CU keeps two workgroups (eight wavefronts per SIMD) in flight; the C tile is read and
 // written once per 128x128.  The operand panels of the tile (128 rows of L and 128
 // rows of W, 16 k-columns per chunk) are fetched once per workgroup with coalesced
-// 1 KB column runs into double-buffered LDS (74 KB), and the next chunk is in
+// 1 KB column runs into double-buffered LDS (70 KB), and the next chunk is in
 // flight while the wavefronts run the current one's MFMAs: nothing touches the fetched
 // values before they go to LDS (a sign or a select there waits for them, 30 TF/s).
-// Layout per chunk and operand: [k][row], rows padded to 144 doubles so that two
-// k-groups of a wavefront's reads cover the 64 banks once (132: 1% more per factorization).
+// Layout per chunk and operand: [k][row], rows padded to 136 doubles (132 and 144: 2% more
+// per update of many columns).
 //
 // What bounds it: at 64 columns the C stream, 2 x 8 bytes per 128 flops (4.0 TB/s of the
-// 4.6 a copy reaches); so a panel that the pivot-free path accepted whole updates the next
-// panel's columns only, one column of tiles, and if the next one is whole too both go into
-// C together, 128 columns (45 TF/s: 17 shifts of order 4096 788 us, two updates of 64
-// 1080).  Otherwise the panel before is caught up first (`auxs` given: the panel's masks
+// 4.6 a copy reaches).  So a panel that the pivot-free path accepted whole updates the next
+// panel's columns only, one column of tiles, and up to kDeferPanels of them go into C
+// together; then the matrix instructions bound it (50 TF/s; 68 without the staging).  When
+// a panel is not whole, those waiting are caught up first (`auxs` given: the panel's masks
 // decide), since pivoting may look at any column.  The order of the sums is the same either
-// way, so the factors are the same bits.
-// With STREAM the C tile is read and written non-temporally: when the shifts run in
-// two groups on two streams (large orders), C has no reuse in the caches before the
-// next update, and streaming it keeps the other group's panel data resident (at
-// order 12288, 49 shifts: 2975 -> 2718 us per update launch, about 2% per
-// factorization).
+// way, so the factors are the same bits.  17 shifts of order 4096, 384 columns: 1.75 ms, in
+// six updates of 64 3.2.
 constexpr int kUpdK = 16;           // k-columns per staged chunk
-constexpr int kUpdLd = 128 + 16;    // padded row count per k-column
+constexpr int kUpdLd = 128 + 8;     // padded row count per k-column
 template <bool STREAM>
 __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(8))) void k_trailing_update_lds(
     int n, double* const* LDs, long ldld, double* const* Wps, long ldw, const FactorState* states,
@@ -1821,7 +1815,7 @@ static bool panel_team(const FactorPlan& fp, long rem_max, long& need) {
          (need <= 1 || (need <= kTeamMax && need * fp.nshift <= (long)fp.cus * 7 / 8 / fp.groups));
 }
 
-static void panel_launch(const FactorPlan& fp, hipStream_t st, long rem_max, int nbpiv, int groups, bool defer) {
+static void panel_launch(const FactorPlan& fp, hipStream_t st, long rem_max, int nbpiv, int groups, int defer) {
   const int n = fp.n, S = fp.nshift, nb = fp.nb;
   if (!fp.pivot) {
     SL_LAUNCH(k_bk_panel<false>, dim3(S), dim3(1024), 0, st, n, fp.d_LD, fp.ldld, fp.d_W, fp.ldw,
@@ -1877,10 +1871,10 @@ static void update_tiles_launch(const FactorPlan& fp, hipStream_t st, long rem, 
 // pivot-free panel, the pivoting panel and the trailing update.  k0_lb is a lower
 // bound on the step's first column (it sizes the update grid).  `after_panel`,
 // when given, is recorded once the pivoting panel is enqueued.
-// With `defer` a whole panel may leave its update to the next one (the panels run as teams);
+// With `defer` > 0 a whole panel may leave its update to a later one (at most `defer` together);
 // `pending` says that the step before was such a step.
 static void factor_step(const FactorPlan& fp, hipStream_t st, long k0_lb, sislice_handle* ph,
-                        hipEvent_t after_panel, bool defer = false, bool pending = false) {
+                        hipEvent_t after_panel, int defer = 0, bool pending = false) {
   const int n = fp.n, S = fp.nshift, nb = fp.nb;
   const int nbpiv = fp.fast ? fp.nbpiv : nb;
   const int min_kb = factor_min_panel(nb, fp.nbpiv, fp.fast != 0);
@@ -1942,15 +1936,20 @@ static void factor_tail(const FactorPlan& fp, hipStream_t st) {
   SL_LAUNCH_CHECK();
 }
 
-// Whether updates in pairs pay with `rem` rows left: where the trailing triangles (half of
-// 8 rem^2 bytes each) outgrow the 256 MB memory-side cache and an update is a pass over
-// memory.  With every panel whole, pairs on and off: order 4096, 17 shifts 19.1 and 21.4 ms;
-// 8192, 24 shifts 137 and 165; 8192, 2 shifts 21.0 and 23.1; below, 4096, 4 shifts 8.30 and
-// 8.20; 2048, 8 shifts 3.76 and 3.61 (two more launches a pair).
-static bool pairs_pay(long rem, int nb, int nshift) {
+// Whether whole panels wait for one another with `rem` rows left: where the trailing
+// triangles (half of 8 rem^2 bytes each) outgrow the 256 MB memory-side cache and an update
+// is a pass over memory.  With every panel whole, in pairs and at once: order 4096, 17 shifts
+// 19.1 and 21.4 ms; 8192, 24 shifts 137 and 165; 8192, 2 shifts 21.0 and 23.1; below, 4096,
+// 4 shifts 8.30 and 8.20; 2048, 8 shifts 3.76 and 3.61 (a launch more a panel).
+static bool defer_pays(long rem, int nb, int nshift) {
   return nb == kMaxNb && 4.0 * (double)rem * (double)rem * nshift >= (double)(256u << 20);
 }
-bool factor_pairs(int n, int nb, int nshift, bool pivot) { return pivot && pairs_pay(n, nb, nshift); }
+int factor_defers(int n, int nb, int nshift, bool pivot) {
+  if (!pivot || n <= 0 || nshift <= 0 || !defer_pays(n, nb, nshift)) return 0;
+  const double panel = 8.0 * (double)n * nb * nshift;  // bytes of W a panel
+  const int p = (int)std::min<double>(kDeferPanels, 1.0 + (double)(4ull << 30) / panel);
+  return p > 1 ? p : 0;
+}
 
 void factor_steps_launch(const FactorPlan& fp, hipStream_t st, bool readback) {
   const int n = fp.n, S = fp.nshift, nb = fp.nb;
@@ -1983,7 +1982,7 @@ void factor_steps_launch(const FactorPlan& fp, hipStream_t st, bool readback) {
   std::vector<long> kmin(G, 0);
   std::vector<int> steps(G, 0);
   std::vector<char> launched(G, 0);
-  // updates in pairs: whether the last chunk's panels were mostly whole, the panels and whole
+  // waiting updates: whether the last chunk's panels were mostly whole, the panels and whole
   // panels so far, and whether the step before deferred
   std::vector<char> mostly(G, 1), pending(G, 0);
   std::vector<long> panels(G, 0), whole(G, 0);
@@ -2009,9 +2008,9 @@ void factor_steps_launch(const FactorPlan& fp, hipStream_t st, bool readback) {
       for (int q = 0; q < kChunk && steps[g] < step_cap; ++q, ++steps[g]) {
         hipEvent_t mark = (first && q == 0 && g + 1 < G) ? group_event(ph, g + 1) : nullptr;
         const long lb = std::min<long>(n, kmin[g] + (long)q * min_kb);
-        const bool defer = mostly[g] && sub[g].defer && pairs_pay(n - lb, nb, S);
+        const int defer = mostly[g] && defer_pays(n - lb, nb, S) ? sub[g].defer : 0;
         factor_step(sub[g], gs[g], lb, ph, mark, defer, pending[g]);
-        pending[g] = defer;
+        pending[g] = defer > 0;
         if (mark) SL_HIP(hipStreamWaitEvent(gs[g + 1], mark, 0));
       }
       const FactorPlan& f = sub[g];

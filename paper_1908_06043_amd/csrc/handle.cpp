@@ -175,8 +175,8 @@ FactorPlan build_factor(sislice_handle* h, int bufid, int n, const double* A, lo
   const long ldw = n;
   Sizer z;
   z.take<double>(S);                          // sigmas
-  const bool defer = factor_pairs(n, nb, S, pivot);
-  const int wcols = (defer ? 2 * nb : nb) + 2;
+  const int defer = factor_defers(n, nb, S, pivot);
+  const int wcols = std::max(defer, 1) * nb + 2;
   z.take<double>((size_t)S * ldw * wcols);  // W
   for (int q = 0; q < 4; ++q) z.take<int>((size_t)S * n);
   z.take<int>((size_t)S * npmax);

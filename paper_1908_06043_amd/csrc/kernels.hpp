@@ -9,6 +9,11 @@ namespace sislice {
 
 constexpr int kSpecGroups = 256;  // workgroups of a shift's pivot-free panel, at most
 
+// Whole panels that are updated together, at most (W of all of them is kept).  Order 12288, 49
+// shifts: 880 ms with 2, 843 with 3, 795 with 6, 788 with 8; order 4096, 17 shifts: 23.6, 23.1,
+// 22.9, 23.1.
+constexpr int kDeferPanels = 6;
+
 // Words of one shift's team area (k_bk_team): the roster, then the mailboxes.
 constexpr int kTeamMax = 32;  // workgroups in a team
 constexpr int kTeamRow = 136;  // words of one workgroup's row
@@ -47,7 +52,7 @@ struct FactorPlan {
   int fast = 1;                    // use the pivot-free path
   int nbpiv = 32;                  // columns a pivoting panel handles after a rejection (default_nbpiv)
   int wide_min = 1024;             // trailing order from which the update takes 128x128 tiles
-  int defer = 0;                   // W has room for two panels: whole ones may be updated in pairs
+  int defer = 0;                   // whole panels whose updates may wait for one another (W has room)
   int stream_c = 0;                // the 128-tile update streams C (shift groups on two streams)
   int cus = 256;                   // compute units of the device (its persistent grid)
   int groups = 1;                  // shift groups run on separate streams (with readback)
@@ -63,8 +68,9 @@ void factor_launch(const FactorPlan& fp, hipStream_t st);
 // device tables only).
 void factor_shift_form_launch(const FactorPlan& fp, hipStream_t st);
 void factor_steps_launch(const FactorPlan& fp, hipStream_t st, bool readback);
-// Columns of W a shift needs, and whether updates in pairs can pay at all.
-bool factor_pairs(int n, int nb, int nshift, bool pivot);
+// Whole panels that may wait for one another (W then holds as many, 4 GiB of them at most,
+// so that a factorization which fills the memory still fits); 0: none.
+int factor_defers(int n, int nb, int nshift, bool pivot);
 // One-time kernel attributes of the factorization (outside any capture).
 void factor_prepare();
 

@@ -62,12 +62,12 @@ def test_more_shifts_than_workgroups_a_shift(gpu_lib, shifts):
         assert torch.equal(torch.tril(g.LD), torch.tril(facs[k].LD))
 
 
-@pytest.mark.parametrize("rows", [[], [0], [1], [2, 3], [5, 8, 9], [0, 1, 2, 3, 4, 5, 6, 7, 8], [31]])
-def test_paired_updates_equal_single_ones_bitwise(gpu_lib, rows):
-    """17 shifts of order 2085 are large enough for whole panels to be updated in pairs, one
-    shift alone is not.  The panels named get an entry that needs pivoting, so that pairs are
-    completed, caught up, left at the end or never begun."""
-    n, S = 2085, 17
+@pytest.mark.parametrize("rows", [[], [0], [1], [2, 3], [5, 8, 9], [6], [7, 19], [0, 1, 2, 3, 4, 5, 6, 7, 8], [31]])
+def test_waiting_updates_equal_single_ones_bitwise(gpu_lib, rows):
+    """17 shifts of order 2600 are large enough (down to 1987 rows) for whole panels to wait for one another, one
+    shift alone is not.  The panels named get an entry that needs pivoting, so that rows of
+    waiting panels are completed, caught up, left at the end or never begun."""
+    n, S = 2600, 17
     C = _dominant(n)
     for p in rows:
         i, j = 64 * p + 11, min(64 * p + 900, n - 1)
