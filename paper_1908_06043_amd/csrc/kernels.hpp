@@ -42,8 +42,7 @@ struct FactorPlan {
   int64_t* d_inertia = nullptr;  // device [3 * nshift]
   int* pstart_base = nullptr;    // device [nshift * npmax] panel starts
   int npmax = 0;
-  // pivot-free speculative panel path (per shift): staged L of the panel (n x nb),
-  // D of the panel, inverse of the diagonal block (nb x nb), column maxima
+  // pivot-free panel path (per shift): D of the panel and the columns that fail its test
   double* const* d_aux = nullptr;  // [nb] D | [kSpecGroups] rejected columns (a uint64 a workgroup)
   unsigned long long* d_team = nullptr;  // device [nshift * kTeamWords]: mailboxes of the panel teams
   unsigned* wait_err = nullptr;    // raised when a team's wait exceeds wait_limit polls
