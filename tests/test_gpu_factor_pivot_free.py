@@ -83,3 +83,14 @@ def test_waiting_updates_equal_single_ones_bitwise(gpu_lib, rows):
     f = facs[9]
     B = C - sig[9] * np.eye(n)
     assert backward_error(B, f.LD.cpu().numpy(), f.ipiv.cpu().numpy()) <= 100 * n * U
+
+
+@pytest.mark.parametrize("n,zero", [(200, 0), (200, 31), (200, 32), (300, 299), (2100, 64), (2100, 100)])
+def test_singular_b_is_refused(gpu_lib, n, zero):
+    """B's factorization takes no interchange: a zero pivot ends the accepted columns and the
+    panel goes on column by column; the planner refuses the pencil."""
+    A = inputs.random_symmetric(n, n + 1)
+    B = np.eye(n)
+    B[zero, zero] = 0.0
+    with pytest.raises(Exception, match="invalid argument"):
+        gpu_lib.plan_shifts_kpm(dev(A), dev(B), n // 10, 4)
