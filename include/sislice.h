@@ -146,15 +146,19 @@ sislice_status sislice_create(sislice_handle **h, int device, void *stream);
 sislice_status sislice_destroy(sislice_handle *h);
 sislice_status sislice_set_stream(sislice_handle *h, void *stream);
 
-/* Bound of the device-side waits.  The triangular solves of the shift-invert
- * step (Algorithm 2, third step) hand row blocks between workgroups, and a
- * workgroup polls for a block it needs; a poll that does not find it after
- * `polls` attempts (about 1 us each; default 2^21, about 2 s) gives up so that
- * the launch still completes, and the call that ran it (or, for the
+/* Bound of each device-side wait.  The triangular solves of the shift-invert
+ * step (Algorithm 2, third step) hand row blocks between workgroups, and the
+ * factorization's pivoting panels of many rows exchange pivot candidates between
+ * workgroups; a workgroup polls for what it needs, and a wait that has not found
+ * it after `polls` attempts (about 1 us each; default 2^21, about 2 s) gives up
+ * so that the launch still completes, and the call that ran it (or, for the
  * asynchronous sislice_ldlt_solve, the next synchronising call on the handle)
  * returns SISLICE_ERR_HIP.  Correct hand-offs complete in microseconds; the
- * bound only turns a logic fault into an error instead of a hung device.
- * polls in [0, 2^32 - 1]; applies to the handle and its batch workers. */
+ * bound only turns a logic fault into an error instead of a hung device.  With
+ * less than 2^16 polls the factorization's panels run on one workgroup each (the
+ * same factors, without waits), so a small bound fails no factorization.
+ * polls in [0, 2^32 - 1]; applies to the handle, its batch workers and the
+ * factorizations they captured earlier. */
 sislice_status sislice_set_wait_limit(sislice_handle *h, int64_t polls);
 
 /* Bunch-Kaufman LDL^T of C = A - sigma B (Sec. 2.1: the probe's major cost) and

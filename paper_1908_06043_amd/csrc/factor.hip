@@ -780,10 +780,12 @@ __global__ __launch_bounds__(1024) void k_bk_panel(int n, double* const* LDs, lo
 // of a column.
 //
 // The team must run at the same time.  Workgroups sign in to a roster; the one that
-// completes the team closes it, and if the team is not complete within about 20 us the
-// first one closes it for itself and runs the panel alone (bk_panel_rows) while late ones
-// leave.  So no workgroup ever waits for one that is not running, whatever else occupies
-// the device.  Every wait is bounded besides (wait_limit polls).
+// completes the team closes it, and if the team is not complete within about 20 us
+// (kTeamGather polls) the first one closes it for itself and runs the panel alone
+// (bk_panel_rows) while late ones leave.  So no workgroup ever waits for one that is not
+// running, whatever else occupies the device.  Every wait is bounded besides (wait_limit
+// unsuccessful polls each); with a limit that a running team could reach, no team gathers
+// (gather 0: the first one closes at once) and there is no wait to expire.
 struct TeamArgs {
   int n;
   double* const* LDs;
@@ -800,6 +802,7 @@ struct TeamArgs {
   unsigned long long* teams;
   unsigned* wait_err;
   unsigned wait_limit;
+  unsigned gather;        // polls for the team to gather; 0: it never does
   int nb, nbpiv, groups;  // groups: workgroups of k_fast_panel
   int defer;              // whole panels that may be updated together (0: each by itself)
 };
@@ -959,7 +962,7 @@ __global__ __launch_bounds__(NT) void k_bk_team(TeamArgs a) {
       sz = 0;
       if ((old & closed) || r >= need) {
         r = -1;
-      } else if (r == need - 1) {
+      } else if (r == need - 1 && a.gather) {
         if (!(__hip_atomic_fetch_or(roster, closed, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) & closed))
           __hip_atomic_store(size, (unsigned)need, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       }
@@ -968,7 +971,7 @@ __global__ __launch_bounds__(NT) void k_bk_team(TeamArgs a) {
         for (unsigned polls = 0;; ++polls) {
           sz = (int)__hip_atomic_load(size, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
           if (sz) break;
-          if (r == 0 && polls >= 40u &&
+          if (r == 0 && polls >= a.gather &&
               !(__hip_atomic_fetch_or(roster, closed, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) & closed)) {
             __hip_atomic_store(size, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             sz = 1;
@@ -1069,7 +1072,7 @@ __global__ __launch_bounds__(NT) void k_bk_team(TeamArgs a) {
     neg = __popcll(__ballot(negd));
     pos = __popcll(__ballot(acc && !negd));
   }
-  unsigned polls = 0;  // wavefront 0's unsuccessful polls in all; past the limit it goes on as it is
+  unsigned polls = 0;  // wavefront 0's unsuccessful polls of this wait; past the limit it goes on as it is
   auto expired = [&]() {
     if (polls++ < a.wait_limit) return false;
     __hip_atomic_store(a.wait_err, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -1149,6 +1152,7 @@ __global__ __launch_bounds__(NT) void k_bk_team(TeamArgs a) {
         const unsigned long long* ar = areaB(t);
         unsigned long long h0 = 0, h1 = 0, h2 = 0, t0 = 0, t1 = 0;
         const bool wh = lane < G, wt = rank > 0 && lane < NB;
+        polls = 0;
         for (;;) {
           if (wh && ((h0 >> 32) != tag || (h1 >> 32) != tag || (h2 >> 32) != tag)) {
             h0 = team_word(ar + 4 * lane);
@@ -1196,6 +1200,7 @@ __global__ __launch_bounds__(NT) void k_bk_team(TeamArgs a) {
         const unsigned long long* ar = areaR(t, max(own, 0));
         unsigned long long t0 = 0, t1 = 0, e0 = 0, e1 = 0;
         const bool wt = lane < NB, we = lane == 0;
+        polls = 0;
         for (;;) {
           if (wt && ((t0 >> 32) != tag || (t1 >> 32) != tag)) {
             t0 = team_word(ar + 2 * lane);
@@ -1239,6 +1244,7 @@ __global__ __launch_bounds__(NT) void k_bk_team(TeamArgs a) {
           if (rank == 0 && lane < NB) team_post(ar + 4 * kTeamMax + 2 * lane, tag, Wt[lane * LW + j + 1]);
           unsigned long long h0 = 0, h1 = 0, t0 = 0, t1 = 0, e0 = 0, e1 = 0;
           const bool wh = lane < G, wt = rank > 0 && lane < NB, we = lane == 0 && rank != own;
+          polls = 0;
           for (;;) {
             if (wh && ((h0 >> 32) != tag || (h1 >> 32) != tag)) {
               h0 = team_word(ar + 4 * lane);
@@ -1857,7 +1863,8 @@ static void panel_launch(const FactorPlan& fp, hipStream_t st, long rem_max, int
   long need;
   if (panel_team(fp, rem_max, need)) {
     TeamArgs a{n, fp.d_LD, fp.ldld, fp.d_W, fp.ldw, fp.d_perm, fp.d_sw, fp.d_blk, fp.d_colpanel,
-               fp.d_pstart, fp.d_state, fp.d_aux, fp.d_team, fp.wait_err, fp.wait_limit, nb, nbpiv, groups, defer};
+               fp.d_pstart, fp.d_state, fp.d_aux, fp.d_team, fp.wait_err, fp.wait_limit,
+               fp.wait_limit < kTeamMinLimit ? 0u : kTeamGather, nb, nbpiv, groups, defer};
     // As few threads as hold the rows: a column's reductions, tests and barriers cost every
     // wavefront the same instructions, so a SIMD's wavefronts take turns at them.  Five
     // shifts at order 1001, all panels: 1.52 ms with 1024 threads to the end, 1.04 so.

@@ -98,7 +98,7 @@ void check_waits(sislice_handle* h) {
   if (hv == 0) return;
   SL_HIP(hipMemsetAsync(h->wait_word, 0, sizeof(unsigned), h->stream));
   SL_HIP(hipStreamSynchronize(h->stream));
-  throw Error(SISLICE_ERR_HIP, "a triangular-solve hand-off wait exceeded its bound of " +
+  throw Error(SISLICE_ERR_HIP, "a device-side hand-off wait exceeded its bound of " +
                                    std::to_string(h->wait_limit) + " polls");
 }
 
@@ -266,7 +266,8 @@ void factor_run(sislice_handle* h, const FactorPlan& fp, hipStream_t st) {
   sislice_handle::FactorGraph* g = nullptr;
   for (auto& q : h->fgraphs)
     if (q.n == fp.n && q.S == fp.nshift && q.nb == fp.nb && q.nbpiv == fp.nbpiv &&
-        q.wide_min == fp.wide_min && q.ldld == fp.ldld && q.state == fp.d_state)
+        q.wide_min == fp.wide_min && q.ldld == fp.ldld && q.state == fp.d_state &&
+        q.wait_limit == fp.wait_limit)
       g = &q;
   if (!g) {
     factor_prepare();
@@ -283,6 +284,7 @@ void factor_run(sislice_handle* h, const FactorPlan& fp, hipStream_t st) {
     ng.wide_min = fp.wide_min;
     ng.ldld = fp.ldld;
     ng.state = fp.d_state;
+    ng.wait_limit = fp.wait_limit;
     hipError_t e = hipStreamBeginCapture(st, hipStreamCaptureModeThreadLocal);
     if (e == hipSuccess) {
       try {
@@ -301,7 +303,8 @@ void factor_run(sislice_handle* h, const FactorPlan& fp, hipStream_t st) {
     h->prof = prof;
     SL_HIP(e);
     SL_HIP(hipGraphInstantiate(&ng.exec, ng.graph, nullptr, nullptr, 0));
-    // a graph of the same shape over a workspace that has moved is stale
+    // a graph of the same shape over a workspace that has moved, or with another wait limit,
+    // is stale
     for (auto it = h->fgraphs.begin(); it != h->fgraphs.end();) {
       if (it->n == ng.n && it->S == ng.S && it->nb == ng.nb && it->nbpiv == ng.nbpiv &&
           it->wide_min == ng.wide_min) {

@@ -77,11 +77,13 @@ struct sislice_handle {
   int cur_nbpiv = 0, cur_wide_min = 0;
   // Captured factorization sequences (panel/update steps, interchanges, inertia)
   // replayed with hipGraphLaunch when graphs are on: one per (order, shift
-  // count, panel parameters) and factorization workspace.
+  // count, panel parameters) and factorization workspace, with the wait limit it was
+  // captured under.
   struct FactorGraph {
     int n = 0, S = 0, nb = 0, nbpiv = 0, wide_min = 0;
     long ldld = 0;
     const void* state = nullptr;  // the workspace the graph's kernels address
+    unsigned wait_limit = 0;
     hipGraph_t graph = nullptr;
     hipGraphExec_t exec = nullptr;
   };

@@ -19,6 +19,12 @@ constexpr int kTeamMax = 32;  // workgroups in a team
 constexpr int kTeamRow = 136;  // words of one workgroup's row
 constexpr int kTeamWords = 64 + 4 * (4 * kTeamMax + 128) + 2 * kTeamMax * kTeamRow;
 
+// Polls (about half a microsecond each) that the first workgroup gives its team to gather, and
+// the wait limit below which no team gathers: its members run at the same time and answer
+// within microseconds, so from here on (some 60 ms) only a fault lets a wait expire.
+constexpr unsigned kTeamGather = 40;
+constexpr unsigned kTeamMinLimit = 1u << 16;
+
 // One lock-step factorization of `nshift` shifted matrices of order n.
 struct FactorPlan {
   int n = 0, nshift = 0, nb = 32;
