@@ -65,6 +65,19 @@ def test_first_workgroup_alone_with_waiting_updates(gpu_lib):
         _same(f, g)
 
 
+@pytest.mark.parametrize("kind", ["random", "two_by_two", "ties"])
+def test_many_shifts_from_memory_equal_the_team(gpu_lib, kind):
+    """With 120 shifts of order 2100 the teams do not fit the device until 512 rows are left:
+    some 25 panels run from memory, one workgroup a shift, each after the interchanges of
+    those before.  One shift alone runs as a team throughout."""
+    n = 2100
+    A, I = dev(_matrix(kind, n)), dev(np.eye(n))
+    sig = [float(s) for s in np.linspace(-31.0, 29.0, 120)]
+    facs = gpu_lib.ldlt_factor_multi(A, I, sig)
+    for k in (0, 41, 60, 119):
+        _same(facs[k], gpu_lib.ldlt_factor(A, I, sig[k]))
+
+
 def test_captured_factorizations_follow_the_bound(gpu_lib):
     """On a stream of its own a solve replays its captured factorization.  Captured under a
     bound of zero (the sweeps' waits expire), it must not fail the solves that follow."""
