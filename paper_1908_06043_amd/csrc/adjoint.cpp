@@ -330,7 +330,6 @@ extern "C" sislice_status sislice_adjoint(sislice_handle* h, int64_t n, const do
     check_waits(h);
     return st;
   } catch (const Error& e) {
-    std::fprintf(stderr, "sislice: %s\n", e.what());
-    return e.status;
+    return error_status(h, e);
   }
 }

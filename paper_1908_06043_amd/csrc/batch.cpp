@@ -195,8 +195,9 @@ extern "C" sislice_status sislice_solve_batched(sislice_handle* h, int64_t count
             check_handle(w);
             pick[k] = tune_factor(w, problems[todo[k]], o);
           } catch (const Error& e) {
+            const Error r(error_status(w, e), e.what());
             std::lock_guard<std::mutex> lk(mu);
-            errs.push_back(e);
+            errs.push_back(r);
           }
         });
         set_current_handle(h);
@@ -239,8 +240,8 @@ extern "C" sislice_status sislice_solve_batched(sislice_handle* h, int64_t count
         check_waits(w);
         conv[i] = (status[i] == SISLICE_OK || status[i] == SISLICE_NOT_CONVERGED) ? rep.n_converged : 0;
       } catch (const Error& e) {
-        std::fprintf(stderr, "sislice: problem %d: %s\n", i, e.what());
-        status[i] = e.status;
+        std::fprintf(stderr, "sislice: problem %d:\n", i);
+        status[i] = error_status(w, e);
         w->cur_nbpiv = 0;
         w->cur_wide_min = 0;
       }

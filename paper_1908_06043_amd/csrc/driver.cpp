@@ -188,6 +188,7 @@ sislice_status plan_impl(sislice_handle* h, int64_t n64, const double* A, int64_
     SL_HIP(hipMemcpyAsync(inert, fp.d_inertia, sizeof(inert), hipMemcpyDeviceToHost, st));
     SL_HIP(hipStreamSynchronize(st));
     ring.synced();
+    check_factor(h, inert, 1);
     if (inert[0] != 0 || inert[1] != 0) throw Error(SISLICE_ERR_ARG, "B is not positive definite");
   }
   {
@@ -535,6 +536,7 @@ DriverWs driver_factor(sislice_handle* h, Ring& ring, int n, const double* A, lo
                         hipMemcpyDeviceToHost, st));
   SL_HIP(hipStreamSynchronize(st));
   ring.synced();
+  check_factor(h, w.inert.data(), S1);
   for (int s = 0; s < S1; ++s)
     if (w.inert[3 * s + 1] != 0) return w;  // singular: nothing is cached
   // the factorizations stay in the driver workspace for sislice_adjoint
@@ -612,6 +614,7 @@ sislice_status solve_impl(sislice_handle* h, int64_t n64, const double* A, int64
       SL_HIP(hipMemcpyAsync(&inert[3 * P], f1.d_inertia, sizeof(int64_t) * 3, hipMemcpyDeviceToHost, st));
       SL_HIP(hipStreamSynchronize(st));
       ring.synced();
+      check_factor(h, &inert[3 * P], 1);
       if (inert[3 * P + 1] != 0) inert[3 * P] = -1;  // exactly singular: step on
     }
     SL_CHECK_ARG(inert[3 * P] >= n_e, "no top boundary with n_e eigenvalues below it");
@@ -1541,6 +1544,7 @@ sislice_status solve_impl(sislice_handle* h, int64_t n64, const double* A, int64
       SL_HIP(hipMemcpyAsync(ni.data(), f.d_inertia, sizeof(int64_t) * 3 * Pn, hipMemcpyDeviceToHost, st));
       SL_HIP(hipStreamSynchronize(st));
       ring.synced();
+      check_factor(h, ni.data(), Pn);
       solve_prep_launch(n, Pn, reinterpret_cast<const int* const*>(ring.ptrs(nip)), ring.ptrs(nperm),
                         ring.ptrs(nblk), ring.cptrs(nLD), n, ring.ptrs(nLinv), st);
       // the merged shift set and the windows of the new probes in it
@@ -1822,8 +1826,7 @@ sislice_status sislice_plan_shifts_kpm(sislice_handle* h, int64_t n, const doubl
     SL_CHECK_ARG(A && B && lda >= n && ldb >= n && sigmas && omega_top, "bad argument");
     return plan_impl(h, n, A, lda, B, ldb, n_e, n_s, o, sigmas, omega_top, moments, bounds);
   } catch (const Error& e) {
-    std::fprintf(stderr, "sislice: %s\n", e.what());
-    return e.status;
+    return error_status(h, e);
   }
 }
 
@@ -1846,8 +1849,7 @@ sislice_status sislice_plan_shifts_lanczos(sislice_handle* h, int64_t n, const d
     return plan_impl(h, n, A, lda, B, ldb, n_e, n_s, o, sigmas, omega_top, nullptr, bounds, mode, k,
                      nv);
   } catch (const Error& e) {
-    std::fprintf(stderr, "sislice: %s\n", e.what());
-    return e.status;
+    return error_status(h, e);
   }
 }
 
@@ -1872,8 +1874,7 @@ sislice_status sislice_solve(sislice_handle* h, int64_t n, const double* A, int6
     check_waits(h);
     return st;
   } catch (const Error& e) {
-    std::fprintf(stderr, "sislice: %s\n", e.what());
-    return e.status;
+    return error_status(h, e);
   }
 }
 
@@ -1926,8 +1927,7 @@ sislice_status sislice_sisubit(sislice_handle* h, int64_t n, const double* A, in
     check_waits(h);
     return SISLICE_OK;
   } catch (const Error& e) {
-    std::fprintf(stderr, "sislice: %s\n", e.what());
-    return e.status;
+    return error_status(h, e);
   }
 }
 

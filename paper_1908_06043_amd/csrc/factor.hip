@@ -1777,11 +1777,13 @@ __global__ __launch_bounds__(1024) void k_left_gather(int n, double* const* LDs,
   for (int i = e + threadIdx.x; i < n; i += 1024) LD[i] = col[i - e];
 }
 
-// ipiv in the documented format and the inertia triple of every shift.
+// ipiv in the documented format and the inertia triple of every shift.  A factorization that
+// a wait's expiry spoiled, or whose steps ended before its columns, gets kSpoiledInertia or
+// kUnfinishedInertia for a count, which the host reads with the inertias (check_factor).
 __global__ __launch_bounds__(256) void k_factor_finalize(int n, const int* const* perms,
                                                          const int* const* blks, int* const* ipivs,
                                                          const FactorState* states,
-                                                         int64_t* inertia) {
+                                                         int64_t* inertia, const unsigned* wait_err) {
   const int s = blockIdx.y;
   const int* perm = global_ptr(perms[s]);
   const int* blk = global_ptr(blks[s]);
@@ -1791,7 +1793,7 @@ __global__ __launch_bounds__(256) void k_factor_finalize(int n, const int* const
     ipiv[i] = two ? -(perm[i] + 1) : perm[i];
   }
   if (blockIdx.x == 0 && threadIdx.x == 0) {
-    inertia[3 * s + 0] = states[s].neg;
+    inertia[3 * s + 0] = *wait_err ? kSpoiledInertia : (states[s].done ? states[s].neg : kUnfinishedInertia);
     inertia[3 * s + 1] = states[s].zero;
     inertia[3 * s + 2] = states[s].pos;
   }
@@ -1970,7 +1972,7 @@ static void factor_tail(const FactorPlan& fp, hipStream_t st) {
     SL_LAUNCH_CHECK();
   }
   SL_LAUNCH(k_factor_finalize, dim3((unsigned)ceil_div(n, 256), S), dim3(256), 0, st, n, fp.d_perm,
-            fp.d_blk, fp.d_ipiv, fp.d_state, fp.d_inertia);
+            fp.d_blk, fp.d_ipiv, fp.d_state, fp.d_inertia, fp.wait_err);
   SL_LAUNCH_CHECK();
 }
 

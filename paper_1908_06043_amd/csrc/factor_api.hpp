@@ -22,4 +22,9 @@ FactorPlan build_factor(sislice_handle* h, int bufid, int n, const double* A, lo
 // first use).
 void factor_run(sislice_handle* h, const FactorPlan& fp, hipStream_t st);
 
+// After the inertias of S factorizations were read back (3 counts each) and before anything
+// uses them: throws SISLICE_ERR_HIP, with the wait-error word cleared, when a device wait
+// expired or a factorization's steps ended before its columns.
+void check_factor(sislice_handle* h, const int64_t* inertia, int S);
+
 }  // namespace sislice

@@ -102,6 +102,25 @@ void check_waits(sislice_handle* h) {
                                    std::to_string(h->wait_limit) + " polls");
 }
 
+sislice_status error_status(sislice_handle* h, const Error& e) {
+  std::fprintf(stderr, "sislice: %s\n", e.what());
+  try {
+    check_waits(h);
+  } catch (const Error& w) {
+    std::fprintf(stderr, "sislice: %s\n", w.what());
+    return w.status;
+  }
+  return e.status;
+}
+
+void check_factor(sislice_handle* h, const int64_t* inertia, int S) {
+  for (int s = 0; s < S; ++s) {
+    if (inertia[3 * s] >= 0) continue;
+    check_waits(h);
+    throw Error(SISLICE_ERR_HIP, "a factorization did not complete");
+  }
+}
+
 hipStream_t group_stream(sislice_handle* h, int g) {
   while ((int)h->group_streams.size() <= g) {
     hipStream_t s = nullptr;
@@ -459,7 +478,7 @@ sislice_status sislice_ldlt_factor_multi(sislice_handle* h, int64_t n, const dou
                                          const double* B, int64_t ldb, int64_t n_shifts,
                                          const double* sigmas, double* const* LD, int64_t ldld,
                                          int32_t* const* ipiv, int64_t* inertia) {
-  SL_API_BEGIN
+  try {
   check_handle(h);
   SL_CHECK_ARG(n >= 0 && n <= (int64_t)1 << 20, "n out of range");
   SL_CHECK_ARG(n_shifts >= 1 && n_shifts <= 4096, "n_shifts out of range");
@@ -479,12 +498,17 @@ sislice_status sislice_ldlt_factor_multi(sislice_handle* h, int64_t n, const dou
   SL_HIP(hipMemcpyAsync(hi, fp.d_inertia, sizeof(int64_t) * 3 * n_shifts, hipMemcpyDeviceToHost,
                         h->stream));
   SL_HIP(hipStreamSynchronize(h->stream));
+  check_factor(h, hi, (int)n_shifts);
   bool singular = false;
   for (int64_t s = 0; s < 3 * n_shifts; ++s) inertia[s] = hi[s];
-  check_waits(h);
   for (int64_t s = 0; s < n_shifts; ++s) singular |= inertia[3 * s + 1] > 0;
   return singular ? SISLICE_SINGULAR_SHIFT : SISLICE_OK;
-  SL_API_END
+  } catch (const Error& e) {
+    return error_status(h, e);
+  } catch (const std::exception& e) {
+    std::fprintf(stderr, "sislice: %s\n", e.what());
+    return SISLICE_ERR_HIP;
+  }
 }
 
 sislice_status sislice_ldlt_factor(sislice_handle* h, int64_t n, const double* A, int64_t lda,

@@ -152,6 +152,9 @@ void* noalloc_scratch_setup(int device);
 // After a stream synchronisation: throws SISLICE_ERR_HIP (and clears the word)
 // when a device wait of an earlier launch expired.
 void check_waits(sislice_handle* h);
+// The status of a synchronising call that ended in `e`: an expired wait comes first, since `e`
+// may be what followed from it; the word is clear for the next call.
+sislice_status error_status(sislice_handle* h, const Error& e);
 inline unsigned next_epoch(sislice_handle* h) { return ++h->epoch; }
 
 // Kernel-class timing: prof_begin records an event before a launch on the

@@ -79,6 +79,10 @@ int factor_defers(int n, int nb, int nshift, bool pivot);
 // One-time kernel attributes of the factorization (outside any capture).
 void factor_prepare();
 
+// What the first inertia count holds of a factorization that is not one.
+constexpr int64_t kUnfinishedInertia = -1;
+constexpr int64_t kSpoiledInertia = -2;
+
 // Narrowest panel that is not the last one: a pivoting panel stops at nb - 1
 // columns (room for a closing 2x2 pivot) and, behind the pivot-free path, after
 // nbpiv columns from the first rejected one.

@@ -348,8 +348,7 @@ sislice_status sislice_scf_step(sislice_scf* s, const double* A, int64_t lda, co
     check_waits(h);
     return st;
   } catch (const Error& e) {
-    std::fprintf(stderr, "sislice: %s\n", e.what());
-    return e.status;
+    return error_status(s ? s->h : nullptr, e);
   }
 }
 

@@ -8,6 +8,7 @@ import pytest
 import torch
 
 from paper_1908_06043_amd import inputs
+from paper_1908_06043_amd._lib import SisliceError
 
 pytestmark = pytest.mark.gpu
 DEFAULT = 1 << 21
@@ -96,3 +97,37 @@ def test_captured_factorizations_follow_the_bound(gpu_lib):
         out = gpu_lib.solve(A, B, 120, 8, check=False)
         assert out["status"] == 0
     torch.cuda.synchronize()
+
+
+def _expired_solve(lib):
+    """Leaves the word of an expired wait behind an asynchronous solve."""
+    n = 1000
+    C = inputs.random_symmetric(n, 5)
+    f = lib.ldlt_factor(dev(C), dev(np.eye(n)), 0.0)
+    Y = dev(np.random.default_rng(1).standard_normal((n, 8)))
+    _limited(lib, 0, lambda: lib.ldlt_solve(f, Y))
+
+
+def _code(call):
+    try:
+        call()
+        return 0
+    except SisliceError as e:
+        return e.code
+
+
+def test_expired_wait_is_reported_once_by_the_next_synchronising_call(gpu_lib):
+    """By the first factorization that is read back, before its counts are used, and whatever
+    else would have ended the call; the call after it starts with a clear word."""
+    P = inputs.pencil_scf(600, 60, seed=1)
+    A, B = dev(P.A), dev(P.B)
+    bad = B.clone()
+    bad[100, 100] = -1.0
+    calls = [lambda: gpu_lib.plan_shifts_kpm(A, B, 60, 4), lambda: gpu_lib.solve(A, B, 60, 4),
+             lambda: gpu_lib.ldlt_factor(A, B, 0.1), lambda: gpu_lib.solve(A, bad, 60, 4)]
+    after = [0, 0, 0, -1]   # B is not positive definite
+    for call, st in zip(calls, after):
+        _expired_solve(gpu_lib)
+        assert _code(call) == -2
+        assert _code(call) == st
+        assert _code(call) == st
