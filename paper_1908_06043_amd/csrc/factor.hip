@@ -687,8 +687,9 @@ __device__ __forceinline__ void bk_panel_rows(int n, double* const* LDs, long ld
 }
 
 // Accepts the prefix, one workgroup a column, where no team follows (a team accepts for
-// itself).  Without pivoting the panel ends here: the workgroup that arrives last, when all have
-// read the state, writes it, or, where a column failed (a zero or non-finite pivot), goes on
+// itself).  Without pivoting the panel ends here: the workgroup that arrives last, when all of
+// the shift's (those past a ragged panel's columns as well) have read the state, writes it, or,
+// where a column failed (a zero or non-finite pivot), goes on
 // column by column after writing the accepted ones once more for itself.  That saves a launch
 // a panel: planning at order 2048 5.56 -> 5.48 ms, a solve of order 1000 18.0 -> 17.6.
 template <bool PIVOT>
@@ -705,7 +706,7 @@ __global__ __launch_bounds__(256) void k_fast_commit(int n, double* const* LDs, 
   const int k0 = st.k0 + st.kb;
   if (st.done || k0 >= n) return;
   const int nbe = min(nb, n - k0);
-  if (c >= nbe) return;
+  if (PIVOT && c >= nbe) return;
   const double* Dv = global_ptr(auxs[s]);
   const double* Wp = global_ptr(Wps[s]) + st.pend * ldw;
   double* LD = global_ptr(LDs[s]);
@@ -722,7 +723,7 @@ __global__ __launch_bounds__(256) void k_fast_commit(int n, double* const* LDs, 
     sh = (int)__hip_atomic_fetch_add(reinterpret_cast<unsigned*>(teams + (long)s * kTeamWords), 1u,
                                      __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   __syncthreads();
-  if (sh != nbe - 1) return;
+  if (sh != (int)gridDim.x - 1) return;
   if (threadIdx.x < 64) accept_state(states + s, Dv, js);
   if (js == nbe) {
     if (threadIdx.x == 0) {
