@@ -23,7 +23,10 @@ inline double ms_since(Clock::time_point t0) {
 // to the device in one copy, issued by the launch macro just before the next
 // kernel (stream order then delivers them first).  The host bytes stay untouched
 // until the stream has passed that copy: the ring is rewound only after a
-// stream synchronisation.
+// stream synchronisation.  The ring has two halves, and a full half goes on in the
+// other one: whatever put() returned stays whole until half a ring more has been
+// staged, so that several tables can be put, in part found staged already, and be
+// launched together later.
 // Rings nest (a driver that calls the planner): both use the handle's one ring
 // memory, so a nested ring first uploads the outer one's staged tables, waits
 // for the stream and rewinds the outer ring (whose earlier tables have all been
@@ -31,13 +34,12 @@ inline double ms_since(Clock::time_point t0) {
 // hands the launch hook back to the outer ring.
 class Ring {
  public:
-  explicit Ring(sislice_handle* h, size_t cap = 16u << 20) : h_(h), cap_(cap) {
+  explicit Ring(sislice_handle* h, size_t cap = 16u << 20) : h_(h), half_(cap / 2) {
     if (h->flush_fn == &Ring::flush_thunk && h->flush_ctx) {
       outer_ = static_cast<Ring*>(h->flush_ctx);
       outer_->flush();
       SL_HIP(hipStreamSynchronize(h->stream));
-      outer_->off_ = outer_->pend_ = 0;
-      outer_->seen_.clear();
+      outer_->restart(0);
     }
     if (h->ring_cap < cap) {
       if (h->ring_host) {
@@ -73,7 +75,7 @@ class Ring {
   void* put(const void* src, size_t bytes) {
     if (bytes == 0) bytes = 8;
     const size_t b = (bytes + 255) & ~size_t(255);
-    SL_CHECK_ARG(b <= cap_, "table too large for the upload ring");
+    SL_CHECK_ARG(b <= half_, "table too large for the upload ring");
     uint64_t key = 0;
     if (src) {
       key = 1469598103934665603ull ^ bytes;  // FNV-1a over the bytes
@@ -84,11 +86,10 @@ class Ring {
           std::memcmp(host_ + it->second.first, src, bytes) == 0)
         return dev_ + it->second.first;
     }
-    if (off_ + b > cap_) {
+    if (off_ + b > base_ + half_) {
       flush();
       SL_HIP(hipStreamSynchronize(h_->stream));
-      off_ = pend_ = 0;
-      seen_.clear();
+      restart(base_ ? 0 : half_);
     }
     if (src)
       std::memcpy(host_ + off_, src, bytes);
@@ -126,17 +127,21 @@ class Ring {
       flush();
       SL_HIP(hipStreamSynchronize(h_->stream));
     }
-    off_ = pend_ = 0;
-    seen_.clear();
+    restart(0);
   }
 
  private:
+  void restart(size_t base) {
+    base_ = off_ = pend_ = base;
+    seen_.clear();
+  }
   static void flush_thunk(void* self) { static_cast<Ring*>(self)->flush(); }
   sislice_handle* h_;
   Ring* outer_ = nullptr;
-  size_t cap_;
+  size_t half_;
   char* host_;
   char* dev_;
+  size_t base_ = 0;  // the half in use
   size_t off_ = 0;
   size_t pend_ = 0;
   std::unordered_map<uint64_t, std::pair<size_t, size_t>> seen_;  // key -> (offset, bytes)
