@@ -33,6 +33,7 @@ void* ws_get(sislice_handle* h, int id, size_t bytes) {
     }
     size_t cap = bytes + bytes / 8;
     if (hipMalloc(&b.ptr, cap) != hipSuccess) {
+      (void)hipGetLastError();  // not for the next launch's check
       b.ptr = nullptr;
       throw Error(SISLICE_ERR_ALLOC, "device workspace allocation failed");
     }
@@ -192,10 +193,10 @@ FactorPlan build_factor(sislice_handle* h, int bufid, int n, const double* A, lo
   const int nbpiv = h->cur_nbpiv > 0 ? h->cur_nbpiv : default_nbpiv(nb);
   const int npmax = factor_npanel_max(n, nb, nbpiv, defaults.fast != 0);
   const long ldw = n;
+  const int defer = h->lean_factor ? 0 : factor_defers(n, nb, S, pivot);
+  const int wcols = std::max(defer, 1) * nb + 2;
   Sizer z;
   z.take<double>(S);                          // sigmas
-  const int defer = factor_defers(n, nb, S, pivot);
-  const int wcols = std::max(defer, 1) * nb + 2;
   z.take<double>((size_t)S * ldw * wcols);  // W
   for (int q = 0; q < 4; ++q) z.take<int>((size_t)S * n);
   z.take<int>((size_t)S * npmax);
@@ -205,7 +206,16 @@ FactorPlan build_factor(sislice_handle* h, int bufid, int n, const double* A, lo
   z.take<void*>(10 * (size_t)S);
   z.take<double>((size_t)S * (nb + kSpecGroups));   // aux
   z.take<unsigned long long>((size_t)S * kTeamWords);
-  Carver c(ws_get(h, bufid, z.off));
+  void* ws = nullptr;
+  try {
+    ws = ws_get(h, bufid, z.off);
+  } catch (const Error& e) {
+    if (e.status != SISLICE_ERR_ALLOC || defer == 0) throw;
+    // the W of several panels does not fit beside the factors: one at a time, from now on
+    h->lean_factor = true;
+    return build_factor(h, bufid, n, A, lda, B, ldb, S, sigmas_host, LD_host, ldld, ipiv_host, nb, pivot);
+  }
+  Carver c(ws);
   FactorPlan fp;
   fp.n = n;
   fp.nshift = S;

@@ -75,6 +75,8 @@ struct sislice_handle {
   std::map<int, FactorTune> tuned;
   // panel parameters for the next factorizations (0: the library defaults)
   int cur_nbpiv = 0, cur_wide_min = 0;
+  // no room for the W of several panels once: factorizations keep one panel's
+  bool lean_factor = false;
   // Captured factorization sequences (panel/update steps, interchanges, inertia)
   // replayed with hipGraphLaunch when graphs are on: one per (order, shift
   // count, panel parameters) and factorization workspace, with the wait limit it was
