@@ -162,6 +162,6 @@ def load():
 
 
 class SisliceError(RuntimeError):
-    def __init__(self, code, where):
+    def __init__(self, code, where, detail=""):
         self.code = code
-        super().__init__(f"{where}: status {code} ({STATUS.get(code, 'unknown')})")
+        super().__init__(f"{where}: status {code} ({STATUS.get(code, 'unknown')})" + (f": {detail}" if detail else ""))

@@ -321,8 +321,10 @@ def solve_batched(pencils, opts=None, workers=0, check=True):
     rep = BatchReport()
     st = _lib.load().sislice_solve_batched(handle(dev_index), count, probs, C.byref(o), int(workers),
                                           status.ctypes.data_as(_lib.c_int32_p), C.byref(rep))
-    if check:
-        _check(st, "sislice_solve_batched")
+    if check and st != 0:
+        failed = [f"pencil {i} of order {p[0].shape[0]}: status {status[i]} ({_lib.STATUS.get(int(status[i]), 'unknown')})"
+                  for i, p in enumerate(pencils) if status[i] != 0]
+        raise SisliceError(st, "sislice_solve_batched", "; ".join(failed))
     for i, d in enumerate(outs):
         d["status"] = int(status[i])
         d.pop("_keep")
