@@ -193,7 +193,6 @@ sislice_status adjoint_impl(sislice_handle* h, int n, const double* A, long lda,
       sa.n = n;
       sa.nshift = G;
       sa.nrhs = kAdjGroup;
-      sa.epoch = next_epoch(h);
       std::vector<double*> ld(G), li(G), yy(G), xx(G), zz(G), vv(G);
       std::vector<int*> pe(G), bl(G);
       for (int g = 0; g < G; ++g) {

@@ -958,7 +958,6 @@ sislice_status solve_impl(sislice_handle* h, int64_t n64, const double* A, int64
         sa.n = n;
         sa.nshift = na;
         sa.nrhs = b;
-        sa.epoch = next_epoch(h);
         sa.LD = ring.cptrs(act_vec(js, [&](int j) { return LD[j]; }));
         sa.ldld = n;
         sa.perm = ring.cptrs(act_vec(js, [&](int j) { return perm[j]; }));

@@ -738,14 +738,13 @@ __global__ __launch_bounds__(256) void k_fast_commit(int n, double* const* LDs, 
                             nbpiv, s, 0);
 }
 
-template <bool PIVOT>
 __global__ __launch_bounds__(1024) void k_bk_panel(int n, double* const* LDs, long ldld,
                                                    double* const* Wps, long ldw, int* const* perms,
                                                    int* const* swps, int* const* blks,
                                                    int* const* colpanels, int* const* pstarts,
                                                    FactorState* states, int nb, int nbpiv, int defer) {
-  bk_panel_rows<PIVOT, 1024>(n, LDs, ldld, Wps, ldw, perms, swps, blks, colpanels, pstarts, states,
-                             nb, nbpiv, blockIdx.x, defer);
+  bk_panel_rows<true, 1024>(n, LDs, ldld, Wps, ldw, perms, swps, blks, colpanels, pstarts, states,
+                            nb, nbpiv, blockIdx.x, defer);
 }
 
 // The pivoting panel with the panel's L in registers: every thread holds one row, a
@@ -1602,7 +1601,6 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(8))) void 
   double* LD = global_ptr(LDs[s]);
   const double* Wp = global_ptr(Wps[s]) + w0 * ldw;
   const int lr = l & 15, lk = l >> 4;
-  const int nks = (kb + 3) >> 2;             // k-steps of 4
   const int nch = (kb + kUpdK - 1) / kUpdK;  // staged chunks
   // staging: thread t fetches row (t % 128) of columns (t / 128) + 8j, j < 2
   const int sr = tid & 127, sc = w >> 1;
@@ -1850,19 +1848,13 @@ static FactorPlan factor_subplan(const FactorPlan& fp, int s0, int cnt) {
 // groups), otherwise one workgroup a shift runs the panel from memory.
 static bool panel_team(const FactorPlan& fp, long rem_max, long& need) {
   need = rem_max <= (fp.nb > 32 ? 512 : 1024) ? 1 : ceil_div(rem_max, 512);
-  return fp.pivot && fp.team && fp.fast &&
+  return fp.pivot &&
          (need <= 1 || (need <= kTeamMax && need * fp.nshift <= (long)fp.cus * 7 / 8 / fp.groups));
 }
 
 static void panel_launch(const FactorPlan& fp, hipStream_t st, long rem_max, int nbpiv, int groups, int defer) {
   const int n = fp.n, S = fp.nshift, nb = fp.nb;
-  if (!fp.pivot) {
-    if (fp.fast) return;  // (k_fast_commit ends the panel)
-    SL_LAUNCH(k_bk_panel<false>, dim3(S), dim3(1024), 0, st, n, fp.d_LD, fp.ldld, fp.d_W, fp.ldw,
-              fp.d_perm, fp.d_sw, fp.d_blk, fp.d_colpanel, fp.d_pstart, fp.d_state, nb, nbpiv, defer);
-    SL_LAUNCH_CHECK();
-    return;
-  }
+  if (!fp.pivot) return;  // (k_fast_commit ends the panel)
   long need;
   if (panel_team(fp, rem_max, need)) {
     TeamArgs a{n, fp.d_LD, fp.ldld, fp.d_W, fp.ldw, fp.d_perm, fp.d_sw, fp.d_blk, fp.d_colpanel,
@@ -1891,7 +1883,7 @@ static void panel_launch(const FactorPlan& fp, hipStream_t st, long rem_max, int
       SL_LAUNCH((k_bk_team<32, 1024, false>), team, dim3(1024), 0, st, a);
     }
   } else {
-    SL_LAUNCH(k_bk_panel<true>, dim3(S), dim3(1024), 0, st, n, fp.d_LD, fp.ldld, fp.d_W, fp.ldw,
+    SL_LAUNCH(k_bk_panel, dim3(S), dim3(1024), 0, st, n, fp.d_LD, fp.ldld, fp.d_W, fp.ldw,
               fp.d_perm, fp.d_sw, fp.d_blk, fp.d_colpanel, fp.d_pstart, fp.d_state, nb, nbpiv, defer);
   }
   SL_LAUNCH_CHECK();
@@ -1917,34 +1909,28 @@ static void update_tiles_launch(const FactorPlan& fp, hipStream_t st, long rem, 
 static void factor_step(const FactorPlan& fp, hipStream_t st, long k0_lb, sislice_handle* ph,
                         hipEvent_t after_panel, int defer = 0, bool pending = false) {
   const int n = fp.n, S = fp.nshift, nb = fp.nb;
-  const int nbpiv = fp.fast ? fp.nbpiv : nb;
-  const int min_kb = factor_min_panel(nb, fp.nbpiv, fp.fast != 0);
-  int tpan = -1;
-  int groups = 0;
-  if (fp.fast) {
-    // one timed ticket per panel step: the speculative group and the pivoting
-    // panel are consecutive launches of the panel class
-    tpan = prof_begin(ph, kProfPanel, st);
-    // a workgroup per 256 rows below the block, as many as run side by side (two a CU)
-    groups = (int)std::max<long>(
-        1, std::min<long>({ceil_div(n - k0_lb - 1, 256), (long)kSpecGroups, 2l * fp.cus / S}));
-    const auto panel = nb > 32 ? (fp.pivot ? k_fast_panel<64, true> : k_fast_panel<64, false>)
-                               : (fp.pivot ? k_fast_panel<32, true> : k_fast_panel<32, false>);
-    SL_LAUNCH(panel, dim3((unsigned)groups, S), dim3(320), 0, st, n, (const double* const*)fp.d_LD,
-              fp.ldld, fp.d_W, fp.ldw, fp.d_aux, fp.d_state, fp.d_team, nb);
-    SL_LAUNCH_CHECK();
-    long need;
-    if (pending) update_tiles_launch(fp, st, n - k0_lb, groups);  // a panel that is not whole
-    if (!panel_team(fp, n - k0_lb, need)) {
-      SL_LAUNCH(fp.pivot ? k_fast_commit<true> : k_fast_commit<false>, dim3(nb, S), dim3(256), 0, st, n,
-                fp.d_LD, fp.ldld, fp.d_W, fp.ldw, (const double* const*)fp.d_aux, fp.d_perm, fp.d_sw,
-                fp.d_blk, fp.d_colpanel, fp.d_pstart, fp.d_state, fp.d_team, nb, nbpiv, groups);
-      SL_LAUNCH_CHECK();
-    }
-  }
-  if (tpan < 0) tpan = prof_begin(ph, kProfPanel, st);
-  panel_launch(fp, st, n - k0_lb, nbpiv, groups, defer);
+  const int nbpiv = fp.nbpiv;
+  const int min_kb = factor_min_panel(nb, nbpiv);
+  // one timed ticket per panel step: the pivot-free group and the pivoting panel are
+  // consecutive launches of the panel class
+  const int tpan = prof_begin(ph, kProfPanel, st);
+  // a workgroup per 256 rows below the block, as many as run side by side (two a CU)
+  const int groups = (int)std::max<long>(
+      1, std::min<long>({ceil_div(n - k0_lb - 1, 256), (long)kSpecGroups, 2l * fp.cus / S}));
+  const auto panel = nb > 32 ? (fp.pivot ? k_fast_panel<64, true> : k_fast_panel<64, false>)
+                             : (fp.pivot ? k_fast_panel<32, true> : k_fast_panel<32, false>);
+  SL_LAUNCH(panel, dim3((unsigned)groups, S), dim3(320), 0, st, n, (const double* const*)fp.d_LD,
+            fp.ldld, fp.d_W, fp.ldw, fp.d_aux, fp.d_state, fp.d_team, nb);
   SL_LAUNCH_CHECK();
+  long need;
+  if (pending) update_tiles_launch(fp, st, n - k0_lb, groups);  // a panel that is not whole
+  if (!panel_team(fp, n - k0_lb, need)) {
+    SL_LAUNCH(fp.pivot ? k_fast_commit<true> : k_fast_commit<false>, dim3(nb, S), dim3(256), 0, st, n,
+              fp.d_LD, fp.ldld, fp.d_W, fp.ldw, (const double* const*)fp.d_aux, fp.d_perm, fp.d_sw,
+              fp.d_blk, fp.d_colpanel, fp.d_pstart, fp.d_state, fp.d_team, nb, nbpiv, groups);
+    SL_LAUNCH_CHECK();
+  }
+  panel_launch(fp, st, n - k0_lb, nbpiv, groups, defer);
   prof_end(ph, tpan, st);
   if (after_panel) SL_HIP(hipEventRecord(after_panel, st));
   const long k1_lb = std::min<long>(n, k0_lb + min_kb);
@@ -2000,8 +1986,8 @@ void factor_steps_launch(const FactorPlan& fp, hipStream_t st, bool readback) {
                      fp.d_state, fp.d_perm, fp.d_sw, fp.d_team);
   SL_LAUNCH_CHECK();
   sislice_handle* ph = current_handle();
-  const int min_kb = factor_min_panel(nb, fp.nbpiv, fp.fast != 0);
-  const int step_cap = factor_npanel_max(n, nb, fp.nbpiv, fp.fast != 0);
+  const int min_kb = factor_min_panel(nb, fp.nbpiv);
+  const int step_cap = factor_npanel_max(n, nb, fp.nbpiv);
   SL_CHECK_ARG(step_cap <= fp.npmax, "panel bookkeeping smaller than the step bound");
   if (!readback) {
     // a fixed sequence (for graph capture): every step up to the bound; steps

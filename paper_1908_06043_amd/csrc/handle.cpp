@@ -189,9 +189,8 @@ FactorPlan build_factor(sislice_handle* h, int bufid, int n, const double* A, lo
                         const double* B, long ldb, int S, const double* sigmas_host,
                         double* const* LD_host, long ldld, int32_t* const* ipiv_host, int nb,
                         bool pivot) {
-  const FactorPlan defaults;
   const int nbpiv = h->cur_nbpiv > 0 ? h->cur_nbpiv : default_nbpiv(nb);
-  const int npmax = factor_npanel_max(n, nb, nbpiv, defaults.fast != 0);
+  const int npmax = factor_npanel_max(n, nb, nbpiv);
   const long ldw = n;
   const int defer = h->lean_factor ? 0 : factor_defers(n, nb, S, pivot);
   const int wcols = std::max(defer, 1) * nb + 2;

@@ -18,9 +18,8 @@ struct sislice_handle {
   Buf bufs[11];
   void* host_stage = nullptr;  // pinned staging for small host<->device records
   size_t host_cap = 0;
-  unsigned* sync = nullptr;  // epoch flags and ticket counters of the persistent solves
+  unsigned* sync = nullptr;  // ticket counters of the persistent solves
   size_t sync_cap = 0;       // in unsigned words
-  unsigned epoch = 0;
   // bounded device waits: polls before a waiter gives up, and the device word it
   // raises then (allocated on first use, zero while no wait has expired)
   unsigned wait_limit = 1u << 21;
@@ -157,7 +156,6 @@ void check_waits(sislice_handle* h);
 // The status of a synchronising call that ended in `e`: an expired wait comes first, since `e`
 // may be what followed from it; the word is clear for the next call.
 sislice_status error_status(sislice_handle* h, const Error& e);
-inline unsigned next_epoch(sislice_handle* h) { return ++h->epoch; }
 
 // Kernel-class timing: prof_begin records an event before a launch on the
 // handle's stream and returns a ticket; prof_end records the closing event.

@@ -53,8 +53,6 @@ struct FactorPlan {
   unsigned long long* d_team = nullptr;  // device [nshift * kTeamWords]: mailboxes of the panel teams
   unsigned* wait_err = nullptr;    // raised when a team's wait exceeds wait_limit polls
   unsigned wait_limit = 0;
-  int team = 1;                    // pivoting panels by teams of workgroups (L in registers)
-  int fast = 1;                    // use the pivot-free path
   int nbpiv = 32;                  // columns a pivoting panel handles after a rejection (default_nbpiv)
   int wide_min = 1024;             // trailing order from which the update takes 128x128 tiles
   int defer = 0;                   // whole panels whose updates may wait for one another (W has room)
@@ -86,15 +84,15 @@ constexpr int64_t kSpoiledInertia = -2;
 // Narrowest panel that is not the last one: a pivoting panel stops at nb - 1
 // columns (room for a closing 2x2 pivot) and, behind the pivot-free path, after
 // nbpiv columns from the first rejected one.
-inline int factor_min_panel(int nb, int nbpiv, bool fast) {
-  const int w = fast ? std::min(nbpiv, nb - 1) : nb - 1;
+inline int factor_min_panel(int nb, int nbpiv) {
+  const int w = std::min(nbpiv, nb - 1);
   return w < 1 ? 1 : w;
 }
 
 // Upper bound on the number of panel steps (and so on the panels) of one
 // factorization; sizes the panel-start and interchange-snapshot arrays.
-inline int factor_npanel_max(int n, int nb, int nbpiv, bool fast) {
-  return (int)ceil_div(n, factor_min_panel(nb, nbpiv, fast)) + 2;
+inline int factor_npanel_max(int n, int nb, int nbpiv) {
+  return (int)ceil_div(n, factor_min_panel(nb, nbpiv)) + 2;
 }
 
 }  // namespace sislice

@@ -12,7 +12,6 @@ constexpr int kSolveGroup = 16;    // its columns per group: one MFMA tile
 
 struct SolveArgs {
   int n = 0, nshift = 0, nrhs = 0;
-  unsigned epoch = 0;            // strictly increasing per launch pair
   const double* const* LD = nullptr;
   long ldld = 0;
   const int* const* perm = nullptr;
