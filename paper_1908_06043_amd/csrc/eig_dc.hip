@@ -34,6 +34,7 @@
 // (Ritz values from 3 to 5000) components of the small ones' vectors along each other
 // 1e-16 against 9e-15.
 #include <algorithm>
+#include <cfloat>
 #include <type_traits>
 #include <utility>
 
@@ -261,9 +262,11 @@ __global__ __launch_bounds__(NT) void k_eig_dc(EigArgs a, double* __restrict__ r
       const int r = min(max(i, j), m - 1), cc = min(min(i, j), m - 1);
       const double v = Ain[r + (long)cc * lda];
       x[c][h] = (i < m && j < m) ? v : 0.0;
-      mx = fmax(mx, fabs(x[c][h]));
+      mx = fmax(mx, fabs(x[c][h]) <= DBL_MAX ? fabs(x[c][h]) : INFINITY);
     }
-  // entries whose squares leave the range are brought back by a power of two
+  // An entry that is not finite makes every result NaN.  Otherwise the largest entry is brought
+  // to between 1e-20 and 1e20 by a power of two: what is below 1e-100 then (squares leave the
+  // range) is far below its rounding, and is dropped by the reduction and the deflation.
   mx = fmax(mx, dpp<0xB1>(mx));
   mx = fmax(mx, dpp<0x4E>(mx));
   mx = fmax(mx, dpp<0x141>(mx));
@@ -273,8 +276,13 @@ __global__ __launch_bounds__(NT) void k_eig_dc(EigArgs a, double* __restrict__ r
   lds_barrier();
   mx = S.red[0];
   for (int k = 1; k < NW; ++k) mx = fmax(mx, S.red[k]);
+  if (mx > DBL_MAX) {  // uniform
+    for (int k = tid; k < m; k += NT) a.W[b][k] = NAN;
+    for (int k = tid; k < m * m; k += NT) a.V[b][k % m + (long)(k / m) * a.ldv] = NAN;
+    return;
+  }
   int ex = 0;
-  if (mx > 0.0 && mx < 1e308 && (mx < 1e-90 || mx > 1e90)) {
+  if (mx > 0.0 && (mx < 1e-20 || mx > 1e20)) {
     ex = ilogb(mx);
 #pragma unroll
     for (int c = 0; c < NB; ++c)
@@ -323,7 +331,7 @@ __global__ __launch_bounds__(NT) void k_eig_dc(EigArgs a, double* __restrict__ r
       const double sig = sum_wave((lane > k + 1 ? v0 * v0 : 0.0) + (lane + 64 > k + 1 ? v1 * v1 : 0.0));
       // H = I - u u^T / h maps the column to beta e_{k+1}; u = the column with alpha - beta
       double beta = alpha, hinv = 0.0;
-      if (sig > 0.0) {
+      if (sig > 1e-200) {
         const double n2 = fma(alpha, alpha, sig), nr = n2 * rsq2(n2);
         beta = -copysign(nr, alpha);
         hinv = rcp2(fma(nr, fabs(alpha), n2));
@@ -442,7 +450,7 @@ __global__ __launch_bounds__(NT) void k_eig_dc(EigArgs a, double* __restrict__ r
     double tol = 0.0;
     bool nd = false;
     if (merging) {
-      tol = 8.0 * kEps * fmax(fmax(fabs(S.dl[s0]), fabs(S.dl[s2 - 1])), rho);
+      tol = 8.0 * kEps * fmax(fmax(fabs(S.dl[s0]), fabs(S.dl[s2 - 1])), fmax(rho, 1e-120));
       nd = rho * fabs(S.zl[i]) > tol;
       if (q == 0) {
         S.nd[i] = nd ? 1 : 0;
@@ -466,7 +474,7 @@ __global__ __launch_bounds__(NT) void k_eig_dc(EigArgs a, double* __restrict__ r
       const int t0 = seg(g, m, lv), t1 = seg(2 * g + 1, m, lv + 1), t2 = seg(g + 1, m, lv);
       if (!(t0 < t1 && t1 < t2) || !S.cl[t0]) continue;  // uniform
       const double rg = 2.0 * fabs(S.e[t1 - 1]);
-      const double tg = 8.0 * kEps * fmax(fmax(fabs(S.dl[t0]), fabs(S.dl[t2 - 1])), rg);
+      const double tg = 8.0 * kEps * fmax(fmax(fabs(S.dl[t0]), fabs(S.dl[t2 - 1])), fmax(rg, 1e-120));
       // each rotation changes the next test; every lane follows the same steps, lane 0 writes
       int pr = -1, nr = 0;
       for (int p = t0; p < t2; ++p) {
