@@ -50,7 +50,9 @@ typedef struct sislice_handle sislice_handle;
 typedef struct {
   int32_t block;         /* Lanczos block size b (8)                                   */
   int32_t max_basis;     /* active Lanczos basis cap, multiple of block, <= 112 (112)   */
-  int32_t max_cycles;    /* restart cycles per probe before NOT_CONVERGED (40)           */
+  int32_t max_cycles;    /* restart cycles per probe before NOT_CONVERGED (40); a probe  */
+                         /* whose shift all but coincides with an eigenvalue may begin   */
+                         /* again, up to four times, and then has all of them            */
   int32_t kpm_moments;   /* Chebyshev moments of the DOS estimate (64)                   */
   int32_t kpm_vectors;   /* Rademacher probe vectors (20)                                */
   int32_t bounds_steps;  /* Lanczos steps of the spectral-bounds estimate (30)           */
@@ -518,10 +520,12 @@ sislice_status sislice_sym_eig_var(sislice_handle *h, int32_t batch, const int32
                                    int32_t mmax, const double *A, int64_t lda, double *W,
                                    double *V);
 
-/* The eigensolver of the solve path's projected problems (Rayleigh-Ritz and the Lanczos
- * matrices, Sec. 2.1): Householder tridiagonalisation and divide and conquer.  Arguments
+/* The eigensolver of the solve path's iteration (the Lanczos matrices, and the B-Gram
+ * matrices of Rayleigh-Ritz, Sec. 2.1; the last Rayleigh-Ritz matrix goes to the solver of
+ * sislice_sym_eig_var): Householder tridiagonalisation and divide and conquer.  Arguments
  * as sislice_sym_eig_var.  Eigenvalues and residuals are accurate to rounding of the
- * matrix's norm, the eigenvectors orthogonal to working precision.  The reflectors
+ * matrix's norm, the eigenvectors orthogonal to working precision; a matrix with an entry
+ * that is not finite gives NaN throughout.  The reflectors
  * are kept in a workspace of the handle (100 KB per matrix of order 112, at most
  * 64 MB; larger batches run in chunks). */
 sislice_status sislice_proj_eig(sislice_handle *h, int32_t batch, const int32_t *m, int32_t mmax,

@@ -118,7 +118,7 @@ sislice_handle::FactorTune tune_factor(sislice_handle* w, const sislice_problem&
     time_cfg(t);
   }
   w->fc.id = 0;  // the timing factorizations are not a solve's
-  if (singular) {  // a singular point: keep the defaults
+  if (singular) {  // a singular point: keep what the search starts from
     best.nb = default_nb((int)p.n);
     best.nbpiv = 32;
     best.wide_min = 1024;

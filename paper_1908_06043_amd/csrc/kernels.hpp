@@ -35,7 +35,7 @@ struct FactorPlan {
   const double* d_sigmas = nullptr;  // device [nshift]
   double* const* d_LD = nullptr;     // device table of nshift device pointers
   long ldld = 0;
-  double* const* d_W = nullptr;  // panel buffers n x (nb + 2)
+  double* const* d_W = nullptr;  // panel buffers n x (max(defer, 1) nb + 2)
   long ldw = 0;
   int* const* d_perm = nullptr;
   int* const* d_sw = nullptr;

@@ -9,8 +9,8 @@
 //
 // Each GPU holds its own copy of the array; its address on a device is taken
 // once, when the first handle on that device is created, and used from then
-// on.  The array keeps the contents of the last call; the ticket counter that
-// must start at zero is cleared by that same kernel at the start of each call.
+// on.  The array keeps the contents of the last call; the ticket counters
+// that must start at zero are cleared by a kernel at the start of each call.
 // Calls that overlap on one GPU (two streams, two handles) share the array and
 // race.
 #include <mutex>
